@@ -323,105 +323,350 @@ __global__ void k_castv(long n, const double *a, T *b) {
 }
 
 // ------------------------------------------------------------- coarsest
-__global__ void k_to_dense(int n, const int *rp, const int *col, const double *val, double *a) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    for (int j = 0; j < n; j++) a[(long)i * n + j] = 0.0;
-    for (int z = rp[i]; z < rp[i + 1]; z++) a[(long)i * n + col[z]] += val[z];
+// One workgroup per row of the dense matrix.
+__global__ void k_to_dense(int n, const int *rp, const int *col, const double *val, double *a,
+                           int *pos) {
+    int i = blockIdx.x;
+    double *row = a + (long)i * n;
+    for (int j = threadIdx.x; j < n; j += blockDim.x) row[j] = 0.0;
+    if (threadIdx.x == 0) pos[i] = i;
+    __syncthreads();
+    // a row's columns are distinct
+    for (int z = rp[i] + (int)threadIdx.x; z < rp[i + 1]; z += blockDim.x) row[col[z]] = val[z];
 }
 
-// LU with partial pivoting (largest magnitude, ties to the smaller row) by
-// one workgroup, in place (unit L below the diagonal, U on and above).
-__global__ __launch_bounds__(1024) void k_dense_lu(int n, double *a, int *piv, int *status) {
-    __shared__ double sv[1024];
-    __shared__ int si[1024];
-    int tid = threadIdx.x, nt = blockDim.x;
-    for (int k = 0; k < n; k++) {
+// LU with partial pivoting (largest magnitude, ties to the smaller position)
+// in panels of NB columns: k_lu_panel (one workgroup) factorises the panel,
+// k_lu_update (many workgroups) applies it to the columns right of it.  Rows
+// never move: pos[r] is the position a row has or is at present, row[k] the
+// row chosen at position k.  L stays in the rows of `a`; every pivot row's U
+// part goes to u[k].  Each entry receives its updates one pivot at a time in
+// ascending order, as the unblocked algorithm does, so the factors are the
+// same.
+// What bounds it: a chain of n pivot steps.  One workgroup doing the whole
+// matrix read it from L2 at every step (about 450 rows: 6.8 ms); with the
+// panel in registers a step is one reduction, two barriers and at most NB
+// multiply-subtracts, and the rest of the matrix is updated once per panel by
+// the whole chip (the same matrix: 13 panels of 40 us, 12 updates of 22 us).
+// The state of a panel workgroup: RPT rows per thread, their panel columns
+// from the current pivot's on in registers (column kk of the panel is r[q][0]
+// when its turn comes), and the rows' positions.
+template <int T, int RPT, int NB>
+struct LuPanel {
+    double r[RPT][NB];
+    int ps[RPT];
+    double (*sv)[T / 64], (*prow)[NB];
+    int (*si)[T / 64];
+};
+
+// Pivots kk .. kk + 7 (below nb) with at most W panel columns left; false
+// when a pivot is zero or not a number (the same in every thread).
+template <int T, int RPT, int NB, int W>
+__device__ __forceinline__ bool lu_steps(LuPanel<T, RPT, NB> &S, int n, int k0, int kk, int nb,
+                                         double *a, double *u, int *row) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int end = min(kk + 8, nb);
+    for (; kk < end; kk++) {
+        const int k = k0 + kk, buf = kk & 1;
         double best = -1.0;
         int bi = n;
-        for (int i = k + tid; i < n; i += nt) {
-            double v = fabs(a[(long)i * n + k]);
-            if (v > best || (v == best && i < bi)) { best = v; bi = i; }
-        }
-        sv[tid] = best;
-        si[tid] = bi;
+        // selects, not branches: this is the step's chain
+        auto take = [&](double v, int i) {
+            bool t = (v > best) | ((v == best) & (i < bi));
+            best = t ? v : best;
+            bi = t ? i : bi;
+        };
+#pragma unroll
+        for (int q = 0; q < RPT; q++) take(S.ps[q] >= k ? fabs(S.r[q][0]) : -1.0, S.ps[q]);
+        take(dpp_move<DPP_XOR1>(best), dpp_move<DPP_XOR1>(bi));
+        take(dpp_move<DPP_XOR2>(best), dpp_move<DPP_XOR2>(bi));
+        take(dpp_move<DPP_HALF_MIRROR>(best), dpp_move<DPP_HALF_MIRROR>(bi));
+        take(dpp_move<DPP_ROR8>(best), dpp_move<DPP_ROR8>(bi));
+        take(__shfl_xor(best, 16, 64), __shfl_xor(bi, 16, 64));
+        take(__shfl_xor(best, 32, 64), __shfl_xor(bi, 32, 64));
+        if (lane == 0) { S.sv[buf][wid] = best; S.si[buf][wid] = bi; }
         __syncthreads();
-        for (int w = nt / 2; w > 0; w >>= 1) {
-            if (tid < w) {
-                double v = sv[tid + w];
-                int ii = si[tid + w];
-                if (v > sv[tid] || (v == sv[tid] && ii < si[tid])) { sv[tid] = v; si[tid] = ii; }
+        best = S.sv[buf][lane & (T / 64 - 1)];
+        bi = S.si[buf][lane & (T / 64 - 1)];
+        take(dpp_move<DPP_XOR1>(best), dpp_move<DPP_XOR1>(bi));
+        take(dpp_move<DPP_XOR2>(best), dpp_move<DPP_XOR2>(bi));
+        if (T >= 512) take(dpp_move<DPP_HALF_MIRROR>(best), dpp_move<DPP_HALF_MIRROR>(bi));
+        if (T >= 1024) take(dpp_move<DPP_ROR8>(best), dpp_move<DPP_ROR8>(bi));
+        if (!(best > 0.0)) return false;
+#pragma unroll
+        for (int q = 0; q < RPT; q++) {
+            if (S.ps[q] == bi) {
+#pragma unroll
+                for (int j = 0; j < W; j++) S.prow[buf][j] = S.r[q][j];
+                row[k] = (int)threadIdx.x + q * T;
             }
-            __syncthreads();
+            S.ps[q] = S.ps[q] == bi ? k : (S.ps[q] == k ? bi : S.ps[q]);
         }
-        int p = si[0];
-        double pv = sv[0];
         __syncthreads();
-        if (tid == 0) piv[k] = p;
-        if (pv == 0.0 || pv != pv) {
-            if (tid == 0) *status = 1;
-            return;
-        }
-        if (p != k)
-            for (int j = tid; j < n; j += nt) {
-                double t = a[(long)k * n + j];
-                a[(long)k * n + j] = a[(long)p * n + j];
-                a[(long)p * n + j] = t;
+        if ((int)threadIdx.x < min(W, nb - kk))
+            u[(long)k * n + k + threadIdx.x] = S.prow[buf][threadIdx.x];
+        double inv = 1.0 / S.prow[buf][0];
+#pragma unroll
+        for (int q = 0; q < RPT; q++) {
+            if (S.ps[q] > k) {
+                double l = S.r[q][0] * inv;
+                a[(long)((int)threadIdx.x + q * T) * n + k] = l;
+#pragma unroll
+                for (int j = 1; j < W; j++) S.r[q][j - 1] = S.r[q][j] - l * S.prow[buf][j];
             }
-        __syncthreads();
-        double inv = 1.0 / a[(long)k * n + k];
-        for (int i = k + 1 + tid; i < n; i += nt) a[(long)i * n + k] = a[(long)i * n + k] * inv;
-        __syncthreads();
-        long rem = (long)(n - k - 1) * (n - k - 1);
-        for (long t = tid; t < rem; t += nt) {
-            int i = k + 1 + (int)(t / (n - k - 1)), j = k + 1 + (int)(t % (n - k - 1));
-            double l = a[(long)i * n + k];
-            if (l != 0.0) a[(long)i * n + j] -= l * a[(long)k * n + j];
         }
-        __syncthreads();
+    }
+    if constexpr (W > 8) {
+        if (kk < nb) return lu_steps<T, RPT, NB, W - 8>(S, n, k0, kk, nb, a, u, row);
+    }
+    return true;
+}
+
+template <int T, int RPT, int NB>
+__global__ __launch_bounds__(T) void k_lu_panel(int n, int k0, double *a, double *u, int *pos,
+                                                int *row, int *status) {
+    __shared__ double sv[2][T / 64], prow[2][NB];
+    __shared__ int si[2][T / 64];
+    if (*status) return;
+    const int nb = min(NB, n - k0);
+    LuPanel<T, RPT, NB> S;
+    S.sv = sv;
+    S.prow = prow;
+    S.si = si;
+#pragma unroll
+    for (int q = 0; q < RPT; q++) {
+        int i = (int)threadIdx.x + q * T;
+        S.ps[q] = i < n ? pos[i] : -1;
+#pragma unroll
+        for (int j = 0; j < NB; j++)
+            S.r[q][j] = a[(long)min(i, n - 1) * n + k0 + min(j, nb - 1)];
+#pragma unroll
+        for (int j = 0; j < NB; j++) S.r[q][j] = j < nb ? S.r[q][j] : 0.0;
+    }
+    if (!lu_steps<T, RPT, NB, NB>(S, n, k0, 0, nb, a, u, row)) {
+        if (threadIdx.x == 0) *status = 1;
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < RPT; q++)
+        if (S.ps[q] >= k0) pos[(int)threadIdx.x + q * T] = S.ps[q];
+}
+
+// The columns right of a panel: a workgroup takes 64 columns and LU_R rows.
+// It solves its columns of U (unit lower triangle of the panel; a wavefront
+// takes 16 of the columns, its lanes a quarter of the remaining rows each;
+// written to u by the first row of workgroups), then subtracts the panel's
+// multiples from its rows that are still active.
+constexpr int LU_R = 32;
+template <int NB>
+__global__ __launch_bounds__(256, 2) void k_lu_update(int n, int k0, double *a, double *u,
+                                                      const int *pos, const int *row,
+                                                      const int *status) {
+    __shared__ double lt[NB][NB + 1], ut[NB][64], ls[LU_R][NB];
+    if (*status) return;
+    const int cx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int j0 = k0 + NB + blockIdx.x * 64, j = j0 + cx, i0 = blockIdx.y * LU_R;
+    for (int e = threadIdx.x; e < NB * NB; e += 256)
+        lt[e / NB][e % NB] = a[(long)row[k0 + e / NB] * n + k0 + e % NB];
+    for (int e = threadIdx.x; e < LU_R * NB; e += 256) {
+        int i = i0 + e / NB;
+        ls[e / NB][e % NB] = i < n ? a[(long)i * n + k0 + e % NB] : 0.0;
+    }
+    for (int k = ty; k < NB; k += 4) ut[k][cx] = j < n ? a[(long)row[k0 + k] * n + j] : 0.0;
+    __syncthreads();
+    {
+        const int col = 16 * ty + (cx & 15), g = cx >> 4;
+        for (int k = 0; k < NB; k++) {
+            double v = ut[k][col];
+            for (int i = k + 1 + g; i < NB; i += 4) ut[i][col] -= lt[i][k] * v;
+            // the next row of U is read by other lanes of this wavefront
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+    __syncthreads();
+    if (j >= n) return;
+    double uk[NB];
+#pragma unroll
+    for (int k = 0; k < NB; k++) uk[k] = ut[k][cx];
+    if (blockIdx.y == 0)
+        for (int k = ty; k < NB; k += 4) u[(long)(k0 + k) * n + j] = ut[k][cx];
+    for (int q = ty; q < LU_R; q += 4) {
+        int i = i0 + q;
+        if (i >= n || pos[i] < k0 + NB) continue;
+        double t = a[(long)i * n + j];
+#pragma unroll
+        for (int k = 0; k < NB; k++) t -= ls[q][k] * uk[k];
+        a[(long)i * n + j] = t;
     }
 }
 
-// Column c of the inverse from the LU factors, one wavefront per column:
-// x = P e_c, then the unit-lower and upper triangular solves, each row's
-// inner product split over the lanes (row i of the factors is read by every
-// column's wavefront, so it is served from L2) and summed by a fixed
-// butterfly.  Written column-major, invT[c*n + i] = (A^-1)_ic, so the
-// coarse solve reads it coalesced.
-__global__ __launch_bounds__(64) void k_dense_inv_col(int n, const double *a, const int *piv,
+// L below U in position order: u[k][j] = a[row[k]][j], j < k.
+__global__ void k_lu_gather(int n, const double *a, const int *row, double *u) {
+    int k = blockIdx.x;
+    const double *src = a + (long)row[k] * n;
+    for (int j = threadIdx.x; j < k; j += blockDim.x) u[(long)k * n + j] = src[j];
+}
+
+// Column c of the inverse from the LU factors f (position order), one
+// wavefront per column: x = P e_c, then the unit-lower and upper triangular
+// solves, each row's inner product split over the lanes (lane l holds x_l,
+// x_l+64, .. in registers) and summed by a fixed butterfly.  The rows are
+// taken in blocks of 64, so that the registers a row needs are fixed, and
+// requested AH rows before they are used.  What bounds it is the chain of
+// 2 n rows: a step is one row's products, one butterfly and one update (about
+// 450 rows: 0.20 ms; 1.0 ms with each row requested at its use and the
+// iterate in LDS, 0.28 ms with every register masked at every step, 0.39 ms
+// with two columns per wavefront).  Written column-major,
+// invT[c*n + i] = (A^-1)_ic, so the coarse solve reads it coalesced.
+template <int NR, int AH>
+__global__ __launch_bounds__(64) void k_dense_inv_col(int n, const double *f, const int *pos,
                                                       const int *status, double *invT) {
-    extern __shared__ double xs[];
     if (*status) return;             // singular: the factors are incomplete
-    int c = blockIdx.x, lane = threadIdx.x;
-    for (int i = lane; i < n; i += 64) xs[i] = i == c ? 1.0 : 0.0;
-    __syncthreads();
-    if (lane == 0)
-        for (int k = 0; k < n; k++) {
-            int p = piv[k];
-            if (p != k && p >= 0 && p < n) {
-                double t = xs[k];
-                xs[k] = xs[p];
-                xs[p] = t;
+    const int c = blockIdx.x, lane = threadIdx.x;
+    const int p = pos[c];
+    // x: right-hand side and forward solution; z: the solution, zero until
+    // known, so that neither inner product needs a mask
+    double x[NR], z[NR], w[AH][NR];
+#pragma unroll
+    for (int t = 0; t < NR; t++) {
+        x[t] = lane + 64 * t == p ? 1.0 : 0.0;
+        z[t] = 0.0;
+    }
+    // registers t0 .. t1 of row i of the factors (past the matrix: an end row)
+    auto fetch = [&](double (&b)[NR], int i, int t0, int t1) {
+        const double *r = f + (long)min(max(i, 0), n - 1) * n;
+#pragma unroll
+        for (int t = 0; t < NR; t++)
+            if (t >= t0 && t <= t1) b[t] = r[min(lane + 64 * t, n - 1)];
+    };
+    // forward: rows up to p would only add products with zeros
+#pragma unroll
+    for (int tb = 0; tb < NR; tb++) {
+        const int i1 = min(64 * tb + 64, n);
+        int i = max(64 * tb, p + 1);
+        if (i >= i1) continue;
+#pragma unroll
+        for (int q = 0; q < AH; q++) fetch(w[q], i + q, 0, tb);
+        for (; i < i1; i += AH) {
+#pragma unroll
+            for (int q = 0; q < AH; q++) {
+                if (i + q < i1) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int t = 0; t < NR; t++)
+                        if (t <= tb) s += w[q][t] * (t < tb || lane + 64 * t < i + q ? x[t] : 0.0);
+                    s = wave_sum_down(s);
+                    fetch(w[q], i + q + AH, 0, tb);
+                    x[tb] = lane + 64 * tb == i + q ? x[tb] - s : x[tb];
+                }
             }
         }
+    }
+#pragma unroll
+    for (int tb = NR - 1; tb >= 0; tb--) {
+        const int i1 = 64 * tb;
+        int i = min(64 * tb + 63, n - 1);
+        if (i < i1) continue;
+#pragma unroll
+        for (int q = 0; q < AH; q++) fetch(w[q], i - q, tb, NR - 1);
+        for (; i >= i1; i -= AH) {
+#pragma unroll
+            for (int q = 0; q < AH; q++) {
+                if (i - q >= i1) {
+                    double s = 0.0;
+#pragma unroll
+                    for (int t = 0; t < NR; t++)
+                        if (t >= tb) s += w[q][t] * z[t];
+                    s = wave_sum_down(s);
+                    double v = (x[tb] - s) / w[q][tb];
+                    z[tb] = lane + 64 * tb == i - q ? v : z[tb];
+                    fetch(w[q], i - q - AH, tb, NR - 1);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NR; t++)
+        if (lane + 64 * t < n) invT[(long)c * n + lane + 64 * t] = z[t];
+}
+
+// The same with the iterate in LDS, for matrices whose rows do not fit the
+// registers (above 1,024 rows: an explicit max_coarse, or a stalled
+// coarsening).
+__global__ __launch_bounds__(64) void k_dense_inv_col_lds(int n, const double *f, const int *pos,
+                                                          const int *status, double *invT) {
+    extern __shared__ double xs[];
+    if (*status) return;
+    int c = blockIdx.x, lane = threadIdx.x, p = pos[c];
+    for (int i = lane; i < n; i += 64) xs[i] = i == p ? 1.0 : 0.0;
     __syncthreads();
-    for (int i = 1; i < n; i++) {
+    for (int i = p + 1; i < n; i++) {
         double s = 0.0;
-        for (int j = lane; j < i; j += 64) s += a[(long)i * n + j] * xs[j];
-        for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+        for (int j = lane; j < i; j += 64) s += f[(long)i * n + j] * xs[j];
+        s = wave_sum_down(s);
         __syncthreads();
         if (lane == 0) xs[i] -= s;
         __syncthreads();
     }
     for (int i = n - 1; i >= 0; i--) {
         double s = 0.0;
-        for (int j = i + 1 + lane; j < n; j += 64) s += a[(long)i * n + j] * xs[j];
-        for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+        for (int j = i + 1 + lane; j < n; j += 64) s += f[(long)i * n + j] * xs[j];
+        s = wave_sum_down(s);
         __syncthreads();
-        if (lane == 0) xs[i] = (xs[i] - s) / a[(long)i * n + i];
+        if (lane == 0) xs[i] = (xs[i] - s) / f[(long)i * n + i];
         __syncthreads();
     }
     for (int i = lane; i < n; i += 64) invT[(long)c * n + i] = xs[i];
+}
+
+// The inverse of the coarsest matrix (n <= 4096 rows) into P->cinv.
+template <int T, int RPT, int NB>
+static int dense_lu(r2p_cpr *P, int n, hipStream_t s) {
+    for (int k0 = 0; k0 < n; k0 += NB) {
+        k_lu_panel<T, RPT, NB><<<1, T, 0, s>>>(n, k0, P->lu.p, P->luu.p, P->lupos.p, P->lurow.p,
+                                               P->astatus.p);
+        R2P_LAUNCH();
+        int rest = n - k0 - NB;
+        if (rest <= 0) break;
+        k_lu_update<NB><<<dim3(r2p_blocks(rest, 64), r2p_blocks(n, LU_R)), 256, 0, s>>>(
+            n, k0, P->lu.p, P->luu.p, P->lupos.p, P->lurow.p, P->astatus.p);
+        R2P_LAUNCH();
+    }
+    return 0;
+}
+
+static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
+    const int n = C.n;
+    R2P_TRY(P->lu.ensure((size_t)n * n));
+    R2P_TRY(P->luu.ensure((size_t)n * n));
+    R2P_TRY(P->cinv.ensure((size_t)n * n));
+    R2P_TRY(P->lupos.ensure(n));
+    R2P_TRY(P->lurow.ensure(n));
+    k_to_dense<<<n, BS, 0, s>>>(n, C.rp.p, C.col.p, C.val.p, P->lu.p, P->lupos.p);
+    R2P_LAUNCH();
+    // one workgroup holds a panel's rows: fewer columns where a thread holds
+    // two or four rows
+    if (n <= 256) R2P_TRY((dense_lu<256, 1, 32>(P, n, s)));
+    else if (n <= 512) R2P_TRY((dense_lu<512, 1, 32>(P, n, s)));
+    else if (n <= 1024) R2P_TRY((dense_lu<1024, 1, 32>(P, n, s)));
+    else if (n <= 2048) R2P_TRY((dense_lu<1024, 2, 16>(P, n, s)));
+    else R2P_TRY((dense_lu<1024, 4, 8>(P, n, s)));
+    k_lu_gather<<<n, BS, 0, s>>>(n, P->lu.p, P->lurow.p, P->luu.p);
+    R2P_LAUNCH();
+#define R2P_INV(NR, AH) \
+    k_dense_inv_col<NR, AH><<<n, 64, 0, s>>>(n, P->luu.p, P->lupos.p, P->astatus.p, P->cinv.p)
+    // 64 NR >= n
+    if (n <= 128) R2P_INV(2, 8);
+    else if (n <= 256) R2P_INV(4, 6);
+    else if (n <= 512) R2P_INV(8, 4);
+    else if (n <= 1024) R2P_INV(16, 2);
+    else
+        k_dense_inv_col_lds<<<n, 64, sizeof(double) * n, s>>>(n, P->luu.p, P->lupos.p,
+                                                            P->astatus.p, P->cinv.p);
+#undef R2P_INV
+    R2P_LAUNCH();
+    return 0;
 }
 
 // --------------------------------------------------------------- set-up
@@ -657,19 +902,10 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
         return R2P_NOT_CONVERGED;
     }
     P->ncoarse = nc;
-    R2P_TRY(P->lu.ensure((size_t)nc * nc));
-    R2P_TRY(P->cinv.ensure((size_t)nc * nc));
-    R2P_TRY(P->piv.ensure(nc));
     R2P_TRY(P->astatus.ensure(1));
     R2P_TRY(P->apin.ensure(64));
     R2P_HIP(hipMemsetAsync(P->astatus.p, 0, sizeof(int), s));
-    k_to_dense<<<r2p_blocks(nc, BS), BS, 0, s>>>(nc, C.rp.p, C.col.p, C.val.p, P->lu.p);
-    R2P_LAUNCH();
-    k_dense_lu<<<1, 1024, 0, s>>>(nc, P->lu.p, P->piv.p, P->astatus.p);
-    R2P_LAUNCH();
-    k_dense_inv_col<<<nc, 64, sizeof(double) * nc, s>>>(nc, P->lu.p, P->piv.p, P->astatus.p,
-                                                          P->cinv.p);
-    R2P_LAUNCH();
+    R2P_TRY(dense_inverse(P, C, s));
     int *h = (int *)P->apin.p;
     R2P_HIP(hipMemcpyAsync(h, P->astatus.p, sizeof(int), hipMemcpyDeviceToHost, s));
     R2P_HIP(hipStreamSynchronize(s));

@@ -249,8 +249,8 @@ struct r2p_cpr {
     int ncoarse = 0;
     DBuf<double> cinv;       // coarsest inverse, column-major: cinv[c*n + i] = (A^-1)_ic
     DBuf<float> cinvf;
-    DBuf<double> lu;         // coarsest dense LU scratch
-    DBuf<int> piv;
+    DBuf<double> lu, luu;    // coarsest dense LU: rows in place (L), U by position
+    DBuf<int> lupos, lurow;  // position of every row, row at every position
     DBuf<double> kscal;      // K-cycle scalars {q1.q1, a1, beta, a2} per level
     DBuf<double> kpart;      // K-cycle dot-product partial sums
     DBuf<double> t_ares;           // pressure stage: residual for the later cycles
@@ -322,6 +322,70 @@ __device__ __forceinline__ double2 ld_stream2(const double2 *p) {
 template <class T>
 __device__ __forceinline__ T ld_stream(const T *p) {
     return __builtin_nontemporal_load(p);
+}
+
+// Cross-lane moves without LDS: a DPP move inside a row of 16 lanes, and the
+// exchange of rows of 16 / halves of 32 lanes (v_permlane16_swap,
+// v_permlane32_swap).  __shfl_xor goes through the LDS crossbar, about a
+// hundred cycles a step; these are plain vector instructions.
+constexpr int DPP_XOR1 = 0xB1;         // quad_perm [1,0,3,2]
+constexpr int DPP_XOR2 = 0x4E;         // quad_perm [2,3,0,1]
+constexpr int DPP_HALF_MIRROR = 0x141; // lane i of 8 takes lane 7 - i
+constexpr int DPP_ROR4 = 0x124, DPP_ROR8 = 0x128;
+template <int CTRL>
+__device__ __forceinline__ int dpp_move(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_move(float v) {
+    return __builtin_bit_cast(float, dpp_move<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+    int2 t = __builtin_bit_cast(int2, v);
+    t.x = dpp_move<CTRL>(t.x);
+    t.y = dpp_move<CTRL>(t.y);
+    return __builtin_bit_cast(double, t);
+}
+// The pair (a, b) whose lanes hold, between them, the value of lane i and of
+// lane i ^ 16 (i ^ 32) in either order.
+__device__ __forceinline__ void rows_swap16(int v, int &a, int &b) {
+    auto r = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+}
+__device__ __forceinline__ void rows_swap32(int v, int &a, int &b) {
+    auto r = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+    a = (int)r[0];
+    b = (int)r[1];
+}
+template <int D>
+__device__ __forceinline__ double swap_add(double v) {
+    int2 t = __builtin_bit_cast(int2, v), a, b;
+    if (D == 16) { rows_swap16(t.x, a.x, b.x); rows_swap16(t.y, a.y, b.y); }
+    else { rows_swap32(t.x, a.x, b.x); rows_swap32(t.y, a.y, b.y); }
+    return __builtin_bit_cast(double, a) + __builtin_bit_cast(double, b);
+}
+// Sum over the wavefront in every lane, with every lane active: the additions
+// of the butterfly v += __shfl_xor(v, d) for d = 32, 16, .., 1 (down) or
+// d = 1, 2, .., 32 (up), bit for bit.  Where a DPP move takes another lane
+// than i ^ d, that lane holds the same value by then.
+__device__ __forceinline__ double wave_sum_down(double v) {
+    v = swap_add<32>(v);
+    v = swap_add<16>(v);
+    v += dpp_move<DPP_ROR8>(v);
+    v += dpp_move<DPP_ROR4>(v);
+    v += dpp_move<DPP_XOR2>(v);
+    v += dpp_move<DPP_XOR1>(v);
+    return v;
+}
+__device__ __forceinline__ double wave_sum_up(double v) {
+    v += dpp_move<DPP_XOR1>(v);
+    v += dpp_move<DPP_XOR2>(v);
+    v += dpp_move<DPP_HALF_MIRROR>(v);
+    v += dpp_move<DPP_ROR8>(v);
+    v = swap_add<16>(v);
+    return swap_add<32>(v);
 }
 
 // Source of a Jacobian block for the subdomain matrices: >= 0 is a slot block
