@@ -18,9 +18,8 @@
 // weights once and each 2 x 8 x 32 output tile's input with its halo in
 // LDS.  The input gradient is the same kernel
 // on mirrored taps with per-tap transposed weights.  The weight gradient is a
-// GEMM over voxels: each wavefront stages 32-voxel chunks of the output
-// gradient and of the tap-shifted input, transposed, in LDS and accumulates
-// the tap's 32 x 32 block; workgroup partials are summed in a fixed order.
+// GEMM over voxels on the same tiles, its operands read from LDS transposed;
+// workgroup partials are summed in a fixed order.
 // Training keeps FP32 master weights with Adam moments.
 #include <algorithm>
 #include <cmath>
@@ -34,8 +33,7 @@ namespace {
 constexpr int CH = 32;                      // channels of every layer (padded)
 constexpr int TAPS = 27;
 constexpr int WLAYER = TAPS * CH * CH;      // weights of one padded layer
-constexpr int CBS = 256;                    // conv workgroup: 4 wavefronts
-constexpr int DW_VPB = 2048;                // voxels per weight-gradient workgroup
+constexpr int CBS = 256;                    // reduction workgroups
 constexpr int NIN = 6, NOUT = 2;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -256,103 +254,207 @@ __global__ __launch_bounds__(CWG) void k_conv(ConvArgs A) {
     }
 }
 
-// Weight gradient of one tap (blockIdx.y): dW[t, o, i] = sum_v gy[v, o] x[v + off_t, i]
-// over the workgroup's voxels; one partial 32 x 32 block per workgroup.
-constexpr int DW_ROW = 40;                  // LDS row (32 voxels) padded to 80 bytes
-__global__ __launch_bounds__(CBS) void k_conv_dw(const u16 *gy, const u16 *x, Geo g, float *part) {
-    __shared__ __attribute__((aligned(16))) u16 st[4][2][CH * DW_ROW];
-    __shared__ float red[4][CH * CH];
-    const long V = g.V();
-    const int t = blockIdx.y;
-    int dz, dy, dx;
-    tap_off(t, dz, dy, dx);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// Weight and bias gradients of a layer: dW[t, o, i] = sum_v gy[v, o] x[v + off_t, i],
+// db[o] = sum_v gy[v, o].  A GEMM with the voxels as its inner dimension: a
+// persistent workgroup takes tiles of TZ x TY x TX voxels, stages gy and x
+// (with its halo) in LDS as they lie in memory, and reads both operands
+// transposed (ds_read_b64_tr_b16: four voxels of one channel per lane), so a
+// tap is only another start address.  Wavefront 3 (dz + 1) + (dx + 1) owns the
+// three taps dy = -1, 0, 1: as it walks the tile's input rows, each row of x is
+// read once and multiplied with the three rows of gy it meets, which stay in
+// registers.  The tenth wavefront multiplies gy with ones for the bias.  The
+// sums stay in registers over all tiles of the workgroup: one partial block
+// per workgroup, added in workgroup order by k_sum_parts.
+// What bounds it: the staging of a tile and the matrix cores in turn (45 us at
+// 460,800 voxels, where the products alone are 10 us at peak).  One launch
+// column per tap that read gy and x 27 times and transposed them through
+// 2-byte LDS stores took 228 us, and the bias sums a pass of their own, 121 us.
+constexpr int DWT = 640;                        // ten wavefronts
+constexpr int TV = TZ * TY * TX;                // voxels of a tile
+constexpr int DXC = (HV * 4 + DWT - 1) / DWT;   // 16-byte chunks of x, of gy per thread
+constexpr int DGC = (TV * 4 + DWT - 1) / DWT;
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Place of a 16-byte chunk of a staged row: the four chunks of voxel v of the
+// row are permuted by v, so that reads of one chunk of consecutive voxels, 64
+// bytes apart, fall on different LDS banks.
+__device__ __forceinline__ int chunk_at(int v, int part) { return v * 4 + (part ^ ((v >> 2) & 3)); }
+
+// Voxels v .. v + 31 of a staged row as a matrix operand of the 16 channels of
+// `half`: lane (i, kg) gets channel 16 half + i of voxels v + 8 kg .. + 7, by
+// two transposing reads of four voxels each.  The lane's offsets within a row
+// (tr_off) do not depend on the row.
+__device__ __forceinline__ int tr_off(int v, int half, int j) {
+    const int lane = threadIdx.x & 63, q = lane & 3;
+    const int vl = v + 8 * (lane >> 4) + ((lane & 15) >> 2) + 4 * j;
+    return chunk_at(vl, 2 * half + (q >> 1)) * 8 + 4 * (q & 1);
+}
+__device__ __forceinline__ bf16x8 ld_tr(const u16 *row, const int (&off)[2]) {
+    uint4 r;
+    s16x4 *h = reinterpret_cast<s16x4 *>(&r);
+#pragma unroll
+    for (int j = 0; j < 2; j++)
+        h[j] = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) s16x4 *)(row + off[j]));
+    return __builtin_bit_cast(bf16x8, r);
+}
+
+__global__ __launch_bounds__(DWT) void k_conv_dw(const u16 *gy, const u16 *x, Geo g, float *part,
+                                                 float *bpart) {
+    __shared__ __attribute__((aligned(16))) u16 xl[HV * CH], gl[TV * CH];
+    const int ntx = (g.nx + TX - 1) / TX, nty = (g.ny + TY - 1) / TY, ntz = (g.nz + TZ - 1) / TZ;
+    const int ntile = g.nb * ntz * nty * ntx;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, kg = lane >> 4;
-    u16 *GT = st[wave][0], *XT = st[wave][1];
-    f32x4 acc[2][2];
-    for (int a = 0; a < 2; a++)
-        for (int b = 0; b < 2; b++) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const long v0 = (long)blockIdx.x * DW_VPB;
-    for (long c0 = v0 + 32 * wave; c0 < v0 + DW_VPB && c0 < V; c0 += 32 * 4) {
-        // stage the chunk transposed: GT[o][q] = gy[c0+q, o], XT[i][q] = x[nb(c0+q), i]
-        for (int e = lane; e < 128; e += 64) {
-            int q = e >> 2, cq = e & 3;
-            long vq = c0 + q;
-            uint4 gr{0u, 0u, 0u, 0u}, xr{0u, 0u, 0u, 0u};
-            if (vq < V) {
-                gr = *reinterpret_cast<const uint4 *>(gy + vq * CH + 8 * cq);
-                long r = vq;
-                int xx = (int)(r % g.nx);
-                r /= g.nx;
-                int yy = (int)(r % g.ny);
-                r /= g.ny;
-                int zz = (int)(r % g.nz);
-                long nb = neighbour(vq, xx, yy, zz, dz, dy, dx, g);
-                if (nb >= 0) xr = *reinterpret_cast<const uint4 *>(x + nb * CH + 8 * cq);
-            }
-            const u16 *gs = reinterpret_cast<const u16 *>(&gr);
-            const u16 *xs = reinterpret_cast<const u16 *>(&xr);
+    const int dz = wave / 3 - 1, dx = wave % 3 - 1;
+    int xo[2][2], go[2][2];             // this lane's offsets in a row of x and of gy
 #pragma unroll
-            for (int u = 0; u < 8; u++) {
-                GT[(8 * cq + u) * DW_ROW + q] = gs[u];
-                XT[(8 * cq + u) * DW_ROW + q] = xs[u];
-            }
-        }
-        __builtin_amdgcn_s_waitcnt(0xc07f);      // this wavefront's LDS writes done
-        __builtin_amdgcn_wave_barrier();
-        bf16x8 a[2], b[2];
-#pragma unroll
-        for (int mi = 0; mi < 2; mi++)
-            a[mi] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const uint4 *>(&GT[(16 * mi + i) * DW_ROW + 8 * kg]));
-#pragma unroll
-        for (int nj = 0; nj < 2; nj++)
-            b[nj] = __builtin_bit_cast(
-                bf16x8, *reinterpret_cast<const uint4 *>(&XT[(16 * nj + i) * DW_ROW + 8 * kg]));
-#pragma unroll
-        for (int mi = 0; mi < 2; mi++)
-#pragma unroll
-            for (int nj = 0; nj < 2; nj++)
-                acc[mi][nj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mi], b[nj], acc[mi][nj], 0, 0, 0);
-        __builtin_amdgcn_wave_barrier();
+    for (int u = 0; u < 4; u++) {
+        xo[u >> 1][u & 1] = tr_off(1 + dx, u >> 1, u & 1);
+        go[u >> 1][u & 1] = tr_off(0, u >> 1, u & 1);
     }
+    uint4 xr[DXC], gr[DGC];
+    auto fetch = [&](int tile) {
+        const TileAt T = tile_at(tile, g);
+        // the chunks' places are worked out for every tile: kept across the
+        // tile loop they would take more registers than there are
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
 #pragma unroll
-    for (int mi = 0; mi < 2; mi++)
+        for (int u = 0; u < DXC; u++) {
+            int c = tid + u * DWT, hv = c >> 2;
+            int gx = T.x0 + hv % HX - 1, gyy = T.y0 + (hv / HX) % HY - 1, gz = T.z0 + hv / (HX * HY) - 1;
+            bool in = c < HV * 4 && gx >= 0 && gx < g.nx && gyy >= 0 && gyy < g.ny && gz >= 0 && gz < g.nz;
+            long at = in ? (T.cb + ((long)gz * g.ny + gyy) * g.nx + gx) * CH + 8 * (c & 3) : 0;
+            uint4 v = *reinterpret_cast<const uint4 *>(x + at);
+            xr[u] = in ? v : uint4{0u, 0u, 0u, 0u};
+        }
 #pragma unroll
-        for (int nj = 0; nj < 2; nj++)
+        for (int u = 0; u < DGC; u++) {
+            int c = tid + u * DWT, tv = c >> 2;
+            int gx = T.x0 + tv % TX, gyy = T.y0 + (tv / TX) % TY, gz = T.z0 + tv / (TX * TY);
+            bool in = c < TV * 4 && gx < g.nx && gyy < g.ny && gz < g.nz;
+            long at = in ? (T.cb + ((long)gz * g.ny + gyy) * g.nx + gx) * CH + 8 * (c & 3) : 0;
+            uint4 v = *reinterpret_cast<const uint4 *>(gy + at);
+            gr[u] = in ? v : uint4{0u, 0u, 0u, 0u};
+        }
+    };
+    f32x4 acc[3][2][2];
+#pragma unroll
+    for (int a = 0; a < 12; a++) acc[a / 4][(a >> 1) & 1][a & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if ((int)blockIdx.x < ntile) fetch(blockIdx.x);
+    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
+        __syncthreads();                // the previous tile's reads are done
+#pragma unroll
+        for (int u = 0; u < DXC; u++) {
+            int c = (int)threadIdx.x + u * DWT;
+            int hv = c >> 2, v = hv % HX;
+            if (c < HV * 4) reinterpret_cast<uint4 *>(xl)[(hv - v) * 4 + chunk_at(v, c & 3)] = xr[u];
+        }
+#pragma unroll
+        for (int u = 0; u < DGC; u++) {
+            int c = (int)threadIdx.x + u * DWT;
+            int tv = c >> 2, v = tv % TX;
+            if (c < TV * 4) reinterpret_cast<uint4 *>(gl)[(tv - v) * 4 + chunk_at(v, c & 3)] = gr[u];
+        }
+        __syncthreads();
+        if (tile + (int)gridDim.x < ntile) fetch(tile + gridDim.x);
+        if (wave < 9) {
+            for (int z = 0; z < TZ; z++) {
+                // rows of gy by row mod 3, of x by row mod 2; each is requested
+                // one input row before its use
+                bf16x8 ga[3][2], xb[2][2];
+                auto row_x = [&](int yy) {
+#pragma unroll
+                    for (int n = 0; n < 2; n++)
+                        xb[yy & 1][n] = ld_tr(xl + ((z + 1 + dz) * HY + yy) * HX * CH, xo[n]);
+                };
+                auto row_g = [&](int y) {
+#pragma unroll
+                    for (int m = 0; m < 2; m++)
+                        ga[y % 3][m] = ld_tr(gl + (z * TY + y) * TX * CH, go[m]);
+                };
+                row_x(0);
+                row_g(0);
+#pragma unroll
+                for (int yy = 0; yy < HY; yy++) {
+                    if (yy + 1 < HY) row_x(yy + 1);
+                    // input row yy - 1 of the tile meets gy row yy - 1 - dy, the
+                    // oldest first: its registers take row yy + 1
+#pragma unroll
+                    for (int a = 2; a >= 0; a--) {
+                        const int y = yy - a;
+                        if (y < 0 || y >= TY) continue;
+#pragma unroll
+                        for (int m = 0; m < 2; m++)
+#pragma unroll
+                            for (int n = 0; n < 2; n++)
+                                acc[a][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                    ga[y % 3][m], xb[yy & 1][n], acc[a][m][n], 0, 0, 0);
+                    }
+                    if (yy + 1 < TY) row_g(yy + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else {
+            const bf16x8 one = {(__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f,
+                                (__bf16)1.f, (__bf16)1.f, (__bf16)1.f, (__bf16)1.f};
+            for (int r = 0; r < TZ * TY; r++)
+#pragma unroll
+                for (int m = 0; m < 2; m++)
+                    acc[0][m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                        ld_tr(gl + r * TX * CH, go[m]), one, acc[0][m][0], 0, 0, 0);
+        }
+    }
+    if (wave < 9) {
+        float *out = part + (long)blockIdx.x * TAPS * CH * CH;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            int t = 9 * (dz + 1) + 3 * a + dx + 1;
+#pragma unroll
+            for (int m = 0; m < 2; m++)
+#pragma unroll
+                for (int n = 0; n < 2; n++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++)
+                        out[(t * CH + 16 * m + 4 * kg + r) * CH + 16 * n + i] = acc[a][m][n][r];
+        }
+    } else if (i == 0) {
+#pragma unroll
+        for (int m = 0; m < 2; m++)
 #pragma unroll
             for (int r = 0; r < 4; r++)
-                red[wave][(16 * mi + 4 * kg + r) * CH + 16 * nj + i] = acc[mi][nj][r];
-    __syncthreads();
-    float *out = part + ((long)blockIdx.x * TAPS + t) * CH * CH;
-    for (int e = threadIdx.x; e < CH * CH; e += CBS)
-        out[e] = ((red[0][e] + red[1][e]) + red[2][e]) + red[3][e];
+                bpart[(long)blockIdx.x * CH + 16 * m + 4 * kg + r] = acc[0][m][0][r];
+    }
 }
 
-// dst[k] = sum over nparts of part[p * stride + k], in order.
-__global__ void k_sum_parts(const float *part, int nparts, long stride, long n, float *dst,
-                            int accumulate) {
-    long k = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (k >= n) return;
+// dst[k] = sum over nparts of part[p * n + k], k < n (n a multiple of 32): a
+// workgroup takes 32 values, eight groups of lanes a contiguous eighth of the
+// parts each (eight loads in flight), then the eighths in order: 9 us for 256
+// parts of a layer.  One thread per value walking every part was a chain of
+// 225 loads, 80 us.
+__global__ __launch_bounds__(CBS) void k_sum_parts(const float *part, int nparts, long n,
+                                                   float *dst) {
+    __shared__ float red[8][32];
+    const int c = threadIdx.x & 31, q = threadIdx.x >> 5;
+    const long k = (long)blockIdx.x * 32 + c;
+    const int per = (nparts + 7) / 8, p1 = min(nparts, (q + 1) * per);
     float s = 0.f;
-    for (int p = 0; p < nparts; p++) s += part[p * stride + k];
-    dst[k] = accumulate ? dst[k] + s : s;
-}
-
-// Column sums of gy ([V][32]): one partial row per workgroup.
-constexpr int CS_VPB = 4096;
-__global__ __launch_bounds__(CBS) void k_colsum(const u16 *gy, long V, float *part) {
-    __shared__ float red[CBS];
-    int c = threadIdx.x & 31, r = threadIdx.x >> 5;
-    long v0 = (long)blockIdx.x * CS_VPB;
-    float s = 0.f;
-    for (long v = v0 + r; v < v0 + CS_VPB && v < V; v += CBS / 32) s += from_bf16(gy[v * CH + c]);
-    red[threadIdx.x] = s;
+    int p = q * per;
+    for (; p + 8 <= p1; p += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) v[u] = part[(long)(p + u) * n + k];
+#pragma unroll
+        for (int u = 0; u < 8; u++) s += v[u];
+    }
+    for (; p < p1; p++) s += part[(long)p * n + k];
+    red[q][c] = s;
     __syncthreads();
-    if (r == 0) {
-        float t = red[c];
-        for (int q = 1; q < CBS / 32; q++) t += red[q * 32 + c];
-        part[(long)blockIdx.x * CH + c] = t;
+    if (q == 0) {
+        float t = red[0][c];
+        for (int u = 1; u < 8; u++) t += red[u][c];
+        dst[k] = t;
     }
 }
 
@@ -487,13 +589,17 @@ __global__ void k_mask_mul(const u16 *a, const u16 *mask, long n, u16 *out) {
     out[k] = from_bf16(mask[k]) > 0.f ? a[k] : (u16)0;
 }
 
-int launch_conv(const ConvArgs &A, hipStream_t s) {
-    const Geo &g = A.g;
+// Workgroups of a persistent tile kernel: one per CU (the staged tiles take
+// most of the LDS), no more than tiles; -1 when the tile count overflows.
+int tile_workgroups(const Geo &g) {
     long tiles = (long)g.nb * ((g.nz + TZ - 1) / TZ) * ((g.ny + TY - 1) / TY) * ((g.nx + TX - 1) / TX);
-    if (tiles >= (1L << 31)) { r2p_set_error("convolution grid too large"); return R2P_EINVAL; }
-    // one workgroup per CU (the staged weights and halo take 139 KB of LDS)
-    int grid = (int)std::min<long>(tiles, r2p_cu_count());
-    if (grid < 1) grid = 1;
+    if (tiles >= (1L << 31)) { r2p_set_error("convolution grid too large"); return -1; }
+    return std::max(1, (int)std::min<long>(tiles, r2p_cu_count()));
+}
+
+int launch_conv(const ConvArgs &A, hipStream_t s) {
+    int grid = tile_workgroups(A.g);
+    if (grid < 0) return R2P_EINVAL;
     k_conv<<<grid, CWG, 0, s>>>(A);
     R2P_LAUNCH();
     return 0;
@@ -562,23 +668,26 @@ int forward_impl(r2p_cnn *C, const u16 *feat, Geo g, hipStream_t s) {
     return launch_conv(Ao, s);
 }
 
-int weight_grad(r2p_cnn *C, const u16 *gy, const u16 *x, Geo g, int layer, hipStream_t s) {
-    long V = g.V();
-    int nwg = (int)((V + DW_VPB - 1) / DW_VPB);
-    R2P_TRY(C->part.ensure((size_t)nwg * TAPS * CH * CH));
-    k_conv_dw<<<dim3(nwg, TAPS), CBS, 0, s>>>(gy, x, g, C->part.p);
+// Weight and bias gradients of one layer into dw ([27][32][32]) and db ([32]);
+// part, bpart: workspace.
+int conv_dw(const u16 *gy, const u16 *x, Geo g, float *dw, float *db, DBuf<float> &part,
+            DBuf<float> &bpart, hipStream_t s) {
+    int nwg = tile_workgroups(g);
+    if (nwg < 0) return R2P_EINVAL;
+    R2P_TRY(part.ensure((size_t)nwg * WLAYER));
+    R2P_TRY(bpart.ensure((size_t)nwg * CH));
+    k_conv_dw<<<nwg, DWT, 0, s>>>(gy, x, g, part.p, bpart.p);
     R2P_LAUNCH();
-    long n = (long)TAPS * CH * CH;
-    k_sum_parts<<<r2p_blocks(n, 256), 256, 0, s>>>(C->part.p, nwg, n, n,
-                                                   C->gw.p + (long)layer * WLAYER, 0);
+    k_sum_parts<<<WLAYER / 32, CBS, 0, s>>>(part.p, nwg, WLAYER, dw);
     R2P_LAUNCH();
-    int ncs = (int)((V + CS_VPB - 1) / CS_VPB);
-    R2P_TRY(C->bpart.ensure((size_t)ncs * CH));
-    k_colsum<<<ncs, CBS, 0, s>>>(gy, V, C->bpart.p);
-    R2P_LAUNCH();
-    k_sum_parts<<<1, CH, 0, s>>>(C->bpart.p, ncs, CH, CH, C->gb.p + layer * CH, 0);
+    k_sum_parts<<<1, CBS, 0, s>>>(bpart.p, nwg, CH, db);
     R2P_LAUNCH();
     return 0;
+}
+
+int weight_grad(r2p_cnn *C, const u16 *gy, const u16 *x, Geo g, int layer, hipStream_t s) {
+    return conv_dw(gy, x, g, C->gw.p + (long)layer * WLAYER, C->gb.p + layer * CH, C->part, C->bpart,
+                   s);
 }
 
 // Input gradient of layer l applied to gy, with an optional mask and addend.
@@ -796,21 +905,8 @@ extern "C" int r2p_cnn_conv_dw(const uint16_t *gy, const uint16_t *x, int nb, in
     R2P_TRY(check_geo(nb, nz, ny, nx));
     hipStream_t s = (hipStream_t)stream;
     Geo g = make_geo(nb, nz, ny, nx);
-    long V = g.V();
-    int nwg = (int)((V + DW_VPB - 1) / DW_VPB);
     DBuf<float> part, bpart;
-    R2P_TRY(part.ensure((size_t)nwg * TAPS * CH * CH));
-    k_conv_dw<<<dim3(nwg, TAPS), CBS, 0, s>>>(gy, x, g, part.p);
-    R2P_LAUNCH();
-    long n = (long)TAPS * CH * CH;
-    k_sum_parts<<<r2p_blocks(n, 256), 256, 0, s>>>(part.p, nwg, n, n, dw, 0);
-    R2P_LAUNCH();
-    int ncs = (int)((V + CS_VPB - 1) / CS_VPB);
-    R2P_TRY(bpart.ensure((size_t)ncs * CH));
-    k_colsum<<<ncs, CBS, 0, s>>>(gy, V, bpart.p);
-    R2P_LAUNCH();
-    k_sum_parts<<<1, CH, 0, s>>>(bpart.p, ncs, CH, CH, db, 0);
-    R2P_LAUNCH();
+    R2P_TRY(conv_dw(gy, x, g, dw, db, part, bpart, s));
     R2P_HIP(hipStreamSynchronize(s));
     return 0;
 }
