@@ -14,9 +14,9 @@
 // Device design.  A convolution is an implicit GEMM: for each of the 27 taps
 // a wavefront multiplies 16-voxel x 32-channel blocks of shifted inputs by
 // the tap's 32 x 32 weight block on the matrix cores
-// (v_mfma_f32_16x16x32_bf16); a persistent workgroup per CU stages the
-// weights once and each 2 x 8 x 32 output tile's input with its halo in
-// LDS.  The input gradient is the same kernel
+// (v_mfma_f32_16x16x32_bf16); a workgroup walks the planes of a 16 x 16 column
+// with the weights in registers and the input planes in an LDS ring.  The
+// input gradient is the same kernel
 // on mirrored taps with per-tap transposed weights.  The weight gradient is a
 // GEMM over voxels on the same tiles, its operands read from LDS transposed;
 // workgroup partials are summed in a fixed order.
@@ -24,6 +24,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "r2p_impl.h"
@@ -37,6 +38,7 @@ constexpr int CBS = 256;                    // reduction workgroups
 constexpr int NIN = 6, NOUT = 2;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned short u16;
 
@@ -58,20 +60,6 @@ struct Geo {
     __host__ __device__ long V() const { return (long)nx * ny * nz * nb; }
 };
 
-__device__ __forceinline__ void tap_off(int t, int &dz, int &dy, int &dx) {
-    dz = t / 9 - 1;
-    dy = (t / 3) % 3 - 1;
-    dx = t % 3 - 1;
-}
-
-// Index of the neighbour (dz, dy, dx) of voxel v inside its own crop, or -1.
-__device__ __forceinline__ long neighbour(long v, int x, int y, int z, int dz, int dy, int dx,
-                                          const Geo &g) {
-    int xx = x + dx, yy = y + dy, zz = z + dz;
-    if (xx < 0 || xx >= g.nx || yy < 0 || yy >= g.ny || zz < 0 || zz >= g.nz) return -1;
-    return v + ((long)dz * g.ny + dy) * g.nx + dx;
-}
-
 struct ConvArgs {
     const u16 *x;         // [V][32] input
     Geo g;
@@ -82,24 +70,13 @@ struct ConvArgs {
     int relu, flip;       // flip: taps mirrored (input-gradient form)
     u16 *out;             // [V][32] bf16 result, or NULL
     float *outf;          // [V][32] fp32 result, or NULL
+    float *out2;          // [V][2] fp32 result (channels 0 and 1), or NULL
 };
 
-// out[v, o] = epilogue(bias[o] + sum_t sum_i x[v + s off_t, i] w[t, o, i]),
-// s = -1 when flip.  A workgroup takes tiles of TZ x TY x TX output voxels of
-// one crop in turn: it stages the tile's input with its one-voxel halo (zero
-// outside the crop) in LDS, next to the 27 weight blocks staged once, so the
-// taps read their shifted inputs from LDS with no bounds tests.  The tile's
-// 16 rows of TX voxels make 32 pieces of 16 voxels; each of the 8 wavefronts owns 4
-// pieces and, per tap, multiplies each piece's 16 x 32 input block by the
-// tap's 32 x 32 weight block on the matrix cores (v_mfma_f32_16x16x32_bf16,
-// two 16-channel halves).  A tile reads 1,360 halo voxels for 512 outputs,
-// so each input voxel is fetched from memory about 2.7 times instead of 27.
+// Weight-gradient tiles: TZ x TY x TX voxels of one crop, read with a
+// one-voxel halo.
 constexpr int TZ = 2, TY = 8, TX = 32;
 constexpr int HZ = TZ + 2, HY = TY + 2, HX = TX + 2, HV = HZ * HY * HX;
-constexpr int CWG = 512;                        // convolution workgroup: 8 wavefronts
-constexpr int PIECES = TZ * TY * TX / 16;       // 16-voxel pieces per tile
-constexpr int MT = PIECES / (CWG / 64);         // pieces per wavefront
-constexpr int HCH = (HV * 4 + CWG - 1) / CWG;   // 16-byte halo chunks per thread
 
 struct TileAt {
     long cb;            // first voxel of the tile's crop
@@ -120,138 +97,209 @@ __device__ __forceinline__ TileAt tile_at(int tile, const Geo &g) {
     return T;
 }
 
-// This thread's chunks of a tile's input with halo (zero outside the crop).
-__device__ __forceinline__ void fetch_halo(uint4 (&h)[HCH], const u16 *x, const TileAt &T,
-                                           const Geo &g) {
-#pragma unroll
-    for (int u = 0; u < HCH; u++) {
-        int c = (int)threadIdx.x + u * CWG;
-        int hv = c >> 2, part = c & 3;
-        int hx = hv % HX, hy = (hv / HX) % HY, hz = hv / (HX * HY);
-        int gx = T.x0 + hx - 1, gy = T.y0 + hy - 1, gz = T.z0 + hz - 1;
-        bool in = c < HV * 4 && gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny && gz >= 0 &&
-                  gz < g.nz;
-        long at = in ? (T.cb + ((long)gz * g.ny + gy) * g.nx + gx) * CH + 8 * part : 0;
-        uint4 v = *reinterpret_cast<const uint4 *>(x + at);
-        h[u] = in ? v : uint4{0u, 0u, 0u, 0u};
-    }
-}
+// Place of a 16-byte chunk of a staged row: the four chunks of voxel v of the
+// row are permuted by v, so that reads of one chunk of consecutive voxels, 64
+// bytes apart, fall on different LDS banks.
+__device__ __forceinline__ int chunk_at(int v, int part) { return v * 4 + (part ^ ((v >> 2) & 3)); }
 
-__global__ __launch_bounds__(CWG) void k_conv(ConvArgs A) {
-    __shared__ __attribute__((aligned(16))) u16 wl[WLAYER];
-    __shared__ __attribute__((aligned(16))) u16 xl[HV * CH];
-    for (int e = threadIdx.x; e < WLAYER / 8; e += CWG)
-        reinterpret_cast<uint4 *>(wl)[e] = reinterpret_cast<const uint4 *>(A.w)[e];
+// out[v, o] = epilogue(bias[o] + sum_t sum_i x[v + s off_t, i] w[t, o, i]),
+// s = -1 with FLIP.  A workgroup takes a column of CY x CX voxels of one crop
+// and walks a range of its planes (downwards with FLIP).  Every input plane,
+// with a one-voxel halo that is zero outside the crop, is staged once in LDS
+// (two buffers, the plane after next in registers, one barrier a plane) and
+// adds to the three output planes it meets, which are held in registers.
+// Wavefront q owns rows ROWS (q mod 4) .. of the planes and output channels
+// 16 (q / 4) .. + 15; the 27 weight blocks of those channels stay in its
+// registers, so a 16-byte LDS read a lane (16 voxels x 32 channels) feeds nine
+// v_mfma_f32_16x16x32_bf16.  The weights are the first operand, so a lane ends
+// up with four consecutive channels of one voxel and the epilogue works
+// straight from the registers.  Every output receives its taps in the order
+// t = 0 .. 26.
+// What bounds it: the matrix cores (2M voxels: 53 us at the 2.09 PFLOP/s that
+// back-to-back matrix instructions reach here, 91 us at the rate of a large
+// library product), then each step's epilogue, which the two wavefronts of a
+// SIMD reach together.  Measured over the ten layers of a forward pass at 2M
+// voxels: 115 us a layer.  Tiles of 2 x 8 x 32 voxels whose weights and input
+// both came from LDS read six fragments for eight matrix instructions and
+// took 200 us; the same column walk with all 32 output channels in each of
+// four wavefronts needs 440 registers, which the compiler shuffles, 170 us;
+// every halo plane at full cost, 118 us.
+constexpr int CY = 16, CX = 16;                  // output voxels of a plane
+constexpr int PY = CY + 2, PX = CX + 2, PV = PY * PX;
+constexpr int CWG = 512;                         // eight wavefronts
+constexpr int ROWS = 4;                          // output rows per wavefront
+constexpr int PCH = (PV * 4 + CWG - 1) / CWG;    // 16-byte chunks of a plane per thread
+
+template <int V>
+using Int = std::integral_constant<int, V>;
+
+// OUT2: the output layer; only its two channels are computed and stored.
+template <bool FLIP, bool OUT2>
+__global__ __launch_bounds__(CWG, 1) void k_conv(ConvArgs A, int zc) {
+    __shared__ __attribute__((aligned(16))) u16 buf[2][PV * CH];
     const Geo g = A.g;
-    const int ntile = g.nb * ((g.nz + TZ - 1) / TZ) * ((g.ny + TY - 1) / TY) *
-                      ((g.nx + TX - 1) / TX);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ntx = (g.nx + CX - 1) / CX, nty = (g.ny + CY - 1) / CY, nzc = (g.nz + zc - 1) / zc;
+    int rest = xcd_block(blockIdx.x, gridDim.x);
+    const int x0 = (rest % ntx) * CX;
+    rest /= ntx;
+    const int y0 = (rest % nty) * CY;
+    rest /= nty;
+    const int z0 = (rest % nzc) * zc, z1 = min(z0 + zc, g.nz);
+    const long cb = (long)(rest / nzc) * ((long)g.nx * g.ny * g.nz);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i = lane & 15, kg = lane >> 4;
-    // the next tile's input is requested into registers before the current
-    // tile is computed, so its memory latency overlaps the matrix work
-    uint4 hreg[HCH];
-    // bias of this thread's eight epilogue channels
-    const int part = threadIdx.x & 3;
-    float bz[8];
+    const int rowq = wave & 3, ch = 16 * (wave >> 2) + 4 * kg;     // rows; this lane's channels
+
+    // this thread's chunks of an input plane: place in the plane (-1: outside
+    // the crop, zero) and in LDS
+    int at[PCH], to[PCH];
 #pragma unroll
-    for (int u = 0; u < 8; u++) bz[u] = A.bias ? A.bias[8 * part + u] : 0.f;
-    if ((int)blockIdx.x < ntile) fetch_halo(hreg, A.x, tile_at(blockIdx.x, g), g);
-    for (int tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-        const TileAt T = tile_at(tile, g);
-        const long cb = T.cb;
-        const int x0 = T.x0, y0 = T.y0, z0 = T.z0;
-        __syncthreads();            // weights staged; the previous tile's reads are done
-#pragma unroll
-        for (int u = 0; u < HCH; u++) {
-            int c = (int)threadIdx.x + u * CWG;
-            if (c < HV * 4) reinterpret_cast<uint4 *>(xl)[c] = hreg[u];
-        }
-        __syncthreads();
-        if (tile + (int)gridDim.x < ntile) fetch_halo(hreg, A.x, tile_at(tile + gridDim.x, g), g);
-        f32x4 acc[MT][2];
-#pragma unroll
-        for (int j = 0; j < MT; j++) acc[j][0] = acc[j][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // every piece is computed (pieces past the crop's edge read zeros and
-        // are not stored), so a tap is straight-line code: its ten LDS reads
-        // are issued ahead of its sixteen matrix instructions
-#pragma unroll 3
-        for (int t = 0; t < TAPS; t++) {
-            int dz, dy, dx;
-            tap_off(t, dz, dy, dx);
-            if (A.flip) { dz = -dz; dy = -dy; dx = -dx; }
-            bf16x8 b[2];
-#pragma unroll
-            for (int n = 0; n < 2; n++)
-                b[n] = __builtin_bit_cast(
-                    bf16x8, *reinterpret_cast<const uint4 *>(&wl[(t * CH + 16 * n + i) * CH + 8 * kg]));
-#pragma unroll
-            for (int j = 0; j < MT; j++) {
-                int pc = wave * MT + j, row = pc >> 1;
-                int hv = ((row / TY + 1 + dz) * HY + (row % TY + 1 + dy)) * HX + (pc & 1) * 16 + i + 1 + dx;
-                bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(&xl[hv * CH + 8 * kg]));
-                acc[j][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[0], acc[j][0], 0, 0, 0);
-                acc[j][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[1], acc[j][1], 0, 0, 0);
-            }
-        }
-        // The results go through LDS (the halo buffer is free once every
-        // wavefront has finished its taps): element (voxel 4 kg + r of piece
-        // pc, channel 16 n + i) is stored at float [16 pc + 4 kg + r][32];
-        // then each thread takes eight channels of a voxel, so the addend and
-        // mask are read and the result written 16 bytes per lane.
-        float *st = reinterpret_cast<float *>(xl);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < MT; j++) {
-            int pc = wave * MT + j;
-#pragma unroll
-            for (int n = 0; n < 2; n++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) st[(16 * pc + 4 * kg + r) * CH + 16 * n + i] = acc[j][n][r];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < PIECES * 16 * 4 / CWG; q++) {
-            int tv = q * (CWG / 4) + (int)(threadIdx.x >> 2);     // voxel of the tile
-            int pc = tv >> 4, row = pc >> 1;
-            int xo = x0 + (pc & 1) * 16 + (tv & 15), yo = y0 + row % TY, zo = z0 + row / TY;
-            if (xo >= g.nx || yo >= g.ny || zo >= g.nz) continue;
-            long vo = cb + ((long)zo * g.ny + yo) * g.nx + xo;
-            float4 r0 = *reinterpret_cast<const float4 *>(&st[tv * CH + 8 * part]);
-            float4 r1 = *reinterpret_cast<const float4 *>(&st[tv * CH + 8 * part + 4]);
-            float val[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-#pragma unroll
-            for (int u = 0; u < 8; u++) val[u] += bz[u];
-            if (A.addend) {
-                uint4 ad = *reinterpret_cast<const uint4 *>(A.addend + vo * CH + 8 * part);
-                const u16 *ah = reinterpret_cast<const u16 *>(&ad);
-#pragma unroll
-                for (int u = 0; u < 8; u++) val[u] += from_bf16(ah[u]);
-            }
-            if (A.mask) {
-                uint4 mk = *reinterpret_cast<const uint4 *>(A.mask + vo * CH + 8 * part);
-                const u16 *mh = reinterpret_cast<const u16 *>(&mk);
-#pragma unroll
-                for (int u = 0; u < 8; u++) val[u] = from_bf16(mh[u]) > 0.f ? val[u] : 0.f;
-            }
-            if (A.relu) {
-#pragma unroll
-                for (int u = 0; u < 8; u++) val[u] = val[u] > 0.f ? val[u] : 0.f;
-            }
-            if (A.out) {
-                uint4 o;
-                u16 *oh = reinterpret_cast<u16 *>(&o);
-#pragma unroll
-                for (int u = 0; u < 8; u++) oh[u] = to_bf16(val[u]);
-                *reinterpret_cast<uint4 *>(A.out + vo * CH + 8 * part) = o;
-            }
-            if (A.outf) {
-                *reinterpret_cast<float4 *>(A.outf + vo * CH + 8 * part) =
-                    make_float4(val[0], val[1], val[2], val[3]);
-                *reinterpret_cast<float4 *>(A.outf + vo * CH + 8 * part + 4) =
-                    make_float4(val[4], val[5], val[6], val[7]);
-            }
-        }
+    for (int u = 0; u < PCH; u++) {
+        int c = (int)threadIdx.x + u * CWG, v = c >> 2, hx = v % PX, hy = v / PX;
+        int gx = x0 + hx - 1, gy = y0 + hy - 1;
+        bool in = c < PV * 4 && gx >= 0 && gx < g.nx && gy >= 0 && gy < g.ny;
+        at[u] = in ? (gy * g.nx + gx) * CH + 8 * (c & 3) : -1;
+        to[u] = c < PV * 4 ? hy * PX * 4 + chunk_at(hx, c & 3) : -1;
     }
+    auto fetch = [&](uint4 (&p)[PCH], int z) {
+        const u16 *src = A.x + (cb + (long)min(max(z, 0), g.nz - 1) * g.ny * g.nx) * CH;
+        const bool zin = z >= 0 && z < g.nz;
+#pragma unroll
+        for (int u = 0; u < PCH; u++) {
+            uint4 v = *reinterpret_cast<const uint4 *>(src + max(at[u], 0));
+            p[u] = zin && at[u] >= 0 ? v : uint4{0u, 0u, 0u, 0u};
+        }
+    };
+    auto stage = [&](const uint4 (&p)[PCH], int b) {
+        uint4 *dst = reinterpret_cast<uint4 *>(buf[b]);
+#pragma unroll
+        for (int u = 0; u < PCH; u++)
+            if (to[u] >= 0) dst[to[u]] = p[u];
+    };
+    // step k reads input plane zin(k) and completes output plane zin(k) - s
+    const int n = z1 - z0;
+    auto zin = [&](int k) { return FLIP ? z1 - k : z0 - 1 + k; };
+    uint4 pr[PCH], p0[PCH];
+    fetch(p0, zin(0));
+    fetch(pr, zin(1));
+    bf16x8 wr[TAPS];
+#pragma unroll
+    for (int t = 0; t < TAPS; t++)
+        wr[t] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(
+                                               A.w + (t * CH + 16 * (wave >> 2) + i) * CH + 8 * kg));
+    float bz[4];
+#pragma unroll
+    for (int u = 0; u < 4; u++) bz[u] = A.bias ? A.bias[ch + u] : 0.f;
+    stage(p0, 0);
+    // this lane's place in a staged row, by the tap's x step
+    int xo[3];
+#pragma unroll
+    for (int e = 0; e < 3; e++) xo[e] = chunk_at(i + (FLIP ? 2 - e : e), kg) * 8;
+    const int xi = x0 + i, yb = y0 + rowq * ROWS;
+    f32x4 acc[3][ROWS];                 // output planes zin + s, zin, zin - s
+#pragma unroll
+    for (int d = 0; d < 3; d++)
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) acc[d][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // step k; LO .. HI: the output planes of acc that its plane adds to
+    auto step = [&](int k, auto lo, auto hi) {
+        constexpr int LO = decltype(lo)::value, HI = decltype(hi)::value;
+        __syncthreads();        // this step's plane is staged; the other buffer is not read any more
+        if (k < n + 1) stage(pr, (k + 1) & 1);
+        if (k < n) fetch(pr, zin(k + 2));
+        const int zo = FLIP ? zin(k) + 1 : zin(k) - 1;
+        const long vb = cb + ((long)zo * g.ny + yb) * g.nx + xi;
+        uint2 ad[ROWS], mk[ROWS];
+        auto rows_of = [&](uint2 (&v)[ROWS], const u16 *src) {
+#pragma unroll
+            for (int r = 0; r < ROWS; r++)
+                v[r] = *reinterpret_cast<const uint2 *>(
+                    src + (xi < g.nx && yb + r < g.ny ? vb + (long)r * g.nx : cb) * CH + ch);
+        };
+        if (!OUT2 && A.addend && k >= 2) rows_of(ad, A.addend);
+        if (!OUT2 && A.mask && k >= 2) rows_of(mk, A.mask);
+        if (!OUT2 || wave < 4) {
+            // fragments in order of use (input row, x step), each requested
+            // three before its use; input row yy meets output row yy - a at
+            // tap row a (rows reversed with FLIP)
+            const u16 *pl = buf[k & 1] + rowq * ROWS * PX * CH;
+            constexpr int NF = 3 * (ROWS + 2);
+            uint4 fb[4];
+            auto frag = [&](int f) {
+                const int yy = f / 3;
+                fb[f & 3] = *reinterpret_cast<const uint4 *>(
+                    pl + (FLIP ? ROWS + 1 - yy : yy) * PX * CH + xo[f % 3]);
+            };
+#pragma unroll
+            for (int f = 0; f < 3; f++) frag(f);
+#pragma unroll
+            for (int f = 0; f < NF; f++) {
+                if (f + 3 < NF) frag(f + 3);
+                const int yy = f / 3, e = f % 3;
+                const bf16x8 b = __builtin_bit_cast(bf16x8, fb[f & 3]);
+#pragma unroll
+                for (int a = 0; a < 3; a++) {
+                    const int y = yy - a;
+                    if (y < 0 || y >= ROWS) continue;
+#pragma unroll
+                    for (int d = LO; d <= HI; d++)
+                        acc[d][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            wr[9 * d + 3 * a + e], b, acc[d][y], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (k >= 2) {
+#pragma unroll
+            for (int r = 0; r < ROWS; r++) {
+                if (xi >= g.nx || yb + r >= g.ny) continue;
+                const long vo = vb + (long)r * g.nx;
+                const f32x4 v = acc[2][FLIP ? ROWS - 1 - r : r];
+                float val[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) val[u] = v[u] + bz[u];
+                if (OUT2) {
+                    if (ch == 0) {
+                        A.out2[2 * vo] = val[0];
+                        A.out2[2 * vo + 1] = val[1];
+                    }
+                    continue;
+                }
+                if (A.addend) {
+                    const u16 *ah = reinterpret_cast<const u16 *>(&ad[r]);
+#pragma unroll
+                    for (int u = 0; u < 4; u++) val[u] += from_bf16(ah[u]);
+                }
+                if (A.mask) {
+                    const u16 *mh = reinterpret_cast<const u16 *>(&mk[r]);
+#pragma unroll
+                    for (int u = 0; u < 4; u++) val[u] = from_bf16(mh[u]) > 0.f ? val[u] : 0.f;
+                }
+                if (A.relu) {
+#pragma unroll
+                    for (int u = 0; u < 4; u++) val[u] = val[u] > 0.f ? val[u] : 0.f;
+                }
+                if (A.out) {
+                    // nearest even, as to_bf16 (v_cvt_pk_bf16_f32)
+                    bf16x4 o = {(__bf16)val[0], (__bf16)val[1], (__bf16)val[2], (__bf16)val[3]};
+                    *reinterpret_cast<bf16x4 *>(A.out + vo * CH + ch) = o;
+                }
+                if (A.outf)
+                    *reinterpret_cast<float4 *>(A.outf + vo * CH + ch) =
+                        make_float4(val[0], val[1], val[2], val[3]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < ROWS; r++) {
+            acc[2][r] = acc[1][r];
+            acc[1][r] = acc[0][r];
+            acc[0][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    // the halo planes at the ends of the range meet one output plane each
+    step(0, Int<0>(), Int<0>());
+    for (int k = 1; k <= n; k++) step(k, Int<0>(), Int<2>());
+    step(n + 1, Int<2>(), Int<2>());
 }
 
 // Weight and bias gradients of a layer: dW[t, o, i] = sum_v gy[v, o] x[v + off_t, i],
@@ -274,11 +322,6 @@ constexpr int TV = TZ * TY * TX;                // voxels of a tile
 constexpr int DXC = (HV * 4 + DWT - 1) / DWT;   // 16-byte chunks of x, of gy per thread
 constexpr int DGC = (TV * 4 + DWT - 1) / DWT;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-
-// Place of a 16-byte chunk of a staged row: the four chunks of voxel v of the
-// row are permuted by v, so that reads of one chunk of consecutive voxels, 64
-// bytes apart, fall on different LDS banks.
-__device__ __forceinline__ int chunk_at(int v, int part) { return v * 4 + (part ^ ((v >> 2) & 3)); }
 
 // Voxels v .. v + 31 of a staged row as a matrix operand of the 16 channels of
 // `half`: lane (i, kg) gets channel 16 half + i of voxels v + 8 kg .. + 7, by
@@ -466,15 +509,13 @@ __global__ __launch_bounds__(CBS) void k_mse(const float *out, const float *tgt,
     long v = blockIdx.x * (long)CBS + threadIdx.x;
     double s = 0.0;
     if (v < V) {
-        for (int c = 0; c < CH; c++) {
-            float gv = 0.f;
-            if (c < NOUT) {
-                float d = out[v * CH + c] - tgt[v * NOUT + c];
-                s += (double)d * d;
-                gv = 2.f * d * scale;
-            }
-            gy[v * CH + c] = to_bf16(gv);
-        }
+        float d0 = out[NOUT * v] - tgt[NOUT * v], d1 = out[NOUT * v + 1] - tgt[NOUT * v + 1];
+        s += (double)d0 * d0;
+        s += (double)d1 * d1;
+        unsigned g = (unsigned)to_bf16(2.f * d0 * scale) | ((unsigned)to_bf16(2.f * d1 * scale) << 16);
+        uint4 *row = reinterpret_cast<uint4 *>(gy + v * CH);
+        row[0] = uint4{g, 0u, 0u, 0u};
+        row[1] = row[2] = row[3] = uint4{0u, 0u, 0u, 0u};
     }
     red[threadIdx.x] = s;
     __syncthreads();
@@ -483,13 +524,6 @@ __global__ __launch_bounds__(CBS) void k_mse(const float *out, const float *tgt,
         __syncthreads();
     }
     if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ void k_take2(const float *outf, long V, float *out2) {
-    long v = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (v >= V) return;
-    out2[2 * v] = outf[v * CH];
-    out2[2 * v + 1] = outf[v * CH + 1];
 }
 
 // Adam on the padded FP32 master weights; then bf16 copies in the forward
@@ -582,13 +616,6 @@ __global__ void k_apply_guess(int n, int nw, const double *x, const float *pred,
     }
 }
 
-// out = a where mask > 0, else 0 (bf16 tensors of n elements).
-__global__ void k_mask_mul(const u16 *a, const u16 *mask, long n, u16 *out) {
-    long k = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    out[k] = from_bf16(mask[k]) > 0.f ? a[k] : (u16)0;
-}
-
 // Workgroups of a persistent tile kernel: one per CU (the staged tiles take
 // most of the LDS), no more than tiles; -1 when the tile count overflows.
 int tile_workgroups(const Geo &g) {
@@ -597,10 +624,31 @@ int tile_workgroups(const Geo &g) {
     return std::max(1, (int)std::min<long>(tiles, r2p_cu_count()));
 }
 
+// Planes per workgroup of k_conv.  A workgroup's time is its planes plus about
+// two for the weights and the halo planes, and CUs take workgroups in rounds:
+// the split of the columns' planes with the shortest rounds.
+int conv_planes(const Geo &g, long columns, int cus) {
+    long best = 0;
+    int zc = g.nz;
+    for (int c = 1; c <= g.nz; c++) {
+        int p = (g.nz + c - 1) / c;
+        long wgs = columns * ((g.nz + p - 1) / p);
+        long cost = (wgs + cus - 1) / cus * (p + 2);
+        if (best == 0 || cost < best) { best = cost; zc = p; }
+        if (wgs >= 8L * cus) break;      // full rounds: a finer split only adds to each
+    }
+    return zc;
+}
+
 int launch_conv(const ConvArgs &A, hipStream_t s) {
-    int grid = tile_workgroups(A.g);
-    if (grid < 0) return R2P_EINVAL;
-    k_conv<<<grid, CWG, 0, s>>>(A);
+    const Geo &g = A.g;
+    long columns = (long)g.nb * ((g.ny + CY - 1) / CY) * ((g.nx + CX - 1) / CX);
+    int zc = conv_planes(g, columns, std::max(1, r2p_cu_count()));
+    long wgs = columns * ((g.nz + zc - 1) / zc);
+    if (wgs >= (1L << 31)) { r2p_set_error("convolution grid too large"); return R2P_EINVAL; }
+    if (A.out2) k_conv<false, true><<<(int)wgs, CWG, 0, s>>>(A, zc);
+    else if (A.flip) k_conv<true, false><<<(int)wgs, CWG, 0, s>>>(A, zc);
+    else k_conv<false, false><<<(int)wgs, CWG, 0, s>>>(A, zc);
     R2P_LAUNCH();
     return 0;
 }
@@ -616,55 +664,59 @@ struct r2p_cnn {
     DBuf<u16> wf, wt;           // bf16 weights: forward and input-gradient layouts
     long step = 0;
     // activations of the last forward pass ([V][32] each) and gradients
-    std::vector<DBuf<u16>> act; // f, h0, a0, h1, a1, h2, ..., h_K
-    DBuf<float> outf;           // [V][32]
+    std::vector<DBuf<u16>> act; // h0, a0, h1, a1, h2, ..., h_K
+    DBuf<float> out2;           // [V][2]: the output of a training pass
     DBuf<u16> g0, g1, g2;       // gradient work tensors
     DBuf<float> part, bpart;
     DBuf<double> lpart;
     DBuf<float> pred;
-    DBuf<u16> feat;
+    DBuf<u16> feat, fcopy;
     HostPinned pin;
 };
 
 namespace {
 
 int ensure_acts(r2p_cnn *C, long V) {
-    C->act.resize(2 * C->K + 2);
+    C->act.resize(2 * C->K + 1);
     for (auto &a : C->act) R2P_TRY(a.ensure((size_t)V * CH));
-    R2P_TRY(C->outf.ensure((size_t)V * CH));
-    R2P_TRY(C->g0.ensure((size_t)V * CH));
-    R2P_TRY(C->g1.ensure((size_t)V * CH));
-    R2P_TRY(C->g2.ensure((size_t)V * CH));
+    return 0;
+}
+
+// The features where the kernels can read 16 bytes at a time: the caller's
+// tensor, or a copy when that is not 16-byte aligned.
+int aligned_features(r2p_cnn *C, const u16 *&feat, long V, hipStream_t s) {
+    if (((uintptr_t)feat & 15) == 0) return 0;
+    R2P_TRY(C->fcopy.ensure((size_t)V * CH));
+    R2P_HIP(hipMemcpyAsync(C->fcopy.p, feat, sizeof(u16) * V * CH, hipMemcpyDeviceToDevice, s));
+    feat = C->fcopy.p;
     return 0;
 }
 
 // Layer l: weights at wf + l * WLAYER, bias at b + l * 32.  Activation
-// slots: act[0] = f, act[1] = h0, then a_k at 2 + 2k, h_{k+1} at 3 + 2k.
-int forward_impl(r2p_cnn *C, const u16 *feat, Geo g, hipStream_t s) {
-    long V = g.V();
-    R2P_HIP(hipMemcpyAsync(C->act[0].p, feat, sizeof(u16) * V * CH, hipMemcpyDeviceToDevice, s));
+// slots: act[0] = h0, then a_k at 1 + 2k, h_{k+1} at 2 + 2k; out: [V][2].
+int forward_impl(r2p_cnn *C, const u16 *feat, Geo g, float *out, hipStream_t s) {
     ConvArgs A{};
     A.g = g;
-    A.x = C->act[0].p; A.w = C->wf.p; A.bias = C->b.p; A.relu = 1; A.out = C->act[1].p;
+    A.x = feat; A.w = C->wf.p; A.bias = C->b.p; A.relu = 1; A.out = C->act[0].p;
     R2P_TRY(launch_conv(A, s));
     for (int k = 0; k < C->K; k++) {
         int la = 1 + 2 * k, lb = 2 + 2 * k;
         ConvArgs Aa{};
         Aa.g = g;
-        Aa.x = C->act[1 + 2 * k].p; Aa.w = C->wf.p + (long)la * WLAYER; Aa.bias = C->b.p + la * CH;
-        Aa.relu = 1; Aa.out = C->act[2 + 2 * k].p;
+        Aa.x = C->act[2 * k].p; Aa.w = C->wf.p + (long)la * WLAYER; Aa.bias = C->b.p + la * CH;
+        Aa.relu = 1; Aa.out = C->act[1 + 2 * k].p;
         R2P_TRY(launch_conv(Aa, s));
         ConvArgs Ab{};
         Ab.g = g;
-        Ab.x = C->act[2 + 2 * k].p; Ab.w = C->wf.p + (long)lb * WLAYER; Ab.bias = C->b.p + lb * CH;
-        Ab.addend = C->act[1 + 2 * k].p; Ab.out = C->act[3 + 2 * k].p;
+        Ab.x = C->act[1 + 2 * k].p; Ab.w = C->wf.p + (long)lb * WLAYER; Ab.bias = C->b.p + lb * CH;
+        Ab.addend = C->act[2 * k].p; Ab.out = C->act[2 + 2 * k].p;
         R2P_TRY(launch_conv(Ab, s));
     }
     int lo = C->L - 1;
     ConvArgs Ao{};
     Ao.g = g;
-    Ao.x = C->act[2 * C->K + 1].p; Ao.w = C->wf.p + (long)lo * WLAYER; Ao.bias = C->b.p + lo * CH;
-    Ao.outf = C->outf.p;
+    Ao.x = C->act[2 * C->K].p; Ao.w = C->wf.p + (long)lo * WLAYER; Ao.bias = C->b.p + lo * CH;
+    Ao.out2 = out;
     return launch_conv(Ao, s);
 }
 
@@ -823,10 +875,8 @@ extern "C" int r2p_cnn_forward(r2p_cnn *C, const uint16_t *feat, int nb, int nz,
     hipStream_t s = (hipStream_t)stream;
     Geo g = make_geo(nb, nz, ny, nx);
     R2P_TRY(ensure_acts(C, g.V()));
-    R2P_TRY(forward_impl(C, feat, g, s));
-    k_take2<<<r2p_blocks(g.V(), 256), 256, 0, s>>>(C->outf.p, g.V(), out);
-    R2P_LAUNCH();
-    return 0;
+    R2P_TRY(aligned_features(C, feat, g.V(), s));
+    return forward_impl(C, feat, g, out, s);
 }
 
 extern "C" int r2p_cnn_backward(r2p_cnn *C, const uint16_t *feat, const float *target, int nb,
@@ -837,30 +887,30 @@ extern "C" int r2p_cnn_backward(r2p_cnn *C, const uint16_t *feat, const float *t
     Geo g = make_geo(nb, nz, ny, nx);
     long V = g.V();
     R2P_TRY(ensure_acts(C, V));
-    R2P_TRY(forward_impl(C, feat, g, s));
+    R2P_TRY(C->out2.ensure(2 * (size_t)V));
+    for (DBuf<u16> *t : {&C->g0, &C->g1, &C->g2}) R2P_TRY(t->ensure((size_t)V * CH));
+    R2P_TRY(aligned_features(C, feat, V, s));
+    R2P_TRY(forward_impl(C, feat, g, C->out2.p, s));
     int nbl = r2p_blocks(V, CBS);
     R2P_TRY(C->lpart.ensure(nbl));
-    k_mse<<<nbl, CBS, 0, s>>>(C->outf.p, target, V, 1.0f / (float)(V * NOUT), C->g0.p, C->lpart.p);
+    k_mse<<<nbl, CBS, 0, s>>>(C->out2.p, target, V, 1.0f / (float)(V * NOUT), C->g0.p, C->lpart.p);
     R2P_LAUNCH();
     // output layer
     int lo = C->L - 1, K = C->K;
-    R2P_TRY(weight_grad(C, C->g0.p, C->act[2 * K + 1].p, g, lo, s));
+    R2P_TRY(weight_grad(C, C->g0.p, C->act[2 * K].p, g, lo, s));
     R2P_TRY(input_grad(C, C->g0.p, g, lo, nullptr, nullptr, C->g1.p, s));   // gh
     u16 *gh = C->g1.p, *ga = C->g2.p, *spare = C->g0.p;
     for (int k = K - 1; k >= 0; k--) {
         int la = 1 + 2 * k, lb = 2 + 2 * k;
-        const u16 *a = C->act[2 + 2 * k].p, *h = C->act[1 + 2 * k].p;
+        const u16 *a = C->act[1 + 2 * k].p, *h = C->act[2 * k].p;
         R2P_TRY(weight_grad(C, gh, a, g, lb, s));
         R2P_TRY(input_grad(C, gh, g, lb, a, nullptr, ga, s));               // ga = (W_b^T gh) (a > 0)
         R2P_TRY(weight_grad(C, ga, h, g, la, s));
-        R2P_TRY(input_grad(C, ga, g, la, nullptr, gh, spare, s));          // gh' = gh + W_a^T ga
+        // gh' = gh + W_a^T ga; the input layer needs it only where h0 > 0
+        R2P_TRY(input_grad(C, ga, g, la, k == 0 ? h : nullptr, gh, spare, s));
         std::swap(gh, spare);
     }
-    // input layer: g0 = gh (h0 > 0)
-    u16 *g0m = spare;
-    k_mask_mul<<<r2p_blocks(V * CH, 256), 256, 0, s>>>(gh, C->act[1].p, V * CH, g0m);
-    R2P_LAUNCH();
-    R2P_TRY(weight_grad(C, g0m, C->act[0].p, g, 0, s));
+    R2P_TRY(weight_grad(C, gh, feat, g, 0, s));
     if (loss_host) {
         std::vector<double> lp(nbl);
         R2P_HIP(hipStreamSynchronize(s));

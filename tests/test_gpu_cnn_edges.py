@@ -40,3 +40,48 @@ def test_weight_gradient_at_tile_edges(shape):
     # the bias sums cancel: bound by the sum of magnitudes
     mag = np.abs(g).reshape(-1, 32).sum(0)
     assert np.all(np.abs(db.cpu().numpy() - rdb) <= 1e-6 * mag + 1e-12)
+
+
+# k_conv walks columns of 16 x 16 voxels through ranges of planes
+CONV_SHAPES = SHAPES + [(1, 3, 16, 16), (2, 4, 17, 15), (1, 2, 1, 33), (300, 1, 3, 2), (1, 64, 2, 2)]
+
+
+@pytest.mark.parametrize("flip", [False, True])
+@pytest.mark.parametrize("shape", CONV_SHAPES)
+def test_layer_at_column_edges(shape, flip):
+    from oracle import cnn
+    from paper_1701_06254_amd import r2p
+    rng = np.random.default_rng(sum(shape) + 1)
+    x_t, x = _bits(rng.normal(size=shape + (32,)))
+    W = cnn.bf16_round(rng.normal(0, 0.05, size=(27, 32, 32)))
+    w_t, _ = _bits(np.ascontiguousarray(W.transpose(0, 2, 1)) if flip else W)
+    a_t, a = _bits(rng.normal(size=shape + (32,)))
+    m_t, m = _bits(rng.normal(size=shape + (32,)))
+    b = rng.normal(size=32).astype(np.float32)
+    V = int(np.prod(shape))
+    outf = torch.full((V * 32,), float("nan"), dtype=torch.float32, device="cuda")
+    r2p.cnn_conv(x_t, shape, w_t, bias=torch.from_numpy(b).cuda(), addend=a_t, mask=m_t, flip=flip,
+                 outf=outf)
+    ref = cnn.conv_grad_input(x, W) if flip else cnn.conv(x, W, np.zeros(32))
+    ref = (ref + b + a) * (m > 0)
+    got = outf.cpu().numpy().astype(np.float64).reshape(ref.shape)
+    assert np.max(np.abs(got - ref)) <= 1e-5 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("shape", [(1, 1, 1, 1), (2, 3, 17, 33)])
+def test_features_at_any_alignment(shape):
+    """The feature tensor may start at any 2-byte address: same results as
+    from an aligned one."""
+    from oracle import cnn
+    from paper_1701_06254_amd import r2p
+    rng = np.random.default_rng(5)
+    net = r2p.Cnn(blocks=1)
+    net.set_params(cnn.init_params(rng, 32, 1).astype(np.float32))
+    V = int(np.prod(shape))
+    f = np.zeros((V, 32))
+    f[:, :6] = rng.normal(size=(V, 6))
+    f_t, _ = _bits(f)
+    ref = net.forward(f_t, shape).clone()
+    shifted = torch.zeros(V * 32 + 1, dtype=torch.int16, device="cuda")
+    shifted[1:] = f_t.reshape(-1)
+    assert torch.equal(net.forward(shifted[1:], shape), ref)
