@@ -126,26 +126,54 @@ __host__ __device__ inline int slot_offset(int s, int nx, int nxy) {
 }
 
 // ------------------------------------------------------------------ RAS
-// Block ILU(0) factors of every overlapped subdomain.  Rows ("positions" p,
-// concatenated over subdomains) are stored in level order of each
-// subdomain's dependency graph, rows of a level sorted by descending number
-// of predecessors.  Every level is cut into slices of RAS_ROWS consecutive
-// positions, one wavefront per slice and two lanes per row (lane 2r + h
-// holds the entries e = h, h + 2, ... of row r).  A slice stores its L
-// blocks (predecessors, ascending local order) and its U blocks (successors)
-// in sliced-ELL form with RAS_SLICE entries per column: entry e of row r
-// sits at base + (e / 2) RAS_SLICE + 2r + (e mod 2), so each load
-// instruction of a wavefront is contiguous.  Padding entries (e >= the
-// row's count) hold column -1 and zero blocks.
+// Block ILU(0) factors of every overlapped subdomain.  The rows of each
+// subdomain are stored in level order of its dependency graph, rows of a
+// level sorted by descending number of predecessors, long ones (more than
+// RAS_MAIN predecessors or successors) first.  Every level is cut into slices
+// of RAS_ROWS positions, one wavefront per slice and two lanes per position
+// (lane 2r + h of position r holds the entries e = h, h + 2, .. of its row).
+// Position r of slice sl is 32 sl + r.  A long row takes two positions, an
+// even one and the next, whose lanes hold its entries RAS_MAIN to 2 RAS_MAIN
+// - 1; that second position, like those behind a level's last row, belongs to
+// no row (no counts, a zero diagonal block).  So everything a slice needs lies
+// at a fixed multiple of its number and a sweep reads it with no address
+// arithmetic of its own.  Entries are a row's predecessors in L, successors
+// in U, in ascending local order; unused ones have column -1 and a zero
+// block.  Those past 2 RAS_MAIN, which only well rows have, sit in an overflow
+// region behind the main entries of all slices, 64 entries per pair of columns.
 constexpr int RAS_SLICE = 64;
 constexpr int RAS_ROWS = 32;
-__host__ __device__ inline long ras_entry(long base, int r, int e) {
-    return base + (long)(e >> 1) * RAS_SLICE + 2 * r + (e & 1);
+constexpr int RAS_MAIN = 4;
+constexpr int RAS_MENT = RAS_MAIN * RAS_ROWS;      // main entries of a slice
+// Where the entries of the row at position p are.
+struct RasRow {
+    long b, x;
+    // xb[sl]: the slice's overflow start, less the pairs before it
+    __host__ __device__ RasRow(const int *xb, int p) {
+        int sl = p / RAS_ROWS, r = p % RAS_ROWS;
+        b = (long)sl * RAS_MENT + 2 * r;
+        x = (long)xb[sl] + 2 * r;
+    }
+    __host__ __device__ long operator()(int e) const {
+        // b; the next position's lanes, from their first pair; the overflow
+        long o = e < RAS_MAIN ? b : (e < 2 * RAS_MAIN ? b + 2 - RAS_MENT : x);
+        return o + (long)(e >> 1) * RAS_SLICE + (e & 1);
+    }
+};
+// First value of row j (0, 1) of entry k's 2x2 block in the factor arrays: the
+// sweep's lane 2r + h needs the whole block of entry h, row h first, and rows
+// h of the blocks of entries 2 and 3, so that a slice takes one contiguous
+// load per wavefront for each of: entries 0 and 1 row h, their row 1 - h,
+// entry 2, entry 3.
+__host__ __device__ inline long ras_val(long k, int j) {
+    int i = (int)(k & 63), h = i & 1;
+    long v = (k >> 6) * 256;
+    return (k >> 6) & 1 ? v + h * 128 + (i - h + j) * 2 : v + (j == h ? 0 : 128) + i * 2;
 }
 template <class T>
 struct RasFactors {
-    DBuf<T> lval, uval;   // 4 per entry (row-major 2x2)
-    DBuf<T> dinv;         // 4 per position: inverse of U's diagonal block
+    DBuf<T> lval, uval;   // 4 per entry, laid out by ras_val
+    DBuf<T> dinv;         // 4 per position: inverse of U's diagonal block (row-major)
 };
 
 struct RasStatic {
@@ -163,7 +191,8 @@ struct RasStatic {
 
 struct RasDyn {
     int maxlev = 0;
-    int nseg = 0, nslice = 0, nlent = 0, nuent = 0;
+    int nseg = 0, nslice = 0, npos = 0;   // levels, slices, positions over all subdomains
+    long nlent = 0, nuent = 0;            // L and U entries (main and overflow)
     std::vector<int> h_nlev;              // levels per subdomain
     std::vector<int> h_lbase;             // first segment (level) index per subdomain
     DBuf<int> lev;                        // mtot: level of local row (natural)
@@ -172,25 +201,28 @@ struct RasDyn {
     DBuf<unsigned char> apred;            // nadj: coupling e of row l is a predecessor of l
     DBuf<int> nlnat, nunat;               // mtot: predecessor / successor counts (natural)
     DBuf<int> pos;                        // mtot: position of local row
-    DBuf<int> perm;                       // mtot: local row (natural) at position
-    DBuf<int> glob;                       // mtot: global row at position
-    DBuf<unsigned char> owned;            // mtot
-    DBuf<int> nl, nu;                     // mtot: counts per position
-    DBuf<int> lptr_dev;                   // nseg+1: first position of every level
+    DBuf<int> perm;                       // npos: local row (natural) at position, -1 unused
+    DBuf<int> glob;                       // npos: global row at position, -1 unused
+    DBuf<unsigned char> owned;            // npos
+    DBuf<int> nl, nu;                     // npos: counts per position
+    DBuf<int> lptr_dev;                   // nseg+1: rows before every level
+    DBuf<int> nlong;                      // nseg: long rows of every level
     DBuf<int> soff;                       // nseg+1: first slice of every level
-    DBuf<int> sl_start, sl_cnt, sl_wl, sl_wu, sl_bl, sl_bu;   // per slice
-    DBuf<int> sl_of;                      // mtot: slice of every position
-    DBuf<int4> meta_l, meta_u;            // per slice: (start, rows | slot pairs << 8, entry base, level) of L / U
-    DBuf<int> lcol, ucol;                 // entries: column position (-1 padding)
+    DBuf<int> xl_b, xu_b;                 // nslice+1: overflow starts (see RasRow)
+    DBuf<int> wl, wu;                     // nslice: entries of the longest L / U part
+    DBuf<int> wlong;                      // nslice: long rows
+    DBuf<int4> meta_l, meta_u;            // per slice: what the sweep needs (see k_sweep_cols)
+    DBuf<int> lcol, ucol;                 // entries: column position (-1 unused)
+    DBuf<int> lsw, usw;                   // the same for the sweep, with each column's source of y
     DBuf<int> lsrc, usrc;                 // entries: block source (set-up only)
-    DBuf<int> dsrc_pos;                   // mtot: diagonal block source per position
+    DBuf<int> dsrc_pos;                   // npos: diagonal block source per position
     DBuf<int> ldiag;                      // L entries: entry of U_qp in row q (set-up only)
-    DBuf<int> xptr;                       // mtot+1: extra ILU(0) matches per position
+    DBuf<int> xptr;                       // npos+1: extra ILU(0) matches per position
     DBuf<int4> xl;                        // extra matches (set-up only)
     DBuf<int> sub_lbase;                  // ns: first segment of the subdomain
     DBuf<int> sub_nlev;                   // ns
     DBuf<int> counters;                   // scratch
-    DBuf<int> prog;                       // ns: sweep progress read by the prefetch helpers
+    DBuf<int> prog;                       // ns: slices finished, read by the prefetch helpers
     DBuf<int> swin;                       // ns: ring window of every subdomain's sweep
     RasFactors<double> f64;
     RasFactors<float> f32;

@@ -9,52 +9,54 @@
 // successors stay in local order, so every block update happens in the same
 // sequence as a sequential ILU(0) in that order and the factors match it.
 //
-// One workgroup (8 wavefronts) processes one subdomain level by level, a
-// workgroup barrier between levels; a wavefront takes a slice of 32 rows of
-// a level, two lanes per row (each lane takes every other block of the row;
-// a lane holds two blocks in registers, which covers the L or U part of all
-// but a few rows: the rows of a slice with more than four blocks, well rows
-// and a few others, read the rest from memory), and the wavefronts take the
-// slices of the subdomain in turn.  Levels are a
-// latency chain, so nothing a step waits for is requested in that step:
-// the static data of a slice (columns, factor blocks, right-hand side) are
-// requested three and four steps ahead; the y values its rows need that
-// were finished two steps earlier are requested then; the rest were
-// finished in the last few levels and are read from an LDS ring that holds
-// the results of the most recent rows.  Which of these applies to an entry
-// follows from the fixed schedule, so the set-up marks it in the entry's
-// column.  One CU streams a subdomain's factors
-// at the rate its outstanding L2 misses allow, so helper workgroups of the
-// same launch, placed on the subdomain's XCD, read the static data of the
+// One workgroup (16 wavefronts) processes one subdomain level by level; a
+// wavefront takes a slice of 32 positions of a level, two lanes per position
+// (which hold four blocks of the row in registers; rows with more take two
+// positions, and only rows with more than eight, well rows, read the rest from
+// memory), and the wavefronts take the slices of the subdomain in turn.  A
+// slice may run when all slices of the levels before it are done: the
+// wavefronts count finished slices in LDS and wait on that count alone, so one
+// that has no slice in a level is not held up by it and requests its next data
+// meanwhile.  Levels are a latency chain, so nothing a step waits for is
+// requested in that step: the static data of a slice (columns, factor blocks,
+// right-hand side) and those y values its rows need that were finished by then
+// are requested two steps ahead; the rest were finished in the last few levels
+// and are read from an LDS ring that holds the results of the most recent
+// rows.  Which of these applies to an entry follows from the fixed schedule, so
+// the set-up marks it in the entry's column.  One CU streams a subdomain's
+// factors at the rate its outstanding L2 misses allow, so helper workgroups of
+// the same launch, placed on the subdomain's XCD, read the static data of the
 // slices some levels ahead of the sweep into that XCD's L2; the sweep then
-// finds them in L2 rather than in HBM.  The gather of the right-hand side
-// into local order and the restricted scatter of the result run as separate
-// full-device kernels.
+// finds them in L2 rather than in HBM (at 2M cells and 16 subdomains an
+// application takes 1,122 us without helpers, 762 with 8 each, 754 with 15).
+// The gather of the right-hand side into local order and the restricted
+// scatter of the result run as separate full-device kernels.
 //
 // Compiled without floating-point contraction (reproducible block products).
 #include <algorithm>
 #include <cstring>
+#include <tuple>
 
 #include "r2p_impl.h"
 
 constexpr int BS = 256;
 constexpr int WG = 1024;               // threads of a subdomain workgroup
 constexpr int NWAVE = WG / 64;
-// Sweep workgroup: 8 wavefronts of up to 256 VGPRs (FP64), 12 of up to 168
-// (FP32, whose buffers fit in that); the wavefronts take a subdomain's slices
-// in turn.
+// Sweep workgroup: 16 wavefronts of up to 128 VGPRs, two tasks' data in flight
+// each; the wavefronts take a subdomain's slices in turn.  (8 wavefronts with
+// four tasks each: 883 us per application at 2M cells and 16 subdomains where
+// 16 with two took 817; 12 with two, 820.)
 template <class T>
 struct Sweep {
-    static constexpr int wg = sizeof(T) == 4 ? 768 : 512;
+    static constexpr int wg = 1024;
     static constexpr int ncw = wg / 64;
 };
-constexpr int LK = 4;                  // sweep: slot pairs per round of a long (well) row
-constexpr int MAXK = 2;                // entries per lane held in registers (two lanes per row)
-constexpr int RAS_PAD = MAXK * RAS_SLICE;   // padding after the entry arrays: every task reads MAXK slot pairs
+constexpr int LK = 2;                  // sweep: slot pairs per round of a long (well) row
+constexpr int MAXK = RAS_MAIN / 2;     // entries per lane held in registers (two lanes per row)
 constexpr int MAXLEV = 4096;           // levels per subdomain (set-up limit)
 constexpr int PROG_STRIDE = 64;        // ints between two sweeps' progress counters
-// A factor entry's column (local position, < 2^28) carries in its top bits
-// where the sweep finds that column's y value (set after the factorisation):
+// The sweep's copy of a factor entry's column (local position, < 2^28) carries
+// in its top bits where the sweep finds that column's y value:
 constexpr int COL_BITS = 28;
 constexpr int COL_MASK = (1 << COL_BITS) - 1;
 constexpr int F_RING = 0;              // the LDS ring (finished in the last levels)
@@ -185,33 +187,45 @@ __global__ void k_pred_count(int mtot, int n, int order, const double *phi, cons
     nu[l] = aptr[l + 1] - aptr[l] - a;
 }
 
+// A row that takes two positions.
+__device__ __forceinline__ bool is_long(int nl, int nu) { return max(nl, nu) > RAS_MAIN; }
+
 __global__ void k_level_count(int mtot, const int *sub_of, const int *lev, const int *lbase,
-                              int *cnt) {
+                              const int *nl, const int *nu, int *cnt, int *nlong) {
     int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= mtot) return;
-    atomicAdd(&cnt[lbase[sub_of[l]] + lev[l]], 1);
+    int seg = lbase[sub_of[l]] + lev[l];
+    atomicAdd(&cnt[seg], 1);
+    if (is_long(nl[l], nu[l])) atomicAdd(&nlong[seg], 1);
 }
 
-// Sort key of a row: its level segment, then descending predecessor count
-// (so the widest rows of a level share slices); the sort is stable, rows with
-// equal keys stay in natural local order.
+// Sort key of a row: its level segment, then long rows (key 0) before the
+// others in descending predecessor count; the sort is stable, rows with equal
+// keys stay in natural local order.
 __global__ void k_order_keys(int mtot, const int *sub_of, const int *lev, const int *lbase,
-                             const int *nl, unsigned *key, unsigned *val) {
+                             const int *nl, const int *nu, unsigned *key, unsigned *val) {
     int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= mtot) return;
     unsigned seg = (unsigned)(lbase[sub_of[l]] + lev[l]);
-    unsigned w = 7u - (unsigned)min(nl[l], 7);
+    unsigned w = is_long(nl[l], nu[l]) ? 0u : (unsigned)(RAS_MAIN + 1 - nl[l]);
     key[l] = (seg << 3) | w;
     val[l] = (unsigned)l;
 }
 
-__global__ void k_perm_gather(int mtot, const unsigned *perm, const int *glob_nat,
-                              const unsigned char *owned_nat, const int *nlnat, const int *nunat,
-                              const int *dsrc_nat, int *pos, int *permi, int *glob,
-                              unsigned char *owned, int *nl, int *nu, int *dsrc) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= mtot) return;
-    int l = (int)perm[p];
+// Positions of the sorted rows (key: segment << 3 | ..): slices of RAS_ROWS
+// positions per level, a level's first slice at soff; two positions per long
+// row.
+__global__ void k_perm_gather(int mtot, const unsigned *key, const unsigned *perm, const int *lptr,
+                              const int *nlong, const int *soff, const int *glob_nat,
+                              const unsigned char *owned_nat,
+                              const int *nlnat, const int *nunat, const int *dsrc_nat, int *pos,
+                              int *permi, int *glob, unsigned char *owned, int *nl, int *nu,
+                              int *dsrc) {
+    int q = blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= mtot) return;
+    int l = (int)perm[q], seg = (int)(key[q] >> 3);
+    int i = q - lptr[seg];
+    int p = RAS_ROWS * soff[seg] + i + min(i, nlong[seg]);
     permi[p] = l;
     pos[l] = p;
     glob[p] = glob_nat[l];
@@ -221,82 +235,80 @@ __global__ void k_perm_gather(int mtot, const unsigned *perm, const int *glob_na
     dsrc[p] = dsrc_nat[l];
 }
 
-__global__ void k_slice_count(int nseg, const int *lptr, int *nsl) {
+__global__ void k_slice_count(int nseg, const int *lptr, const int *nlong, int *nsl) {
     int g = blockIdx.x * blockDim.x + threadIdx.x;
-    if (g < nseg) nsl[g] = (lptr[g + 1] - lptr[g] + RAS_ROWS - 1) / RAS_ROWS;
+    if (g < nseg) nsl[g] = (lptr[g + 1] - lptr[g] + nlong[g] + RAS_ROWS - 1) / RAS_ROWS;
     if (g == nseg) nsl[g] = 0;
 }
 
-// One thread per slice: rows, widths, and the slice of every position.
-__global__ void k_slice_fill(int nseg, const int *lptr, const int *soff, int nslice,
-                             const int *nl, const int *nu, int *st, int *cn, int *wl, int *wu,
-                             int *sl_of) {
-    int g = blockIdx.x;             // one workgroup per level segment
-    if (g >= nseg) return;
-    int a = soff[g], b = soff[g + 1];
-    for (int sl = a + (int)threadIdx.x; sl < b; sl += blockDim.x) {
-        int start = lptr[g] + (sl - a) * RAS_ROWS;
-        int cnt = min(RAS_ROWS, lptr[g + 1] - start);
-        int ml = 0, mu = 0;
-        for (int t = 0; t < cnt; t++) {
-            ml = max(ml, nl[start + t]);
-            mu = max(mu, nu[start + t]);
-            sl_of[start + t] = sl;
-        }
-        st[sl] = start;
-        cn[sl] = cnt;
-        wl[sl] = ml;
-        wu[sl] = mu;
+// Entries of every slice's longest L and U part, its long rows, and the
+// overflow entries beyond the main ones; 32 lanes per slice.
+__global__ void k_slice_width(int nslice, const int *nl, const int *nu, int *wl, int *wu,
+                              int *wlong, int *xl, int *xu) {
+    int p = blockIdx.x * blockDim.x + threadIdx.x, sl = p / RAS_ROWS;
+    if (p == 0) xl[nslice] = xu[nslice] = 0;
+    if (sl >= nslice) return;
+    int ml = nl[p], mu = nu[p], lg = is_long(ml, mu);
+    for (int d = 1; d < RAS_ROWS; d <<= 1) {
+        ml = max(ml, __shfl_xor(ml, d, 64));
+        mu = max(mu, __shfl_xor(mu, d, 64));
+        lg += __shfl_xor(lg, d, 64);
     }
+    if (p % RAS_ROWS) return;
+    wl[sl] = ml;
+    wu[sl] = mu;
+    wlong[sl] = lg;
+    xl[sl] = max(0, (ml + 1) / 2 - RAS_MAIN) * RAS_SLICE;
+    xu[sl] = max(0, (mu + 1) / 2 - RAS_MAIN) * RAS_SLICE;
 }
 
-__global__ void k_slice_size(int nslice, const int *w, int *sz) {
+// Scanned overflow offsets to the starts that RasRow expects.
+__global__ void k_overflow_base(int nslice, int *xl, int *xu) {
     int sl = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sl < nslice) sz[sl] = (w[sl] + 1) / 2 * RAS_SLICE;
-    if (sl == nslice) sz[sl] = 0;
+    if (sl >= nslice) return;
+    xl[sl] += (nslice - 2) * RAS_MENT;
+    xu[sl] += (nslice - 2) * RAS_MENT;
 }
 
 // Entries of position p in its slice: predecessors and successors, each in
 // ascending local order (insertion sort over the strided slots).
 __device__ __forceinline__ void fill_row_long(int p, int n, int order, const double *phi, const int *permi,
                               const int *glob_nat, const int *aptr, const int *adj,
-                               const int *asrc, const int *pos, const int *glob, const int *sl_of,
-                              const int *sl_st, const int *sl_bl, const int *sl_bu, int *lcol,
-                              int *lsrc, int *ucol, int *usrc) {
+                              const int *asrc, const int *pos, const int *glob, const int *xlb,
+                              const int *xub, int *lcol, int *lsrc, int *ucol, int *usrc) {
     int l = permi[p], g = glob_nat[l];
-    int sl = sl_of[p], r = p - sl_st[sl];
-    long bl = sl_bl[sl], bu = sl_bu[sl];
+    const RasRow rl(xlb, p), ru(xub, p);
     int el = 0, eu = 0;
     for (int t = aptr[l]; t < aptr[l + 1]; t++) {
         int h = adj[t];
         int gh = glob_nat[h];
         if (before(gh, g, n, order, phi)) {
-            long k = ras_entry(bl, r, el++);
+            long k = rl(el++);
             lcol[k] = pos[h];
             lsrc[k] = asrc[t];
         } else {
-            long k = ras_entry(bu, r, eu++);
+            long k = ru(eu++);
             ucol[k] = pos[h];
             usrc[k] = asrc[t];
         }
     }
     for (int part = 0; part < 2; part++) {
         int cnt = part == 0 ? el : eu;
-        long b = part == 0 ? bl : bu;
+        const RasRow &at = part == 0 ? rl : ru;
         int *col = part == 0 ? lcol : ucol;
         int *src = part == 0 ? lsrc : usrc;
         for (int u = 1; u < cnt; u++) {
-            long ku = ras_entry(b, r, u);
+            long ku = at(u);
             int vc = col[ku], vs = src[ku];
             int vg = glob[vc];
             int k = u - 1;
-            while (k >= 0 && before(vg, glob[col[ras_entry(b, r, k)]], n, order, phi)) {
-                col[ras_entry(b, r, k + 1)] = col[ras_entry(b, r, k)];
-                src[ras_entry(b, r, k + 1)] = src[ras_entry(b, r, k)];
+            while (k >= 0 && before(vg, glob[col[at(k)]], n, order, phi)) {
+                col[at(k + 1)] = col[at(k)];
+                src[at(k + 1)] = src[at(k)];
                 k--;
             }
-            col[ras_entry(b, r, k + 1)] = vc;
-            src[ras_entry(b, r, k + 1)] = vs;
+            col[at(k + 1)] = vc;
+            src[at(k + 1)] = vs;
         }
     }
 }
@@ -318,18 +330,18 @@ __device__ __forceinline__ bool before_v(int h, double ph, int g, double pg, int
     return ph > pg || (ph == pg && h < g);
 }
 
-__global__ void k_fill_entries(int mtot, int n, int order, const double *phi, const int *permi,
+__global__ void k_fill_entries(int npos, int n, int order, const double *phi, const int *permi,
                                const int *glob_nat, const int *aptr, const int *adj,
-                               const int *asrc, const int *pos, const int *glob, const int *sl_of,
-                               const int *sl_st, const int *sl_bl, const int *sl_bu, int *lcol,
-                               int *lsrc, int *ucol, int *usrc) {
+                               const int *asrc, const int *pos, const int *glob, const int *xlb,
+                               const int *xub, int *lcol, int *lsrc, int *ucol, int *usrc) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= mtot) return;
+    if (p >= npos) return;
     int l = permi[p];
+    if (l < 0) return;
     int t0 = aptr[l], deg = aptr[l + 1] - t0;
     if (deg > FE) {
-        fill_row_long(p, n, order, phi, permi, glob_nat, aptr, adj, asrc, pos, glob, sl_of, sl_st,
-                      sl_bl, sl_bu, lcol, lsrc, ucol, usrc);
+        fill_row_long(p, n, order, phi, permi, glob_nat, aptr, adj, asrc, pos, glob, xlb, xub, lcol,
+                      lsrc, ucol, usrc);
         return;
     }
     const bool pot = order != R2P_ORDER_NATURAL;
@@ -364,18 +376,17 @@ __global__ void k_fill_entries(int mtot, int n, int order, const double *phi, co
             }
         }
     }
-    int sl = sl_of[p], r = p - sl_st[sl];
-    long bl = sl_bl[sl], bu = sl_bu[sl];
+    const RasRow rl(xlb, p), ru(xub, p);
     int el = 0, eu = 0;
 #pragma unroll
     for (int k = 0; k < FE; k++) {
         if (k < deg) {
             if (before_v(gh[k], pv[k], g, pg, n, order)) {
-                long e = ras_entry(bl, r, el++);
+                long e = rl(el++);
                 lcol[e] = ps[k];
                 lsrc[e] = sr[k];
             } else {
-                long e = ras_entry(bu, r, eu++);
+                long e = ru(eu++);
                 ucol[e] = ps[k];
                 usrc[e] = sr[k];
             }
@@ -399,60 +410,59 @@ __global__ void k_fill_entries(int mtot, int n, int order, const double *phi, co
 // loop, with the same expressions, so the factors are the same.
 struct FactArgs {
     BlkSrc B;
+    int npos;
     const int *lbase, *nlev, *soff;
-    const int *sl_st, *sl_cn, *sl_bl, *sl_bu, *sl_of;
+    const int *xlb, *xub, *glob;
     const int *nl, *nu, *dsrc, *lcol, *ucol, *lsrc, *usrc;
     int *ldiag;                  // per L entry: entry index of U_qp in row q
-    int *xptr;                   // mtot+1: first extra match of every position
+    int *xptr;                   // npos+1: first extra match of every position
     int4 *xl;                    // extra matches: (e, e2, entry index in row q's U, 0)
     double *lval, *uval, *dinv;
     int *status;
 };
 
-// Entry e of position p in the L (sl_b = sl_bl) or U (sl_bu) arrays.
-__device__ __forceinline__ long slice_entry(const int *sl_of, const int *sl_st, const int *sl_b,
-                                            int p, int e) {
-    int sl = sl_of[p];
-    return ras_entry(sl_b[sl], p - sl_st[sl], e);
+// Block k of a factor array.
+__device__ __forceinline__ void ld_blk(double *v, const double *arr, long k) {
+    const double2 a = *(const double2 *)&arr[ras_val(k, 0)],
+                  b = *(const double2 *)&arr[ras_val(k, 1)];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+}
+__device__ __forceinline__ void st_blk(double *arr, long k, const double *v) {
+    *(double2 *)&arr[ras_val(k, 0)] = make_double2(v[0], v[1]);
+    *(double2 *)&arr[ras_val(k, 1)] = make_double2(v[2], v[3]);
 }
 
-// Entry e of a row whose entry 0 sits at rb (rb = ras_entry(base, r, 0)).
-__device__ __forceinline__ long ent(long rb, int e) {
-    return rb + (long)(e >> 1) * RAS_SLICE + (e & 1);
-}
-
-__global__ void k_bilu_gather(int mtot, FactArgs A) {
+__global__ void k_bilu_gather(FactArgs A) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= mtot) return;
+    if (p >= A.npos || A.glob[p] < 0) return;
     int nlp = A.nl[p], nup = A.nu[p];
-    long bl = slice_entry(A.sl_of, A.sl_st, A.sl_bl, p, 0);
-    long bu = slice_entry(A.sl_of, A.sl_st, A.sl_bu, p, 0);
+    const RasRow rl(A.xlb, p), ru(A.xub, p);
+    double v[4];
     for (int e = 0; e < nlp; e++) {
-        long k = ent(bl, e);
-        load_block(A.B, A.lsrc[k], &A.lval[4 * k]);
+        load_block(A.B, A.lsrc[rl(e)], v);
+        st_blk(A.lval, rl(e), v);
     }
     for (int e = 0; e < nup; e++) {
-        long k = ent(bu, e);
-        load_block(A.B, A.usrc[k], &A.uval[4 * k]);
+        load_block(A.B, A.usrc[ru(e)], v);
+        st_blk(A.uval, ru(e), v);
     }
     load_block(A.B, A.dsrc[p], &A.dinv[4 * (long)p]);
 }
 
 // Pass 0 counts the extra matches of every position and records the
 // diagonal match of every L entry; pass 1 writes the extra matches.
-__device__ __forceinline__ void bilu_sym_long(const FactArgs &A, int p, int nlp, int nup, long bl,
-                                              long bu, int pass) {
+__device__ __forceinline__ void bilu_sym_long(const FactArgs &A, int p, int nlp, int nup,
+                                              const RasRow &rl, const RasRow &ru, int pass) {
     int cnt = 0, out = pass ? A.xptr[p] : 0;
     for (int e = 0; e < nlp; e++) {
-        long k = ent(bl, e);
+        long k = rl(e);
         int q = A.lcol[k];
-        long buq = slice_entry(A.sl_of, A.sl_st, A.sl_bu, q, 0);
+        const RasRow rq(A.xub, q);
         int nuq = A.nu[q];
         for (int e2 = e + 1; e2 <= nlp + nup; e2++) {
-            int cj = e2 < nlp ? A.lcol[ent(bl, e2)]
-                              : (e2 == nlp ? p : A.ucol[ent(bu, e2 - nlp - 1)]);
+            int cj = e2 < nlp ? A.lcol[rl(e2)] : (e2 == nlp ? p : A.ucol[ru(e2 - nlp - 1)]);
             for (int y = 0; y < nuq; y++) {
-                long ky = ent(buq, y);
+                long ky = rq(y);
                 if (A.ucol[ky] != cj) continue;
                 if (e2 == nlp) {
                     if (pass == 0) A.ldiag[k] = (int)ky;
@@ -474,14 +484,17 @@ __device__ __forceinline__ void bilu_sym_long(const FactArgs &A, int p, int nlp,
 // loop's.
 constexpr int SE = 8;
 
-__global__ void k_bilu_sym(int mtot, FactArgs A, int pass) {
+__global__ void k_bilu_sym(FactArgs A, int pass) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= mtot) return;
+    if (p >= A.npos) return;
+    if (A.glob[p] < 0) {
+        if (pass == 0) A.xptr[p] = 0;
+        return;
+    }
     int nlp = A.nl[p], nup = A.nu[p];
-    long bl = slice_entry(A.sl_of, A.sl_st, A.sl_bl, p, 0);
-    long bu = slice_entry(A.sl_of, A.sl_st, A.sl_bu, p, 0);
+    const RasRow rl(A.xlb, p), ru(A.xub, p);
     if (nlp + nup > SE) {
-        bilu_sym_long(A, p, nlp, nup, bl, bu, pass);
+        bilu_sym_long(A, p, nlp, nup, rl, ru, pass);
         return;
     }
     // the row's entries in order: L columns, p itself, U columns
@@ -489,34 +502,28 @@ __global__ void k_bilu_sym(int mtot, FactArgs A, int pass) {
 #pragma unroll
     for (int k = 0; k <= SE; k++) {
         c[k] = -1;
-        if (k < nlp) c[k] = A.lcol[ent(bl, k)];
+        if (k < nlp) c[k] = A.lcol[rl(k)];
         else if (k == nlp) c[k] = p;
-        else if (k <= nlp + nup) c[k] = A.ucol[ent(bu, k - nlp - 1)];
+        else if (k <= nlp + nup) c[k] = A.ucol[ru(k - nlp - 1)];
     }
-    long buq[SE];
     int nuq[SE];
 #pragma unroll
-    for (int e = 0; e < SE; e++) {
-        buq[e] = 0;
-        nuq[e] = 0;
-        if (e < nlp) {
-            buq[e] = slice_entry(A.sl_of, A.sl_st, A.sl_bu, c[e], 0);
-            nuq[e] = A.nu[c[e]];
-        }
-    }
+    for (int e = 0; e < SE; e++) nuq[e] = e < nlp ? A.nu[c[e]] : 0;
     bool fits = true;
 #pragma unroll
     for (int e = 0; e < SE; e++) fits = fits && nuq[e] <= SE;
     if (!fits) {
-        bilu_sym_long(A, p, nlp, nup, bl, bu, pass);
+        bilu_sym_long(A, p, nlp, nup, rl, ru, pass);
         return;
     }
     int u[SE][SE];
 #pragma unroll
-    for (int e = 0; e < SE; e++)
+    for (int e = 0; e < SE; e++) {
+        const RasRow rq(A.xub, e < nlp ? c[e] : p);
 #pragma unroll
         for (int y = 0; y < SE; y++)
-            u[e][y] = (e < nlp && y < nuq[e]) ? A.ucol[ent(buq[e], y)] : -2;
+            u[e][y] = (e < nlp && y < nuq[e]) ? A.ucol[rq(y)] : -2;
+    }
     int cnt = 0, out = pass ? A.xptr[p] : 0;
 #pragma unroll
     for (int e = 0; e < SE; e++) {
@@ -529,9 +536,9 @@ __global__ void k_bilu_sym(int mtot, FactArgs A, int pass) {
             for (int yy = SE - 1; yy >= 0; yy--)
                 if (u[e][yy] == c[e2]) y = yy;
             if (y < 0) continue;
-            long ky = ent(buq[e], y);
+            long ky = RasRow(A.xub, c[e])(y);
             if (e2 == nlp) {
-                if (pass == 0) A.ldiag[ent(bl, e)] = (int)ky;
+                if (pass == 0) A.ldiag[rl(e)] = (int)ky;
             } else {
                 if (pass) A.xl[out + cnt] = make_int4(e, e2, (int)ky, 0);
                 cnt++;
@@ -548,37 +555,45 @@ __device__ __forceinline__ void sub_prod(double *t, const double *l, const doubl
     t[3] -= l[2] * u[1] + l[3] * u[3];
 }
 
-__device__ __forceinline__ void ld4(double *v, const double *p) {
-    const double2 a = ((const double2 *)p)[0], b = ((const double2 *)p)[1];
-    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
+// t -= l u for blocks of the factor arrays.
+__device__ __forceinline__ void sub_prod_at(double *tarr, long kt, const double *l,
+                                            const double *uarr, long ku) {
+    double t[4], u[4];
+    ld_blk(t, tarr, kt);
+    ld_blk(u, uarr, ku);
+    sub_prod(t, l, u);
+    st_blk(tarr, kt, t);
 }
 
 // L entry e of row p (block a = A_pq, pivot dk = D_q^-1, ud = U_qp if kd >=
 // 0): the multiplier l = A_pq D_q^-1 replaces A_pq, then every later entry of
 // row p that row q's U part reaches loses l times that U block, in the row's
 // order (the remaining L entries, the diagonal, the U entries).
-__device__ __forceinline__ void bilu_entry(const FactArgs &A, long bl, long bu, int nlp, int e,
-                                           const double *a, const double *dk, int kd,
+__device__ __forceinline__ void bilu_entry(const FactArgs &A, const RasRow &rl, const RasRow &ru,
+                                           int nlp, int e, const double *a, const double *dk, int kd,
                                            const double *ud, double *d, int &xi, int xe) {
     double l[4];
     l[0] = a[0] * dk[0] + a[1] * dk[2];
     l[1] = a[0] * dk[1] + a[1] * dk[3];
     l[2] = a[2] * dk[0] + a[3] * dk[2];
     l[3] = a[2] * dk[1] + a[3] * dk[3];
-    double2 *o = (double2 *)&A.lval[4 * ent(bl, e)];
-    o[0] = make_double2(l[0], l[1]);
-    o[1] = make_double2(l[2], l[3]);
+    st_blk(A.lval, rl(e), l);
     for (; xi < xe; xi++) {
         int4 m = A.xl[xi];
         if (m.x != e || m.y > nlp) break;
-        sub_prod(&A.lval[4 * ent(bl, m.y)], l, &A.uval[4 * (long)m.z]);
+        sub_prod_at(A.lval, rl(m.y), l, A.uval, m.z);
     }
     if (kd >= 0) sub_prod(d, l, ud);
     for (; xi < xe; xi++) {
         int4 m = A.xl[xi];
         if (m.x != e) break;
-        sub_prod(&A.uval[4 * ent(bu, m.y - nlp - 1)], l, &A.uval[4 * (long)m.z]);
+        sub_prod_at(A.uval, ru(m.y - nlp - 1), l, A.uval, m.z);
     }
+}
+
+__device__ __forceinline__ void ld4(double *v, const double *p) {
+    const double2 a = ((const double2 *)p)[0], b = ((const double2 *)p)[1];
+    v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
 }
 
 // Rows of one level are factorised together, one lane per row, the levels in
@@ -593,13 +608,11 @@ constexpr int BWG = 512;              // 8 waves: registers for the prefetched b
 __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
     int s = blockIdx.x;
     int nlev = A.nlev[s], base = A.lbase[s];
-    int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int L = 0; L < nlev; L++) {
-        int s0 = A.soff[base + L], s1 = A.soff[base + L + 1];
-        for (int sl = s0 + wave; sl < s1; sl += BWG / 64) {
-            if (lane >= A.sl_cn[sl]) continue;
-            int p = A.sl_st[sl] + lane;
-            long bl = ras_entry(A.sl_bl[sl], lane, 0), bu = ras_entry(A.sl_bu[sl], lane, 0);
+        int p0 = RAS_ROWS * A.soff[base + L], p1 = RAS_ROWS * A.soff[base + L + 1];
+        for (int p = p0 + (int)threadIdx.x; p < p1; p += BWG) {
+            if (A.glob[p] < 0) continue;
+            const RasRow rl(A.xlb, p), ru(A.xub, p);
             int nlp = A.nl[p];
             int xi = A.xptr[p], xe = A.xptr[p + 1];
             // an extra match of an earlier entry may change a later L block
@@ -612,34 +625,34 @@ __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
 #pragma unroll
             for (int e = 0; e < LPF; e++) {
                 if (e < nlp) {
-                    long k = ent(bl, e);
+                    long k = rl(e);
                     q[e] = A.lcol[k];
                     kd[e] = A.ldiag[k];
-                    ld4(a[e], &A.lval[4 * k]);
+                    ld_blk(a[e], A.lval, k);
                 }
             }
 #pragma unroll
             for (int e = 0; e < LPF; e++) {
                 if (e < nlp) {
                     ld4(dk[e], &A.dinv[4 * (long)q[e]]);
-                    if (kd[e] >= 0) ld4(ud[e], &A.uval[4 * (long)kd[e]]);
+                    if (kd[e] >= 0) ld_blk(ud[e], A.uval, kd[e]);
                 }
             }
 #pragma unroll
             for (int e = 0; e < LPF; e++) {
                 if (e < nlp) {
-                    if (reread) ld4(a[e], &A.lval[4 * ent(bl, e)]);
-                    bilu_entry(A, bl, bu, nlp, e, a[e], dk[e], kd[e], ud[e], d, xi, xe);
+                    if (reread) ld_blk(a[e], A.lval, rl(e));
+                    bilu_entry(A, rl, ru, nlp, e, a[e], dk[e], kd[e], ud[e], d, xi, xe);
                 }
             }
             for (int e = LPF; e < nlp; e++) {
-                long k = ent(bl, e);
+                long k = rl(e);
                 int qe = A.lcol[k], kde = A.ldiag[k];
                 double ae[4], dke[4], ude[4];
-                ld4(ae, &A.lval[4 * k]);
+                ld_blk(ae, A.lval, k);
                 ld4(dke, &A.dinv[4 * (long)qe]);
-                if (kde >= 0) ld4(ude, &A.uval[4 * (long)kde]);
-                bilu_entry(A, bl, bu, nlp, e, ae, dke, kde, ude, d, xi, xe);
+                if (kde >= 0) ld_blk(ude, A.uval, kde);
+                bilu_entry(A, rl, ru, nlp, e, ae, dke, kde, ude, d, xi, xe);
             }
             double det = d[0] * d[3] - d[1] * d[2];
             if (det == 0.0 || det != det) atomicOr(A.status, 1);
@@ -698,15 +711,13 @@ __global__ void k_ras_scatter(int mtot, int n, const int *glob_nat, const unsign
 
 template <class T>
 struct SweepArgs {
-    const int *lbase, *nlev, *soff, *lptr;
-    const int4 *mL, *mU;         // per slice: (first position, rows | slot pairs << 8, entry base, level)
-    const int *lcol, *ucol;
+    const int *lbase, *nlev, *soff;
+    const int4 *mL, *mU;         // per slice (see k_sweep_cols)
+    const int *lcol, *ucol;      // main entries: slice, lane, pair; overflow as in RasRow
     const T *lval, *uval, *dinv, *rl;
     T *y;
-    long lpad, upad;             // first entry of the L and U arrays' zero padding (columns -1)
-    int *prog;                   // PROG_STRIDE ns: levels passed by each sweep (forward, then
-                                 // nlev + backward), one counter per 256 bytes
-    int mtot;                    // local rows over all subdomains: the extent of y
+    int *prog;                   // PROG_STRIDE ns: slices finished by each sweep (forward, then
+                                 // backward), one counter per 256 bytes
     int ns;                      // subdomains (sweep workgroups)
     int nhelp;                   // prefetch workgroups per subdomain (workgroups ns .. ns (1 + nhelp))
 };
@@ -728,22 +739,17 @@ template <class T>
 struct Vec2 {
     typedef T type __attribute__((ext_vector_type(2)));
 };
-template <class T>
-struct Vec4 {
-    typedef T type __attribute__((ext_vector_type(4)));
-};
-
-// The static data of one task (slice) held by the lane pair of each row:
-// lane h holds entries e = h, h + 2 of the row (slot pairs k < MAXK),
-// component h of the right-hand side and, backward, row h of the inverse
-// diagonal block; y values of entries finished before the prefetch was
-// issued arrive in yf.  st .. L are uniform.
+// The data of one task (slice) held by lane 2r + h for position r: component h
+// of the right-hand side and, backward, row h of the inverse diagonal block;
+// the blocks of entry h (rows h, 1 - h) and rows h of those of entries 2 and 3
+// (3: where a row of the slice has it); the y values of entries h and
+// 2 + h.
 template <class T>
 struct Task {
-    int st, cn, w, b, L;
-    T a, d0, d1;
-    T v[MAXK][4];
-    T yf[MAXK][2];
+    typedef typename Vec2<T>::type V2;
+    T a;
+    V2 d, keep, send, v2, v3;
+    V2 y[MAXK];
 };
 
 // Slice of task j of a wavefront: the wavefronts take the slices of the
@@ -755,241 +761,265 @@ __device__ __forceinline__ int task_slice(int sa, int sb, int wave, int j, int n
     return FWD ? sa + wave + NCW * jj : sb - 1 - wave - NCW * jj;
 }
 
-template <class T, bool FWD>
-__device__ __forceinline__ void load_cols(int (&c)[MAXK], const SweepArgs<T> &A, int4 m, int lane) {
-    int w = __builtin_amdgcn_readfirstlane(m.y) >> 8, b = __builtin_amdgcn_readfirstlane(m.z);
-    const int *cols = FWD ? A.lcol : A.ucol;
-    // slot pairs past the slice's own read the arrays' padding (column -1,
-    // block 0), so they add nothing and need no mask
-    long pad = FWD ? A.lpad : A.upad;
-#pragma unroll
-    for (int k = 0; k < MAXK; k++)
-        c[k] = cols[(k < w ? (long)b + (long)k * RAS_SLICE : pad) + lane];
+// Loads at a wavefront-uniform address plus this lane's byte offset, kept in
+// scalar registers and one vector register (the asm stops the compiler from
+// adding them up outside the loop, which takes a vector add per load).
+typedef const __attribute__((address_space(1))) char *LaneBase;
+template <class V>
+__device__ __forceinline__ V ld_lane(const void *base, unsigned off) {
+    LaneBase p = (LaneBase)base;
+    asm("" : "+s"(p), "+v"(off));
+    return *(const __attribute__((address_space(1))) V *)(p + off);
 }
 
 template <class T, bool FWD>
-__device__ __forceinline__ void load_task(Task<T> &R, const SweepArgs<T> &A, int4 m, int lane) {
-    typedef typename Vec4<T>::type V4;
+__device__ __forceinline__ void load_cols(int (&c)[MAXK], const SweepArgs<T> &A, int sl, unsigned lane) {
+    typedef int I2 __attribute__((ext_vector_type(2)));
+    I2 v = ld_lane<I2>((FWD ? A.lcol : A.ucol) + (long)sl * RAS_MENT, lane * 8u);
+    c[0] = v.x;
+    c[1] = v.y;
+}
+
+// w: entries of the slice's longest row
+template <class T, bool FWD>
+__device__ __forceinline__ void load_task(Task<T> &R, const SweepArgs<T> &A, int sl, int w, unsigned lane) {
     typedef typename Vec2<T>::type V2;
-    R.st = __builtin_amdgcn_readfirstlane(m.x);
-    int cw = __builtin_amdgcn_readfirstlane(m.y);
-    R.cn = cw & 255;
-    R.w = cw >> 8;
-    R.b = __builtin_amdgcn_readfirstlane(m.z);
-    R.L = __builtin_amdgcn_readfirstlane(m.w);
-    int r = lane >> 1;
-    // rows past the slice's end read its last row (never stored)
-    long p = R.st + (r < R.cn ? r : R.cn - 1);
-    int h = lane & 1;
-    R.a = FWD ? A.rl[2 * p + h] : A.y[2 * p + h];
-    if (!FWD) {
-        V2 d = *(const V2 *)&A.dinv[4 * p + 2 * h];
-        R.d0 = d.x;
-        R.d1 = d.y;
-    }
-    const T *vals = FWD ? A.lval : A.uval;
-    long pad = FWD ? A.lpad : A.upad;
-#pragma unroll
-    for (int k = 0; k < MAXK; k++) {
-        long e = (k < R.w ? (long)R.b + (long)k * RAS_SLICE : pad) + lane;
-        V4 v = *(const V4 *)&vals[4 * e];
-        R.v[k][0] = v.x; R.v[k][1] = v.y; R.v[k][2] = v.z; R.v[k][3] = v.w;
-    }
+    // position 32 sl + lane / 2, component lane & 1
+    R.a = ld_lane<T>((FWD ? A.rl : A.y) + (long)sl * 2 * RAS_ROWS, lane * (unsigned)sizeof(T));
+    if (!FWD) R.d = ld_lane<V2>(A.dinv + (long)sl * 4 * RAS_ROWS, lane * (unsigned)sizeof(V2));
+    LaneBase vals = (LaneBase)((FWD ? A.lval : A.uval) + (long)sl * (4 * RAS_MENT));
+    unsigned off = lane * (unsigned)sizeof(V2);
+    asm("" : "+s"(vals), "+v"(off));
+    typedef const __attribute__((address_space(1))) V2 *G2;
+    constexpr int part = 64 * (int)sizeof(V2);
+    R.keep = *(G2)(vals + off);
+    R.send = *(G2)(vals + off + part);
+    R.v2 = *(G2)(vals + off + 2 * part);
+    if (w > 3) R.v3 = *(G2)(vals + off + 3 * part);
 }
 
-// Load the y values of the task's entries marked F_PRE: finished before the
+// Zero for a column whose y value is loaded early.
+__device__ __forceinline__ unsigned not_pre(int c) { return ((unsigned)c >> COL_BITS) ^ (unsigned)F_PRE; }
+
+// Request the y values of the task's entries marked F_PRE: finished before the
 // level the wavefront is at when it issues this load (two steps before the
-// task) and outside the LDS ring's window of the task's level.
-template <class T, bool FWD>
+// task) and outside the LDS ring's window of the task's level.  Few lanes have
+// one, fewer two, and a load occupies the CU's load path for 16 cycles however
+// few lanes take part: one load serves both entries, into y[0], and a lane's
+// second takes another.
+template <class T>
 __device__ __forceinline__ void prefetch_y(Task<T> &R, const int (&c)[MAXK], const T *y) {
     typedef typename Vec2<T>::type V2;
-#pragma unroll
-    for (int k = 0; k < MAXK; k++) {
-        bool far = ((unsigned)c[k] >> COL_BITS) == (unsigned)F_PRE;
-        // only the lanes with such an entry load (a few per task)
-        if (far) {
-            V2 v = *(const V2 *)&y[2 * (long)(c[k] & COL_MASK)];
-            R.yf[k][0] = v.x;
-            R.yf[k][1] = v.y;
-        }
-    }
+    unsigned n0 = not_pre(c[0]), n1 = not_pre(c[1]);
+    if (min(n0, n1) == 0) R.y[0] = *(const V2 *)&y[2 * (long)((n0 == 0 ? c[0] : c[1]) & COL_MASK)];
+    if ((n0 | n1) == 0) R.y[1] = *(const V2 *)&y[2 * (long)(c[1] & COL_MASK)];
 }
 
-// One step of a triangular sweep: task k of the wavefront (buffers U).
-// The task's level barriers come first; then, with every earlier level
-// finished, the y values of task k+2's finished entries are requested,
-// task k's other entries are read from the ring (or, outside it, from
-// global memory), and the metadata of task k+6, the columns of task k+4 and
-// the values of task k+3 are requested; task k is then computed and its
-// rows stored to y and the ring.  Every buffer is filled several steps
-// before its use, so the waits of a step are for loads issued two or more
-// steps earlier.
+// The even or odd lane's value in both lanes of a pair.
+constexpr int DPP_EVEN = 0xa0, DPP_ODD = 0xf5;
+template <int CTRL, class V2>
+__device__ __forceinline__ V2 dpp_move2(V2 v) {
+    V2 r;
+    r.x = dpp_move<CTRL>(v.x);
+    r.y = dpp_move<CTRL>(v.y);
+    return r;
+}
+
+// One step of a triangular sweep: task k of the wavefront (columns and
+// metadata in buffers k mod 4, the rest in buffers k mod 2).  Once the count of
+// finished slices covers every earlier level, task k's entries are read from
+// the ring, its rows computed and stored to y and the ring, and the count
+// raised.  Only then are task k+2's early y values and static data requested
+// (into the buffers just used) and task k+4's columns and metadata: a CU takes
+// 64 bytes of loads a cycle, so a slice's 5 KB hold up the instructions behind
+// them for some 80 cycles, and behind the count they delay no other wavefront.
+//
+// What bounds a sweep: those loads (keep + send + v2, mostly not v3, columns,
+// right-hand side, early y, result: about 0.2 ms per direction of 143,000
+// positions on one CU) where levels are wide, else the chain count - ring -
+// products - ring of a level, about 0.25 us.  An application at 2M cells, 16
+// subdomains of 135,000 rows in 487 levels: 1,262 us with workgroup barriers
+// between the levels, loads before the products and rows of more than four
+// entries finished from memory; 883 with the count, loads after it and two
+// positions for long rows; 817 with 16 wavefronts; 762 with the early y values
+// of both entries in one load, no load for entry 3 where no row has one, and
+// the addresses in scalar registers.
+//
+// LDS operations of a wavefront take effect in the order they are issued, so
+// whoever reads the raised count finds the slice's results in the ring; the
+// stores to y are issued before, and a CU's later loads find them.
 template <class T, bool FWD, int U>
-__device__ __forceinline__ void sweep_step(const SweepArgs<T> &A, T *ring,
-                                           int sa, int sb, int nlev, int wave, int lane, int nt, int k,
-                                           Task<T> (&B)[4], int (&C)[4][MAXK], int4 (&M)[4],
-                                           int &passed) {
+__device__ __forceinline__ void sweep_step(const SweepArgs<T> &A, T *ring, int *count, int sa, int sb,
+                                           int wave, unsigned lane, int nt, int k, Task<T> (&B)[2],
+                                           int (&C)[4][MAXK], int (&M)[4], int &seen) {
     typedef typename Vec2<T>::type V2;
     constexpr int R = RingSize<T>::rows;
-    const int4 *meta = FWD ? A.mL : A.mU;
-    Task<T> &cur = B[U];
-    int rank = FWD ? cur.L : nlev - 1 - cur.L;
-    while (passed < rank) {
-        __syncthreads();
-        passed++;
-    }
-    // every wavefront, every step: a store the helpers poll (unconditional, so
-    // the wait counts stay the same at every step).  Workgroup scope is enough:
-    // the store goes through to the XCD's L2, where the helpers' polls read,
-    // and nothing of the sweep's results depends on when they see it.
-    __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], (FWD ? 0 : nlev) + passed,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    // marked entries of task k+2 (finished by now, outside its ring window)
-    prefetch_y<T, FWD>(B[(U + 2) & 3], C[(U + 2) & 3], A.y);
-    // task k's other entries: from the ring, or (rare) from y
-    T y0[MAXK], y1[MAXK];
-    bool slow = false;
-#pragma unroll
-    for (int kk = 0; kk < MAXK; kk++) {
-        int c = C[U][kk];
-        unsigned f = (unsigned)c >> COL_BITS;
-        V2 rv = *(const V2 *)&ring[2 * (c & (R - 1))];
-        y0[kk] = f == (unsigned)F_PRE ? cur.yf[kk][0] : rv.x;
-        y1[kk] = f == (unsigned)F_PRE ? cur.yf[kk][1] : rv.y;
-        slow |= f == (unsigned)F_SLOW;
-    }
-    if (__builtin_amdgcn_read_exec() & __ballot(slow)) {
-#pragma unroll
-        for (int kk = 0; kk < MAXK; kk++) {
-            int c = C[U][kk];
-            if (((unsigned)c >> COL_BITS) == (unsigned)F_SLOW) {
-                V2 v = *(const V2 *)&A.y[2 * (long)(c & COL_MASK)];
-                y0[kk] = v.x;
-                y1[kk] = v.y;
-            }
-        }
+    constexpr int NCW = Sweep<T>::ncw;
+    Task<T> &cur = B[U & 1];
+    const int need = __builtin_amdgcn_readlane(M[U], 0);
+    const int w = __builtin_amdgcn_readlane(M[U], 1);
+    const int xb = __builtin_amdgcn_readlane(M[U], 2);
+    const int nlong = __builtin_amdgcn_readlane(M[U], 3);      // < 0: has F_SLOW entries
+    // ready before the wait: which entries are in the ring and where, and the y
+    // values loaded early
+    unsigned long in0 = __ballot(not_pre(C[U][0]) != 0), in1 = __ballot(not_pre(C[U][1]) != 0);
+    int s0 = (int)sizeof(V2) * (C[U][0] & (R - 1)), s1 = (int)sizeof(V2) * (C[U][1] & (R - 1));
+    V2 &y0 = cur.y[0], &y1 = cur.y[1];
+    if (not_pre(C[U][0]) != 0) y1 = y0;
+    asm volatile("" : "+s"(in0), "+s"(in1), "+v"(s0), "+v"(s1), "+v"(y1.x), "+v"(y1.y) :: "memory");
+    while (seen < need)
+        seen = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+    asm volatile("" ::: "memory");
+    if (__builtin_expect(__builtin_amdgcn_inverse_ballot_w64(in0), 1))
+        y0 = *(const V2 *)((const char *)ring + s0);
+    if (__builtin_expect(__builtin_amdgcn_inverse_ballot_w64(in1), 1))
+        y1 = *(const V2 *)((const char *)ring + s1);
+    if (nlong < 0) {
+        if (((unsigned)C[U][0] >> COL_BITS) == (unsigned)F_SLOW)
+            y0 = *(const V2 *)&A.y[2 * (long)(C[U][0] & COL_MASK)];
+        if (((unsigned)C[U][1] >> COL_BITS) == (unsigned)F_SLOW)
+            y1 = *(const V2 *)&A.y[2 * (long)(C[U][1] & COL_MASK)];
         __builtin_amdgcn_s_waitcnt(0);      // nothing of this rare path stays in flight
     }
-    __builtin_amdgcn_sched_barrier(0);
-    // metadata of task k+6, columns of task k+4, values of task k+3
-    M[(U + 2) & 3] = meta[task_slice<FWD, Sweep<T>::ncw>(sa, sb, wave, k + 6, nt)];
-    load_cols<T, FWD>(C[U], A, M[U], lane);
-    load_task<T, FWD>(B[(U + 3) & 3], A, M[(U + 3) & 3], lane);
-    __builtin_amdgcn_sched_barrier(0);
-    // t = a - sum_e B_e y_e over this lane's entries; the pair then adds
-    int h = lane & 1;
-    T t0 = h == 0 ? cur.a : (T)0, t1 = h == 0 ? (T)0 : cur.a;
-#pragma unroll
-    for (int kk = 0; kk < MAXK; kk++) {
-        T d0 = cur.v[kk][0] * y0[kk] + cur.v[kk][1] * y1[kk];
-        T d1 = cur.v[kk][2] * y0[kk] + cur.v[kk][3] * y1[kk];
-        // padding entries hold a zero block (their y, from the ring, is finite)
-        t0 -= d0;
-        t1 -= d1;
+    // component h of row r: te = (a if h = 0) - sum over even entries, to = (a if
+    // h = 1) - sum over odd ones, each in order; unused entries hold a zero block
+    // (their y, from the ring, is finite)
+    const bool h = lane & 1;
+    T nk = -cur.keep.x * y0.x - cur.keep.y * y0.y;
+    T ns = -cur.send.x * y0.x - cur.send.y * y0.y;
+    V2 ye = dpp_move2<DPP_EVEN>(y1);
+    T x2 = cur.v2.x * ye.x + cur.v2.y * ye.y, x3 = 0;
+    T nr = dpp_move<DPP_XOR1>(ns);
+    T ak = cur.a + nk;
+    T te = (h ? nr : ak) - x2, to = h ? ak : nr;
+    if (w > 3) {
+        V2 yo = dpp_move2<DPP_ODD>(y1);
+        x3 = cur.v3.x * yo.x + cur.v3.y * yo.y;
+        to -= x3;
     }
-    if (cur.w > MAXK) {
-        // rows with more than 2 MAXK entries (well rows and a few others): the
-        // rest from memory
+    const int ql = nlong & 63;
+    if (ql && w > RAS_MAIN) {
+        // the slice's first ql rows have their next entries in the next
+        // position's lanes
+        bool lg = (int)lane < 4 * ql;
+        T kq = dpp_move<DPP_XOR2>(nk), rq = dpp_move<DPP_XOR2>(nr);
+        T e2 = dpp_move<DPP_XOR2>(x2), e3 = dpp_move<DPP_XOR2>(x3);
+        te += lg ? (h ? rq : kq) : (T)0;
+        to += lg ? (h ? kq : rq) : (T)0;
+        te -= lg ? e2 : (T)0;
+        to -= lg ? e3 : (T)0;
+    }
+    if (w > 2 * RAS_MAIN) {
+        // rows with more than 2 RAS_MAIN entries (well rows): the
+        // rest from the overflow entries
         const int *cols = FWD ? A.lcol : A.ucol;
         const T *vals = FWD ? A.lval : A.uval;
         // in rounds of LK slot pairs: the columns of a round, then its y values
         // and blocks, are requested together (two dependent loads per round);
         // pairs past the row's own re-read its last and are masked
-        typedef typename Vec4<T>::type V4;
-        for (int k0 = MAXK; k0 < cur.w; k0 += LK) {
+        const int np = (w + 1) / 2;
+        for (int k0 = 2 * MAXK; k0 < np; k0 += LK) {
             long idx[LK];
             int q[LK];
 #pragma unroll
             for (int j = 0; j < LK; j++) {
-                idx[j] = (long)cur.b + (long)min(k0 + j, cur.w - 1) * RAS_SLICE + lane;
+                idx[j] = (long)xb + (long)min(k0 + j, np - 1) * RAS_SLICE + lane;
                 q[j] = cols[idx[j]];
             }
-            V2 gv[LK], rv[LK];
-            V4 bv[LK];
+            V2 gv[LK], ov[LK], b0[LK], b1[LK];
 #pragma unroll
             for (int j = 0; j < LK; j++) {
                 int qs = q[j] >= 0 ? q[j] & COL_MASK : 0;
                 gv[j] = *(const V2 *)&A.y[2 * (long)qs];
-                rv[j] = *(const V2 *)&ring[2 * (qs & (R - 1))];
-                bv[j] = *(const V4 *)&vals[4 * idx[j]];
+                ov[j] = *(const V2 *)&ring[2 * (qs & (R - 1))];
+                b0[j] = *(const V2 *)&vals[ras_val(idx[j], h)];
+                b1[j] = *(const V2 *)&vals[ras_val(idx[j], 1 - h)];
             }
 #pragma unroll
             for (int j = 0; j < LK; j++) {
-                bool ok = k0 + j < cur.w && q[j] >= 0;
+                bool ok = k0 + j < np && q[j] >= 0;
                 bool inwin = ((unsigned)q[j] >> COL_BITS) == (unsigned)F_RING;
-                T a0 = inwin ? rv[j].x : gv[j].x, a1 = inwin ? rv[j].y : gv[j].y;
-                T e0 = bv[j].x * a0 + bv[j].y * a1;
-                T e1 = bv[j].z * a0 + bv[j].w * a1;
-                t0 -= ok ? e0 : (T)0;
-                t1 -= ok ? e1 : (T)0;
+                T a0 = inwin ? ov[j].x : gv[j].x, a1 = inwin ? ov[j].y : gv[j].y;
+                T e0 = b0[j].x * a0 + b0[j].y * a1;
+                T e1 = b1[j].x * a0 + b1[j].y * a1;
+                e0 = ok ? e0 : (T)0;
+                e1 = dpp_move<DPP_XOR1>(ok ? e1 : (T)0);
+                te -= h ? e1 : e0;
+                to -= h ? e0 : e1;
             }
         }
         __builtin_amdgcn_s_waitcnt(0);
     }
-    t0 += __shfl_xor(t0, 1, 64);
-    t1 += __shfl_xor(t1, 1, 64);
-    T out = FWD ? (h == 0 ? t0 : t1) : cur.d0 * t0 + cur.d1 * t1;
-    // lanes past the slice's end store its last row again, with that row's
-    // value, so the store needs no branch
-    int r = lane >> 1;
-    int rr = r < cur.cn ? r : cur.cn - 1;
-    out = __shfl(out, 2 * rr + h, 64);
-    long p = (long)cur.st + rr;
-    A.y[2 * p + h] = out;
-    ring[2 * (p & (R - 1)) + h] = out;
+    T out = te + to;
+    if (!FWD) out = cur.d.x * dpp_move<DPP_EVEN>(out) + cur.d.y * dpp_move<DPP_ODD>(out);
+    const int sl = task_slice<FWD, NCW>(sa, sb, wave, k, nt);
+    // positions without a row store too: nothing reads those
+    *(T *)((char *)(A.y + (long)sl * 2 * RAS_ROWS) + lane * (unsigned)sizeof(T)) = out;
+    ring[(sl * 2 * RAS_ROWS + lane) & (2 * R - 1)] = out;
+    // one lane adds (an atomicAdd here comes with a dozen instructions that
+    // combine lanes, between the results and the count)
+    if (lane == 0)
+        asm volatile("ds_add_u32 %0, %1"
+                     :: "v"((unsigned)(size_t)(__attribute__((address_space(3))) int *)count), "v"(1)
+                     : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    // marked entries of task k+2 (finished by now, outside its ring window)
+    prefetch_y(cur, C[(U + 2) & 3], A.y);
+    const int sl4 = task_slice<FWD, NCW>(sa, sb, wave, k + 4, nt);
+    M[U] = ld_lane<int>((FWD ? A.mL : A.mU) + sl4, (lane & 3) * 4u);
+    load_cols<T, FWD>(C[U], A, sl4, lane);
+    load_task<T, FWD>(cur, A, task_slice<FWD, NCW>(sa, sb, wave, k + 2, nt),
+                      __builtin_amdgcn_readlane(M[(U + 2) & 3], 1), lane);
+    // a store the helpers poll.  Workgroup scope is enough: it goes through to
+    // the XCD's L2, where the helpers' polls read, and nothing of the sweep's
+    // results depends on when they see it.
+    if (wave == 0)
+        __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], seen, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_WORKGROUP);
+    __builtin_amdgcn_sched_barrier(0);
 }
 
 // One triangular sweep of a subdomain: forward (L, unit diagonal) or
-// backward (U, then the inverse diagonal block).  Every wavefront passes one
-// workgroup barrier per level, in the same sequence, wherever it has work.
+// backward (U, then the inverse diagonal block).
 template <class T, bool FWD>
-__device__ __forceinline__ void sweep_dir(const SweepArgs<T> &A, T *ring,
-                                          int sa, int sb, int nlev, int wave, int lane) {
+__device__ __forceinline__ void sweep_dir(const SweepArgs<T> &A, T *ring, int *count,
+                                          int sa, int sb, int wave, unsigned lane) {
     int nsl = sb - sa;
     constexpr int NCW = Sweep<T>::ncw;
     int nt = nsl > wave ? (nsl - wave + NCW - 1) / NCW : 0;
-    int passed = 0;
-    if (nt > 0) {
-        const int4 *meta = FWD ? A.mL : A.mU;
-        Task<T> B[4];
-        int C[4][MAXK];
-        int4 M[4];
+    if (nt <= 0) return;
+    Task<T> B[2];
+    int C[4][MAXK];
+    int M[4];
 #pragma unroll
-        for (int j = 0; j < 4; j++) M[j] = meta[task_slice<FWD, Sweep<T>::ncw>(sa, sb, wave, j, nt)];
-#pragma unroll
-        for (int j = 0; j < 4; j++) load_cols<T, FWD>(C[j], A, M[j], lane);
-#pragma unroll
-        for (int j = 0; j < 3; j++) load_task<T, FWD>(B[j], A, M[j], lane);
-        M[0] = meta[task_slice<FWD, Sweep<T>::ncw>(sa, sb, wave, 4, nt)];
-        M[1] = meta[task_slice<FWD, Sweep<T>::ncw>(sa, sb, wave, 5, nt)];
-        // enter the loop with nothing in flight, so that the wait counts the
-        // compiler derives at its head follow the steady state
-        __builtin_amdgcn_s_waitcnt(0);
-        // Steps past the wavefront's last task repeat it: its data were read
-        // before its first computation stored anything (backward, y is read
-        // as input and overwritten), its level barrier is already passed, and
-        // it stores the same values again.  With no exit inside the unrolled
-        // body the wait counts at every step follow the steady state.
-        for (int k = 0; k < nt; k += 4) {
-            sweep_step<T, FWD, 0>(A, ring, sa, sb, nlev, wave, lane, nt, k, B, C, M, passed);
-            sweep_step<T, FWD, 1>(A, ring, sa, sb, nlev, wave, lane, nt, k + 1, B, C, M, passed);
-            sweep_step<T, FWD, 2>(A, ring, sa, sb, nlev, wave, lane, nt, k + 2, B, C, M, passed);
-            sweep_step<T, FWD, 3>(A, ring, sa, sb, nlev, wave, lane, nt, k + 3, B, C, M, passed);
-        }
+    for (int j = 0; j < 4; j++) {
+        int sl = task_slice<FWD, NCW>(sa, sb, wave, j, nt);
+        M[j] = ld_lane<int>((FWD ? A.mL : A.mU) + sl, (lane & 3) * 4u);
+        load_cols<T, FWD>(C[j], A, sl, lane);
+        if (j < 2) load_task<T, FWD>(B[j], A, sl, __builtin_amdgcn_readlane(M[j], 1), lane);
     }
-    while (passed < nlev) {
-        __syncthreads();
-        passed++;
+    // enter the loop with nothing in flight, so that the wait counts the
+    // compiler derives at its head follow the steady state
+    __builtin_amdgcn_s_waitcnt(0);
+    int seen = FWD ? 0 : nsl;
+    for (int k = 0;; k += 4) {
+        sweep_step<T, FWD, 0>(A, ring, count, sa, sb, wave, lane, nt, k, B, C, M, seen);
+        if (k + 1 >= nt) break;
+        sweep_step<T, FWD, 1>(A, ring, count, sa, sb, wave, lane, nt, k + 1, B, C, M, seen);
+        if (k + 2 >= nt) break;
+        sweep_step<T, FWD, 2>(A, ring, count, sa, sb, wave, lane, nt, k + 2, B, C, M, seen);
+        if (k + 3 >= nt) break;
+        sweep_step<T, FWD, 3>(A, ring, count, sa, sb, wave, lane, nt, k + 3, B, C, M, seen);
+        if (k + 4 >= nt) break;
     }
-    __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], (FWD ? 0 : nlev) + passed,
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ------------------------------------------------------- prefetch helpers
 constexpr int PCH = 8;            // slices per helper chunk
 constexpr int PDS = 128;          // slices a chunk is read ahead of the sweep (about 0.8 MB)
 constexpr int PSPIN = 1 << 16;    // bound of a helper's wait for the sweep
-constexpr int MAX_HELP = 4;       // helper workgroups per subdomain
+constexpr int MAX_HELP = 8;       // helper workgroups per subdomain
 
 // Read one dword of every 128-byte line of [p, p + bytes) (all addresses
 // inside the range); the values are summed only so that the loads stay.
@@ -1015,8 +1045,7 @@ __device__ __forceinline__ unsigned touch(const void *p, long bytes) {
 // metadata, columns, factor blocks and right-hand side (backward: the forward
 // result and the inverse diagonal blocks).
 template <class T, bool FWD>
-__device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int sa, int sb,
-                                 int nlev, int base) {
+__device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int sa, int sb) {
     const int4 *meta = FWD ? A.mL : A.mU;
     const int *cols = FWD ? A.lcol : A.ucol;
     const T *vals = FWD ? A.lval : A.uval;
@@ -1024,9 +1053,7 @@ __device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int
     unsigned acc = 0;
     for (int c = j; c * PCH < nsl; c += H) {
         int i0 = c * PCH, i1 = min(i0 + PCH, nsl);
-        int f = FWD ? sa + i0 : sb - i1;           // lowest and highest slice of the chunk
-        int l = FWD ? sa + i1 - 1 : sb - 1 - i0;
-        int4 mf = meta[f], ml = meta[l];
+        long f = FWD ? sa + i0 : sb - i1, m = i1 - i0;       // lowest slice of the chunk, slices
         // one lane polls (the counter's line is written at every step of the
         // sweep), the workgroup waits for it
         if (threadIdx.x == 0) {
@@ -1034,23 +1061,17 @@ __device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int
                 int pr = __hip_atomic_load(&A.prog[PROG_STRIDE * s], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 // slices the sweep has finished in this direction
-                int done;
-                if (FWD)
-                    done = pr >= nlev ? nsl : A.soff[base + max(pr, 0)] - sa;
-                else
-                    done = pr < nlev ? -1 : sb - A.soff[base + nlev - min(pr - nlev, nlev)];
+                int done = FWD ? pr : max(pr - nsl, -1);
                 if (i0 - done <= PDS) break;
                 __builtin_amdgcn_s_sleep(8);
             }
         }
         __syncthreads();
-        long e0 = mf.z, e1 = (long)ml.z + (long)(ml.y >> 8) * RAS_SLICE;
-        long p0 = mf.x, p1 = (long)ml.x + (ml.y & 255);
-        acc += touch(meta + f, 16L * (l - f + 1));
-        acc += touch(cols + e0, 4L * (e1 - e0));
-        acc += touch(vals + 4 * e0, 4L * (long)sizeof(T) * (e1 - e0));
-        acc += touch((FWD ? A.rl : (const T *)A.y) + 2 * p0, 2L * (long)sizeof(T) * (p1 - p0));
-        if (!FWD) acc += touch(A.dinv + 4 * p0, 4L * (long)sizeof(T) * (p1 - p0));
+        acc += touch(meta + f, 16L * m);
+        acc += touch(cols + f * RAS_MENT, 4L * RAS_MENT * m);
+        acc += touch(vals + 4 * f * RAS_MENT, 4L * (long)sizeof(T) * RAS_MENT * m);
+        acc += touch((FWD ? A.rl : (const T *)A.y) + 2 * f * RAS_ROWS, 2L * (long)sizeof(T) * RAS_ROWS * m);
+        if (!FWD) acc += touch(A.dinv + 4 * f * RAS_ROWS, 4L * (long)sizeof(T) * RAS_ROWS * m);
     }
     return acc;
 }
@@ -1061,56 +1082,66 @@ template <class T>
 __global__ __launch_bounds__(Sweep<T>::wg) void k_ras_sweep(SweepArgs<T> A) {
     constexpr int R = RingSize<T>::rows;
     __shared__ __attribute__((aligned(16))) T ring[2 * R];
+    __shared__ int count;            // finished slices, forward then backward
     if ((int)blockIdx.x >= A.ns) {
         // a helper: subdomain (b - ns) mod ns, on the same XCD as its sweep
         // (workgroup b goes to XCD b mod 8 and ns is a multiple of 8)
         int hb = blockIdx.x - A.ns, hs = hb % A.ns;
         int hn = A.nlev[hs], hbase = A.lbase[hs];
         int hsa = A.soff[hbase], hsb = A.soff[hbase + hn];
-        unsigned acc = prefetch_dir<T, true>(A, hs, hb / A.ns, A.nhelp, hsa, hsb, hn, hbase);
-        acc += prefetch_dir<T, false>(A, hs, hb / A.ns, A.nhelp, hsa, hsb, hn, hbase);
+        unsigned acc = prefetch_dir<T, true>(A, hs, hb / A.ns, A.nhelp, hsa, hsb);
+        acc += prefetch_dir<T, false>(A, hs, hb / A.ns, A.nhelp, hsa, hsb);
         if (A.nhelp < 0) A.prog[0] = (int)acc;     // never taken; keeps the reads
         return;
     }
     int s = blockIdx.x;
     int nlev = A.nlev[s], base = A.lbase[s];
     for (int i = threadIdx.x; i < 2 * R; i += Sweep<T>::wg) ring[i] = (T)0;
+    if (threadIdx.x == 0) count = 0;
     int sa = A.soff[base], sb = A.soff[base + nlev];
     __syncthreads();
     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int lane = threadIdx.x & 63;
-    sweep_dir<T, true>(A, ring, sa, sb, nlev, wave, lane);
-    sweep_dir<T, false>(A, ring, sa, sb, nlev, wave, lane);
+    unsigned lane = threadIdx.x & 63;
+    sweep_dir<T, true>(A, ring, &count, sa, sb, wave, lane);
+    __syncthreads();
+    if (threadIdx.x == 0)
+        __hip_atomic_store(&A.prog[PROG_STRIDE * s], sb - sa, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+    sweep_dir<T, false>(A, ring, &count, sa, sb, wave, lane);
 }
 
 // Ring window of every subdomain: positions [end(L) - ring, end(L)) forward
 // ([start(L), start(L) + ring) backward) are still in the LDS ring while
 // level L runs when every level is narrower than the ring; else none is.
-__global__ void k_sub_window(const int *lbase, const int *nlevs, const int *lptr, int ring, int *win) {
+__global__ void k_sub_window(const int *lbase, const int *nlevs, const int *soff, int ring, int *win) {
     __shared__ int mw;
     int s = blockIdx.x, base = lbase[s], nlev = nlevs[s];
     if (threadIdx.x == 0) mw = 0;
     __syncthreads();
     int m = 0;
     for (int L = threadIdx.x; L < nlev; L += blockDim.x)
-        m = max(m, lptr[base + L + 1] - lptr[base + L]);
+        m = max(m, RAS_ROWS * (soff[base + L + 1] - soff[base + L]));
     atomicMax(&mw, m);
     __syncthreads();
     if (threadIdx.x == 0) win[s] = mw <= ring ? ring : 0;
 }
 
-// Where the sweep finds each entry's y value, from the sweep's fixed
-// schedule (ncw wavefronts take a subdomain's slices in turn, forward from
-// the first, backward from the last; the early loads of task j are issued
-// at task j - 2 of the same wavefront, when every level before that task's
-// has finished): in the ring window of the entry's level -> F_RING; else
-// finished before that bound -> F_PRE; else F_SLOW.  One workgroup per
-// slice; the class goes into the column's top bits.
+// The sweep's columns and metadata, one wavefront per slice: where the sweep
+// finds each entry's y value follows from its fixed schedule (ncw wavefronts
+// take a subdomain's slices in turn, forward from the first, backward from
+// the last; the early loads of task j are issued at task j - 2 of the same
+// wavefront, when every level before that task's has finished): in the ring
+// window of the entry's level -> F_RING; else finished before that bound ->
+// F_PRE; else F_SLOW.  The class goes into the column's top bits.  Metadata:
+// the count of finished slices (forward, then backward) at which the slice may
+// run, the entries of its longest row, its overflow start, and its long rows,
+// with the sign bit set if it has F_SLOW entries.
 template <bool FWD>
-__global__ void k_entry_class(int ns, const int *lbase, const int *nlevs, const int *soff,
-                              const int *lptr, const int *win, const int4 *meta, int *cols,
-                              int ncw) {
-    int sl = blockIdx.x;
+__global__ void k_sweep_cols(int ns, const int *lbase, const int *nlevs, const int *soff,
+                             const int *win, const int *perm, const int *lev, const int *w,
+                             const int *wlong, const int *xb, const int *cols, int ncw, int *out,
+                             int4 *meta) {
+    int sl = blockIdx.x, lane = threadIdx.x;
     int lo = 0, hi = ns - 1;                  // subdomain: the last one starting at or before sl
     while (lo < hi) {
         int mid = (lo + hi + 1) >> 1;
@@ -1118,35 +1149,38 @@ __global__ void k_entry_class(int ns, const int *lbase, const int *nlevs, const 
     }
     int s = lo, base = lbase[s], nlev = nlevs[s];
     int sa = soff[base], sb = soff[base + nlev];
-    if (sl < sa || sl >= sb) return;
-    int4 m = meta[sl];
-    int w = m.y >> 8, b = m.z, L = m.w;
-    int idx = FWD ? sl - sa : sb - 1 - sl;
+    // a slice's first position is always a row
+    int L = lev[perm[RAS_ROWS * sl]], idx = FWD ? sl - sa : sb - 1 - sl;
     int bound;
     if (idx / ncw < 2) {
-        bound = FWD ? lptr[base] : lptr[base + nlev];      // nothing finished yet
+        bound = RAS_ROWS * (FWD ? sa : sb);      // nothing finished yet
     } else {
-        int L2 = meta[FWD ? sl - 2 * ncw : sl + 2 * ncw].w;
-        bound = FWD ? lptr[base + L2] : lptr[base + L2 + 1];
+        int L2 = lev[perm[RAS_ROWS * (FWD ? sl - 2 * ncw : sl + 2 * ncw)]];
+        bound = RAS_ROWS * soff[base + (FWD ? L2 : L2 + 1)];
     }
-    int ws = win[s], lev0 = lptr[base + L], lev1 = lptr[base + L + 1];
-    for (int e = b + (int)threadIdx.x; e < b + w * RAS_SLICE; e += blockDim.x) {
-        int q = cols[e];
-        if (q < 0) continue;
+    int ws = win[s], lev0 = RAS_ROWS * soff[base + L], lev1 = RAS_ROWS * soff[base + L + 1];
+    bool slow = false;
+    auto mark = [&](int q, bool main) {
+        if (q < 0) return q;
         bool inwin = FWD ? q >= lev1 - ws : q < lev0 + ws;
         bool pre = (FWD ? q < bound : q >= bound) && !inwin;
-        cols[e] = q | ((inwin ? F_RING : (pre ? F_PRE : F_SLOW)) << COL_BITS);
+        slow |= main && !inwin && !pre;
+        return q | ((inwin ? F_RING : (pre ? F_PRE : F_SLOW)) << COL_BITS);
+    };
+    long b = (long)sl * RAS_MENT;
+    int2 c;
+    c.x = mark(cols[b + lane], true);
+    c.y = mark(cols[b + RAS_SLICE + lane], true);
+    *(int2 *)&out[b + 2 * lane] = c;
+    for (int k = 2 * MAXK; k < (w[sl] + 1) / 2; k++) {
+        long e = (long)xb[sl] + (long)k * RAS_SLICE + lane;
+        out[e] = mark(cols[e], false);
     }
-}
-
-__global__ void k_slice_meta(int nslice, const int *st, const int *cn, const int *wl,
-                             const int *bl, const int *wu, const int *bu, const int *perm,
-                             const int *lev, int4 *mL, int4 *mU) {
-    int sl = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sl >= nslice) return;
-    int L = lev[perm[st[sl]]];
-    mL[sl] = make_int4(st[sl], cn[sl] | ((wl[sl] + 1) / 2) << 8, bl[sl], L);
-    mU[sl] = make_int4(st[sl], cn[sl] | ((wu[sl] + 1) / 2) << 8, bu[sl], L);
+    bool any = __any(slow);
+    if (lane == 0) {
+        int need = FWD ? soff[base + L] - sa : (sb - sa) + (sb - soff[base + L + 1]);
+        meta[sl] = make_int4(need, w[sl], xb[sl], wlong[sl] | (any ? 1 << 31 : 0));
+    }
 }
 
 // ----------------------------------------------------------------- set-up
@@ -1163,13 +1197,6 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     R2P_TRY(D.nlnat.ensure(mtot));
     R2P_TRY(D.nunat.ensure(mtot));
     R2P_TRY(D.pos.ensure(mtot));
-    R2P_TRY(D.perm.ensure(mtot));
-    R2P_TRY(D.glob.ensure(mtot));
-    R2P_TRY(D.owned.ensure(mtot));
-    R2P_TRY(D.nl.ensure(mtot));
-    R2P_TRY(D.nu.ensure(mtot));
-    R2P_TRY(D.sl_of.ensure(mtot));
-    R2P_TRY(D.dsrc_pos.ensure(mtot));
     R2P_TRY(D.counters.ensure(64 + 2 * ns));
     R2P_TRY(D.prog.ensure(PROG_STRIDE * ns));
     R2P_TRY(P->pin.ensure(1 << 16));
@@ -1204,16 +1231,42 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     int nseg = D.h_lbase[ns];
     D.nseg = nseg;
     R2P_TRY(D.lptr_dev.ensure(nseg + 1));
+    R2P_TRY(D.nlong.ensure(nseg));
     R2P_TRY(D.soff.ensure(nseg + 1));
     R2P_TRY(D.sub_lbase.ensure(ns));
     R2P_TRY(D.sub_nlev.ensure(ns));
     R2P_HIP(hipMemcpyAsync(D.sub_lbase.p, D.h_lbase.data(), sizeof(int) * ns, hipMemcpyHostToDevice, s));
     R2P_HIP(hipMemcpyAsync(D.sub_nlev.p, D.h_nlev.data(), sizeof(int) * ns, hipMemcpyHostToDevice, s));
     R2P_HIP(hipMemsetAsync(D.lptr_dev.p, 0, sizeof(int) * (nseg + 1), s));
-    k_level_count<<<nb, BS, 0, s>>>(mtot, S.sub_of.p, D.lev.p, D.sub_lbase.p, D.lptr_dev.p);
+    R2P_HIP(hipMemsetAsync(D.nlong.p, 0, sizeof(int) * nseg, s));
+    k_level_count<<<nb, BS, 0, s>>>(mtot, S.sub_of.p, D.lev.p, D.sub_lbase.p, D.nlnat.p, D.nunat.p,
+                                    D.lptr_dev.p, D.nlong.p);
     R2P_LAUNCH();
     R2P_TRY(r2p_scan_int(D.lptr_dev.p, D.lptr_dev.p, nseg + 1, nullptr, P->iscratch, P->pin, s));
-    // 3. positions: stable sort by (level segment, descending predecessor count)
+    // 3. slices of RAS_ROWS positions per level; positions: stable sort by
+    // (level segment, long rows, descending predecessor count)
+    k_slice_count<<<r2p_blocks(nseg + 1, BS), BS, 0, s>>>(nseg, D.lptr_dev.p, D.nlong.p, D.soff.p);
+    R2P_LAUNCH();
+    int nslice = 0;
+    R2P_TRY(r2p_scan_int(D.soff.p, D.soff.p, nseg + 1, &nslice, P->iscratch, P->pin, s));
+    if (nslice > (1 << COL_BITS) / RAS_ROWS) {
+        r2p_set_error("%d local rows exceed the factor storage", mtot);
+        return R2P_EINVAL;
+    }
+    int npos = RAS_ROWS * nslice;
+    D.nslice = nslice;
+    D.npos = npos;
+    R2P_TRY(D.perm.ensure(npos));
+    R2P_TRY(D.glob.ensure(npos));
+    R2P_TRY(D.owned.ensure(npos));
+    R2P_TRY(D.nl.ensure(npos));
+    R2P_TRY(D.nu.ensure(npos));
+    R2P_TRY(D.dsrc_pos.ensure(npos));
+    R2P_HIP(hipMemsetAsync(D.perm.p, 0xff, sizeof(int) * (size_t)npos, s));
+    R2P_HIP(hipMemsetAsync(D.glob.p, 0xff, sizeof(int) * (size_t)npos, s));
+    R2P_HIP(hipMemsetAsync(D.owned.p, 0, (size_t)npos, s));
+    R2P_HIP(hipMemsetAsync(D.nl.p, 0, sizeof(int) * (size_t)npos, s));
+    R2P_HIP(hipMemsetAsync(D.nu.p, 0, sizeof(int) * (size_t)npos, s));
     {
         DBuf<unsigned> &key = P->ws.u[0], &val = P->ws.u[1], &kt = P->ws.u[2], &vt = P->ws.u[3];
         DBuf<int> &hist = P->ws.i[0];
@@ -1221,132 +1274,123 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
         R2P_TRY(val.ensure(mtot));
         R2P_TRY(kt.ensure(mtot));
         R2P_TRY(vt.ensure(mtot));
-        k_order_keys<<<nb, BS, 0, s>>>(mtot, S.sub_of.p, D.lev.p, D.sub_lbase.p, D.nlnat.p, key.p, val.p);
+        k_order_keys<<<nb, BS, 0, s>>>(mtot, S.sub_of.p, D.lev.p, D.sub_lbase.p, D.nlnat.p, D.nunat.p,
+                                       key.p, val.p);
         R2P_LAUNCH();
         R2P_TRY(r2p_sort_pairs(key.p, val.p, kt.p, vt.p, mtot, r2p_bits_for(nseg) + 3, hist,
                                P->iscratch, P->pin, s));
-        k_perm_gather<<<nb, BS, 0, s>>>(mtot, val.p, S.glob_nat.p, S.owned_nat.p, D.nlnat.p,
-                                        D.nunat.p, S.dsrc.p, D.pos.p, D.perm.p, D.glob.p,
-                                        D.owned.p, D.nl.p, D.nu.p, D.dsrc_pos.p);
+        k_perm_gather<<<nb, BS, 0, s>>>(mtot, key.p, val.p, D.lptr_dev.p, D.nlong.p, D.soff.p,
+                                        S.glob_nat.p, S.owned_nat.p, D.nlnat.p, D.nunat.p, S.dsrc.p, D.pos.p,
+                                        D.perm.p, D.glob.p, D.owned.p, D.nl.p, D.nu.p, D.dsrc_pos.p);
         R2P_LAUNCH();
         R2P_HIP(hipStreamSynchronize(s));
     }
     double t1 = r2p_now_ms();
     P->ms_order = t1 - t0;       // membership (when rebuilt), levels and the local order
-    // 4. slices of 64 rows per level, entry bases
-    k_slice_count<<<r2p_blocks(nseg + 1, BS), BS, 0, s>>>(nseg, D.lptr_dev.p, D.soff.p);
+    // 4. entries: slice widths, overflow starts, columns and block sources
+    int np = r2p_blocks(npos, BS);
+    R2P_TRY(D.wl.ensure(nslice));
+    R2P_TRY(D.wu.ensure(nslice));
+    R2P_TRY(D.wlong.ensure(nslice));
+    R2P_TRY(D.xl_b.ensure(nslice + 1));
+    R2P_TRY(D.xu_b.ensure(nslice + 1));
+    k_slice_width<<<np, BS, 0, s>>>(nslice, D.nl.p, D.nu.p, D.wl.p, D.wu.p, D.wlong.p, D.xl_b.p,
+                                   D.xu_b.p);
     R2P_LAUNCH();
-    int nslice = 0;
-    R2P_TRY(r2p_scan_int(D.soff.p, D.soff.p, nseg + 1, &nslice, P->iscratch, P->pin, s));
-    D.nslice = nslice;
-    R2P_TRY(D.sl_start.ensure(nslice));
-    R2P_TRY(D.sl_cnt.ensure(nslice));
-    R2P_TRY(D.sl_wl.ensure(nslice));
-    R2P_TRY(D.sl_wu.ensure(nslice));
-    R2P_TRY(D.sl_bl.ensure(nslice + 1));
-    R2P_TRY(D.sl_bu.ensure(nslice + 1));
-    k_slice_fill<<<nseg, 64, 0, s>>>(nseg, D.lptr_dev.p, D.soff.p, nslice, D.nl.p, D.nu.p,
-                                     D.sl_start.p, D.sl_cnt.p, D.sl_wl.p, D.sl_wu.p, D.sl_of.p);
+    int nlx = 0, nux = 0;
+    R2P_TRY(r2p_scan_int(D.xl_b.p, D.xl_b.p, nslice + 1, &nlx, P->iscratch, P->pin, s));
+    R2P_TRY(r2p_scan_int(D.xu_b.p, D.xu_b.p, nslice + 1, &nux, P->iscratch, P->pin, s));
+    k_overflow_base<<<r2p_blocks(nslice, BS), BS, 0, s>>>(nslice, D.xl_b.p, D.xu_b.p);
     R2P_LAUNCH();
-    k_slice_size<<<r2p_blocks(nslice + 1, BS), BS, 0, s>>>(nslice, D.sl_wl.p, D.sl_bl.p);
-    R2P_LAUNCH();
-    k_slice_size<<<r2p_blocks(nslice + 1, BS), BS, 0, s>>>(nslice, D.sl_wu.p, D.sl_bu.p);
-    R2P_LAUNCH();
-    int nle = 0, nue = 0;
-    R2P_TRY(r2p_scan_int(D.sl_bl.p, D.sl_bl.p, nslice + 1, &nle, P->iscratch, P->pin, s));
-    R2P_TRY(r2p_scan_int(D.sl_bu.p, D.sl_bu.p, nslice + 1, &nue, P->iscratch, P->pin, s));
-    R2P_TRY(D.meta_l.ensure(nslice));
-    R2P_TRY(D.meta_u.ensure(nslice));
-    k_slice_meta<<<r2p_blocks(nslice, BS), BS, 0, s>>>(nslice, D.sl_start.p, D.sl_cnt.p, D.sl_wl.p,
-                                                       D.sl_bl.p, D.sl_wu.p, D.sl_bu.p, D.perm.p,
-                                                       D.lev.p, D.meta_l.p, D.meta_u.p);
-    R2P_LAUNCH();
+    const long nle = (long)nslice * RAS_MENT + nlx, nue = (long)nslice * RAS_MENT + nux;
+    if (nle > 0x7fffffffL || nue > 0x7fffffffL) {
+        r2p_set_error("%ld factor blocks exceed the factor storage", std::max(nle, nue));
+        return R2P_EINVAL;
+    }
     D.nlent = nle;
     D.nuent = nue;
-    // RAS_PAD entries of padding after each array: the sweep reads MAXK slot
-    // pairs of every slice (the ones past its own are ignored)
-    R2P_TRY(D.lcol.ensure(nle + RAS_PAD));
-    R2P_TRY(D.ucol.ensure(nue + RAS_PAD));
-    R2P_TRY(D.lsrc.ensure(nle));
-    R2P_TRY(D.usrc.ensure(nue));
-    R2P_HIP(hipMemsetAsync(D.lcol.p, 0xff, sizeof(int) * (size_t)(nle + RAS_PAD), s));
-    R2P_HIP(hipMemsetAsync(D.ucol.p, 0xff, sizeof(int) * (size_t)(nue + RAS_PAD), s));
-    k_fill_entries<<<nb, BS, 0, s>>>(mtot, ph.n, order, J->phi_o.p, D.perm.p, S.glob_nat.p,
-                                     S.aptr.p, S.adj.p, S.asrc.p, D.pos.p, D.glob.p, D.sl_of.p,
-                                     D.sl_start.p, D.sl_bl.p, D.sl_bu.p, D.lcol.p, D.lsrc.p,
-                                     D.ucol.p, D.usrc.p);
+    for (DBuf<int> *c : {&D.lcol, &D.lsw, &D.lsrc, &D.ldiag}) R2P_TRY(c->ensure(nle));
+    for (DBuf<int> *c : {&D.ucol, &D.usw, &D.usrc}) R2P_TRY(c->ensure(nue));
+    R2P_HIP(hipMemsetAsync(D.lcol.p, 0xff, sizeof(int) * (size_t)nle, s));
+    R2P_HIP(hipMemsetAsync(D.ucol.p, 0xff, sizeof(int) * (size_t)nue, s));
+    k_fill_entries<<<np, BS, 0, s>>>(npos, ph.n, order, J->phi_o.p, D.perm.p, S.glob_nat.p,
+                                     S.aptr.p, S.adj.p, S.asrc.p, D.pos.p, D.glob.p, D.xl_b.p,
+                                     D.xu_b.p, D.lcol.p, D.lsrc.p, D.ucol.p, D.usrc.p);
     R2P_LAUNCH();
     // 5. numeric factorisation in FP64
-    R2P_TRY(D.f64.lval.ensure(4L * (nle + RAS_PAD)));
-    R2P_TRY(D.f64.uval.ensure(4L * (nue + RAS_PAD)));
-    R2P_TRY(D.f64.dinv.ensure(4L * mtot));
-    // padding slots stay zero (they are loaded, never used)
-    R2P_HIP(hipMemsetAsync(D.f64.lval.p, 0, sizeof(double) * 4 * (size_t)(nle + RAS_PAD), s));
-    R2P_HIP(hipMemsetAsync(D.f64.uval.p, 0, sizeof(double) * 4 * (size_t)(nue + RAS_PAD), s));
+    R2P_TRY(D.f64.lval.ensure(4 * (size_t)nle));
+    R2P_TRY(D.f64.uval.ensure(4 * (size_t)nue));
+    R2P_TRY(D.f64.dinv.ensure(4 * (size_t)npos));
+    // unused entries and positions stay zero (they are read)
+    R2P_HIP(hipMemsetAsync(D.f64.lval.p, 0, sizeof(double) * 4 * (size_t)nle, s));
+    R2P_HIP(hipMemsetAsync(D.f64.uval.p, 0, sizeof(double) * 4 * (size_t)nue, s));
+    R2P_HIP(hipMemsetAsync(D.f64.dinv.p, 0, sizeof(double) * 4 * (size_t)npos, s));
     R2P_TRY(P->status.ensure(4));
     R2P_HIP(hipMemsetAsync(P->status.p, 0, sizeof(int), s));
     FactArgs F;
     F.B.vp = J->vp.p; F.B.vs = J->vs.p; F.B.cw = J->cw.p; F.B.wc = J->wc.p; F.B.wd = J->wd.p;
     F.B.nperf = ph.nperf;
+    F.npos = npos;
     F.lbase = D.sub_lbase.p; F.nlev = D.sub_nlev.p; F.soff = D.soff.p;
-    F.sl_st = D.sl_start.p; F.sl_cn = D.sl_cnt.p; F.sl_bl = D.sl_bl.p; F.sl_bu = D.sl_bu.p;
-    F.sl_of = D.sl_of.p; F.nl = D.nl.p; F.nu = D.nu.p; F.dsrc = D.dsrc_pos.p;
+    F.xlb = D.xl_b.p; F.xub = D.xu_b.p; F.glob = D.glob.p;
+    F.nl = D.nl.p; F.nu = D.nu.p; F.dsrc = D.dsrc_pos.p;
     F.lcol = D.lcol.p; F.ucol = D.ucol.p; F.lsrc = D.lsrc.p; F.usrc = D.usrc.p;
     F.lval = D.f64.lval.p; F.uval = D.f64.uval.p; F.dinv = D.f64.dinv.p; F.status = P->status.p;
-    R2P_TRY(D.ldiag.ensure(nle + RAS_PAD));
-    R2P_TRY(D.xptr.ensure(mtot + 1));
-    R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)(nle + RAS_PAD), s));
-    R2P_HIP(hipMemsetAsync(D.xptr.p + mtot, 0, sizeof(int), s));
+    R2P_TRY(D.xptr.ensure(npos + 1));
+    R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)nle, s));
+    R2P_HIP(hipMemsetAsync(D.xptr.p + npos, 0, sizeof(int), s));
     F.ldiag = D.ldiag.p; F.xptr = D.xptr.p; F.xl = nullptr;
-    k_bilu_gather<<<nb, BS, 0, s>>>(mtot, F);
+    k_bilu_gather<<<np, BS, 0, s>>>(F);
     R2P_LAUNCH();
-    k_bilu_sym<<<nb, BS, 0, s>>>(mtot, F, 0);
+    k_bilu_sym<<<np, BS, 0, s>>>(F, 0);
     R2P_LAUNCH();
     int nx = 0;
-    R2P_TRY(r2p_scan_int(D.xptr.p, D.xptr.p, mtot + 1, &nx, P->iscratch, P->pin, s));
+    R2P_TRY(r2p_scan_int(D.xptr.p, D.xptr.p, npos + 1, &nx, P->iscratch, P->pin, s));
     R2P_TRY(D.xl.ensure(nx));
     F.xl = D.xl.p;
-    k_bilu_sym<<<nb, BS, 0, s>>>(mtot, F, 1);
+    k_bilu_sym<<<np, BS, 0, s>>>(F, 1);
     R2P_LAUNCH();
     k_bilu0<<<ns, BWG, 0, s>>>(F);
     R2P_LAUNCH();
-    if (P->o.precision == R2P_FP32) {
-        long nlp = 4L * (nle + RAS_PAD), nup = 4L * (nue + RAS_PAD);
-        R2P_TRY(D.f32.lval.ensure(nlp));
-        R2P_TRY(D.f32.uval.ensure(nup));
-        R2P_TRY(D.f32.dinv.ensure(4L * mtot));
-        k_cast<float><<<r2p_blocks(nlp, BS), BS, 0, s>>>(nlp, D.f64.lval.p, D.f32.lval.p);
+    // the vectors' unused positions are read too: zero, and never written
+    const bool f32 = P->o.precision == R2P_FP32;
+    if (f32) {
+        R2P_TRY(D.f32.lval.ensure(4 * (size_t)nle));
+        R2P_TRY(D.f32.uval.ensure(4 * (size_t)nue));
+        R2P_TRY(D.f32.dinv.ensure(4 * (size_t)npos));
+        k_cast<float><<<r2p_blocks(4L * nle, BS), BS, 0, s>>>(4L * nle, D.f64.lval.p, D.f32.lval.p);
         R2P_LAUNCH();
-        k_cast<float><<<r2p_blocks(nup, BS), BS, 0, s>>>(nup, D.f64.uval.p, D.f32.uval.p);
+        k_cast<float><<<r2p_blocks(4L * nue, BS), BS, 0, s>>>(4L * nue, D.f64.uval.p, D.f32.uval.p);
         R2P_LAUNCH();
-        k_cast<float><<<r2p_blocks(4L * mtot, BS), BS, 0, s>>>(4L * mtot, D.f64.dinv.p, D.f32.dinv.p);
+        k_cast<float><<<r2p_blocks(4L * npos, BS), BS, 0, s>>>(4L * npos, D.f64.dinv.p, D.f32.dinv.p);
         R2P_LAUNCH();
-        R2P_TRY(P->t_rasf.ensure(2L * mtot));
-        R2P_TRY(P->t_rlf.ensure(2L * mtot));
-        R2P_HIP(hipMemsetAsync(P->t_rasf.p, 0, sizeof(float) * 2 * (size_t)mtot, s));
+        R2P_TRY(P->t_rasf.ensure(2 * (size_t)npos));
+        R2P_TRY(P->t_rlf.ensure(2 * (size_t)npos));
+        R2P_HIP(hipMemsetAsync(P->t_rasf.p, 0, sizeof(float) * 2 * (size_t)npos, s));
+        R2P_HIP(hipMemsetAsync(P->t_rlf.p, 0, sizeof(float) * 2 * (size_t)npos, s));
     } else {
-        R2P_TRY(P->t_ras.ensure(2L * mtot));
-        R2P_TRY(P->t_rl.ensure(2L * mtot));
-        R2P_HIP(hipMemsetAsync(P->t_ras.p, 0, sizeof(double) * 2 * (size_t)mtot, s));
+        R2P_TRY(P->t_ras.ensure(2 * (size_t)npos));
+        R2P_TRY(P->t_rl.ensure(2 * (size_t)npos));
+        R2P_HIP(hipMemsetAsync(P->t_ras.p, 0, sizeof(double) * 2 * (size_t)npos, s));
+        R2P_HIP(hipMemsetAsync(P->t_rl.p, 0, sizeof(double) * 2 * (size_t)npos, s));
     }
-    // entry classes for the sweep of the precision set up
+    // columns and metadata for the sweep of the precision set up
     {
-        bool f32 = P->o.precision == R2P_FP32;
         int ring = f32 ? RingSize<float>::rows : RingSize<double>::rows;
         int ncw = f32 ? Sweep<float>::ncw : Sweep<double>::ncw;
         R2P_TRY(D.swin.ensure(ns));
-        k_sub_window<<<ns, 256, 0, s>>>(D.sub_lbase.p, D.sub_nlev.p, D.lptr_dev.p, ring, D.swin.p);
+        R2P_TRY(D.meta_l.ensure(nslice));
+        R2P_TRY(D.meta_u.ensure(nslice));
+        k_sub_window<<<ns, 256, 0, s>>>(D.sub_lbase.p, D.sub_nlev.p, D.soff.p, ring, D.swin.p);
         R2P_LAUNCH();
-        if (D.nslice > 0) {
-            k_entry_class<true><<<D.nslice, 64, 0, s>>>(ns, D.sub_lbase.p, D.sub_nlev.p, D.soff.p,
-                                                        D.lptr_dev.p, D.swin.p, D.meta_l.p,
-                                                        D.lcol.p, ncw);
-            R2P_LAUNCH();
-            k_entry_class<false><<<D.nslice, 64, 0, s>>>(ns, D.sub_lbase.p, D.sub_nlev.p, D.soff.p,
-                                                         D.lptr_dev.p, D.swin.p, D.meta_u.p,
-                                                         D.ucol.p, ncw);
-            R2P_LAUNCH();
-        }
+        k_sweep_cols<true><<<nslice, 64, 0, s>>>(ns, D.sub_lbase.p, D.sub_nlev.p, D.soff.p, D.swin.p,
+                                                 D.perm.p, D.lev.p, D.wl.p, D.wlong.p, D.xl_b.p, D.lcol.p, ncw,
+                                                 D.lsw.p, D.meta_l.p);
+        R2P_LAUNCH();
+        k_sweep_cols<false><<<nslice, 64, 0, s>>>(ns, D.sub_lbase.p, D.sub_nlev.p, D.soff.p, D.swin.p,
+                                                  D.perm.p, D.lev.p, D.wu.p, D.wlong.p, D.xu_b.p, D.ucol.p, ncw,
+                                                  D.usw.p, D.meta_u.p);
+        R2P_LAUNCH();
     }
     R2P_HIP(hipMemcpyAsync(hflag, P->status.p, sizeof(int), hipMemcpyDeviceToHost, s));
     R2P_HIP(hipStreamSynchronize(s));
@@ -1367,13 +1411,10 @@ static int ras_solve_t(r2p_cpr *P, const double *r, double *out, const double *x
     k_ras_gather<T><<<nb, BS, 0, s>>>(mtot, P->rs.glob_nat.p, D.pos.p, r, rl, D.prog.p, ns);
     R2P_LAUNCH();
     SweepArgs<T> A;
-    A.lbase = D.sub_lbase.p; A.nlev = D.sub_nlev.p; A.soff = D.soff.p; A.lptr = D.lptr_dev.p;
+    A.lbase = D.sub_lbase.p; A.nlev = D.sub_nlev.p; A.soff = D.soff.p;
     A.mL = D.meta_l.p; A.mU = D.meta_u.p;
-    A.lcol = D.lcol.p; A.ucol = D.ucol.p;
+    A.lcol = D.lsw.p; A.ucol = D.usw.p;
     A.lval = F.lval.p; A.uval = F.uval.p; A.dinv = F.dinv.p; A.rl = rl; A.y = y;
-    A.mtot = mtot;
-    A.lpad = D.nlent;
-    A.upad = D.nuent;
     A.ns = ns;
     A.prog = D.prog.p;
     // helpers only where they fit beside the sweeps and share their XCDs
@@ -1404,8 +1445,8 @@ extern "C" int r2p_ras_info(r2p_cpr *P, int sub, int *nsub, int *m, int *nblk, i
     if (nlevels) *nlevels = P->rd.h_nlev[sub];
     if (nblk) {
         std::vector<int> nl(b - a), nu(b - a);
-        R2P_HIP(hipMemcpy(nl.data(), P->rd.nl.p + a, sizeof(int) * (b - a), hipMemcpyDeviceToHost));
-        R2P_HIP(hipMemcpy(nu.data(), P->rd.nu.p + a, sizeof(int) * (b - a), hipMemcpyDeviceToHost));
+        R2P_HIP(hipMemcpy(nl.data(), P->rd.nlnat.p + a, sizeof(int) * (b - a), hipMemcpyDeviceToHost));
+        R2P_HIP(hipMemcpy(nu.data(), P->rd.nunat.p + a, sizeof(int) * (b - a), hipMemcpyDeviceToHost));
         long t = 0;
         for (int i = 0; i < b - a; i++) t += nl[i] + nu[i];
         *nblk = (int)t;
@@ -1420,7 +1461,7 @@ extern "C" int r2p_ras_export(r2p_cpr *P, int sub, int *glob, int *level, unsign
     hipStream_t s = (hipStream_t)stream;
     R2P_HIP(hipStreamSynchronize(s));
     RasDyn &D = P->rd;
-    int mtot = P->rs.mtot, a = P->rs.h_off[sub], b = P->rs.h_off[sub + 1], m = b - a;
+    const size_t npos = D.npos;
     auto pull = [&](const auto *src, size_t cnt, auto &dst) -> int {
         dst.resize(cnt);
         if (cnt) {
@@ -1429,45 +1470,52 @@ extern "C" int r2p_ras_export(r2p_cpr *P, int sub, int *glob, int *level, unsign
         }
         return 0;
     };
-    std::vector<int> g, pm, lv, nl, nu, slof, slst, slbl, slbu, lc, uc;
+    std::vector<int> g, pm, lv, nl, nu, so, xb[2], cc[2];
     std::vector<unsigned char> ow;
-    std::vector<double> lvv, uvv, dv;
-    R2P_TRY(pull(D.glob.p, mtot, g));
-    R2P_TRY(pull(D.perm.p, mtot, pm));
-    R2P_TRY(pull(D.lev.p, mtot, lv));
-    R2P_TRY(pull(D.nl.p, mtot, nl));
-    R2P_TRY(pull(D.nu.p, mtot, nu));
-    R2P_TRY(pull(D.sl_of.p, mtot, slof));
-    R2P_TRY(pull(D.sl_start.p, D.nslice, slst));
-    R2P_TRY(pull(D.sl_bl.p, D.nslice, slbl));
-    R2P_TRY(pull(D.sl_bu.p, D.nslice, slbu));
-    R2P_TRY(pull(D.lcol.p, D.nlent, lc));
-    R2P_TRY(pull(D.ucol.p, D.nuent, uc));
-    R2P_TRY(pull(D.f64.lval.p, 4L * D.nlent, lvv));
-    R2P_TRY(pull(D.f64.uval.p, 4L * D.nuent, uvv));
-    R2P_TRY(pull(D.f64.dinv.p, 4L * mtot, dv));
-    R2P_TRY(pull(D.owned.p, mtot, ow));
-    long k = 0;
-    for (int p = a; p < b; p++) {
-        int i = p - a;
+    std::vector<double> vv[2], dv;
+    R2P_TRY(pull(D.glob.p, npos, g));
+    R2P_TRY(pull(D.perm.p, npos, pm));
+    R2P_TRY(pull(D.lev.p, (size_t)P->rs.mtot, lv));
+    R2P_TRY(pull(D.nl.p, npos, nl));
+    R2P_TRY(pull(D.nu.p, npos, nu));
+    R2P_TRY(pull(D.soff.p, (size_t)D.nseg + 1, so));
+    R2P_TRY(pull(D.xl_b.p, (size_t)D.nslice, xb[0]));
+    R2P_TRY(pull(D.xu_b.p, (size_t)D.nslice, xb[1]));
+    R2P_TRY(pull(D.lcol.p, (size_t)D.nlent, cc[0]));
+    R2P_TRY(pull(D.ucol.p, (size_t)D.nuent, cc[1]));
+    R2P_TRY(pull(D.f64.lval.p, 4 * (size_t)D.nlent, vv[0]));
+    R2P_TRY(pull(D.f64.uval.p, 4 * (size_t)D.nuent, vv[1]));
+    R2P_TRY(pull(D.f64.dinv.p, 4 * npos, dv));
+    R2P_TRY(pull(D.owned.p, npos, ow));
+    long k = 0, i = 0;
+    int p0 = RAS_ROWS * so[D.h_lbase[sub]], p1 = RAS_ROWS * so[D.h_lbase[sub + 1]];
+    // rows by level, descending predecessor count (up to 7), natural order
+    std::vector<int> rows;
+    for (int p = p0; p < p1; p++)
+        if (pm[p] >= 0) rows.push_back(p);
+    auto order = [&](int p) {
+        return std::make_tuple(lv[pm[p]], 7 - std::min(nl[p], 7), pm[p]);
+    };
+    std::sort(rows.begin(), rows.end(), [&](int p, int q) { return order(p) < order(q); });
+    for (int p : rows) {
         if (glob) glob[i] = g[p];
         if (level) level[i] = lv[pm[p]];
         if (owned) owned[i] = ow[p];
-        if (dinv) memcpy(dinv + 4L * i, dv.data() + 4L * p, 4 * sizeof(double));
-        int sl = slof[p], r = p - slst[sl];
+        if (dinv) memcpy(dinv + 4 * i, dv.data() + 4L * p, 4 * sizeof(double));
+        i++;
         for (int part = 0; part < 2; part++) {
+            const RasRow at(xb[part].data(), p);
             int cnt = part == 0 ? nl[p] : nu[p];
-            long base = part == 0 ? slbl[sl] : slbu[sl];
-            const std::vector<int> &cc = part == 0 ? lc : uc;
-            const std::vector<double> &vv = part == 0 ? lvv : uvv;
             for (int e = 0; e < cnt; e++, k++) {
-                long idx = ras_entry(base, r, e);
+                long idx = at(e);
                 if (erow) erow[k] = g[p];
-                if (ecol) ecol[k] = g[cc[idx] & COL_MASK];
-                if (eval) memcpy(eval + 4 * k, vv.data() + 4 * idx, 4 * sizeof(double));
+                if (ecol) ecol[k] = g[cc[part][idx]];
+                if (eval)
+                    for (int j = 0; j < 2; j++)
+                        memcpy(eval + 4 * k + 2 * j, vv[part].data() + ras_val(idx, j),
+                               2 * sizeof(double));
             }
         }
     }
-    (void)m;
     return 0;
 }

@@ -1,0 +1,115 @@
+"""The RAS sweep and factorisation over the shapes of their slice layout.
+
+Rows of a level are cut into slices of 32 positions; rows with more than four
+predecessors or successors take two positions, and entries past the eighth
+lie apart.  The cases put level widths at and around 32, rows of every length
+up to a well's 30 perforations (eight and nine included), levels narrower and
+wider than the sweep's ring of recent results, and both precisions.
+
+Checked from the exported factors themselves: the product L U equals the
+matrix on the pattern (what defines ILU(0)), and one application equals a
+level-by-level solve in NumPy.  Bounds: a product entry sums at most m terms,
+m the longest row, each off by a few eps times the condition of a pivot block;
+a solve in `levels` levels of rows of m entries is off by at most about
+eps m levels, taken five times.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+# nx, ny, nz, px, py, overlap, order (0 natural, 1 potential), pressure spread
+CASES = [(32, 31, 1, 1, 1, 0, 0, 0.0), (34, 33, 2, 1, 1, 0, 0, 0.0), (67, 1, 1, 2, 1, 1, 0, 0.0),
+         (9, 7, 5, 2, 2, 0, 1, 50.0), (12, 11, 7, 3, 2, 2, 1, 50.0), (3, 3, 30, 1, 1, 0, 1, 5.0),
+         (5, 4, 8, 2, 1, 1, 1, 50.0), (5, 4, 9, 1, 1, 1, 0, 50.0), (1, 1, 2, 1, 1, 0, 1, 5.0),
+         (64, 64, 40, 1, 1, 0, 1, 50.0)]
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(str(v) for v in c))
+def test_factors_and_application(case, precision):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1701_06254_amd import r2p
+    nx, ny, nz, px, py, overlap, order, spread = case
+    w = workloads.make_tiny(nx, ny, nz)
+    w["wells"] = w["wells"][:1] + w["wells"][1:] * (nx * ny > 1)
+    m = r2p.Model(w)
+    rng = np.random.default_rng(nx + ny + nz)
+    x = torch.as_tensor(workloads.random_state(w, rng, p_spread=spread), device="cuda")
+    J = r2p.Jacobian(m)
+    J.assemble(x, m.initial_state(), 2.0)
+    P = r2p.Cpr().setup(J, r2p.cpr_opts(px=px, py=py, overlap=overlap, order=order,
+                                        precision=precision))
+    r = rng.standard_normal(2 * (m.n + m.nw))
+    got = P.ras_apply(torch.as_tensor(r, device="cuda")).cpu().numpy().reshape(-1, 2)
+    r = r.reshape(-1, 2)
+    if precision == 1:
+        r = r.astype(np.float32).astype(np.float64)
+    ref = np.zeros_like(got)
+    longest = levels = 0
+    for s in range(P.ras_info()):
+        d = P.ras_subdomain(s)
+        g, lev = d["glob"], d["level"]
+        k = len(g)
+        pos = np.full(m.n + m.nw, -1)
+        pos[g] = np.arange(k)
+        er, ec, ev = pos[d["erow"]], pos[d["ecol"]], d["eval"]
+        assert (er >= 0).all() and (ec >= 0).all()
+        low = lev[ec] < lev[er]
+        assert (lev[ec] != lev[er]).all()
+        longest = max(longest, np.bincount(er, minlength=k).max(initial=0))
+        levels = max(levels, lev.max() + 1)
+        if precision == 0 and k <= 5000:
+            _check_product(J, g, er, ec, ev, low, d["dinv"])
+        if precision == 1:
+            ev, d["dinv"] = ev.astype(np.float32), d["dinv"].astype(np.float32)
+        y = r[g].copy()
+        for part in (True, False):
+            seq = range(lev.max() + 1) if part else range(lev.max(), -1, -1)
+            sel = np.nonzero(low == part)[0]
+            sel = sel[np.argsort(lev[er[sel]], kind="stable")]
+            cut = np.searchsorted(lev[er[sel]], np.arange(lev.max() + 2))
+            rows = np.argsort(lev, kind="stable")
+            rcut = np.searchsorted(lev[rows], np.arange(lev.max() + 2))
+            for L in seq:
+                e = sel[cut[L]:cut[L + 1]]
+                np.subtract.at(y, er[e], np.einsum("eij,ej->ei", ev[e], y[ec[e]]))
+                if not part:
+                    q = rows[rcut[L]:rcut[L + 1]]
+                    y[q] = np.einsum("eij,ej->ei", d["dinv"][q], y[q])
+        ref[g[d["owned"]]] = y[d["owned"]]
+    eps = np.finfo(np.float64 if precision == 0 else np.float32).eps
+    assert np.linalg.norm(got - ref) <= 5 * eps * longest * levels * np.linalg.norm(ref)
+    assert longest >= min(nz, 30)
+    if nx == 64:
+        assert levels < 64, "levels wider than the ring were meant"
+
+
+def _check_product(J, g, er, ec, ev, low, dinv):
+    """(L U)_ij = A_ij on the pattern of the subdomain's rows."""
+    rp, col, val = J.export()
+    k = len(g)
+    A = {(int(i), int(j)): v for i, j, v in
+         zip(np.repeat(np.arange(len(rp) - 1), np.diff(rp)), col, val)}
+    D = np.linalg.inv(dinv)
+    cond = np.linalg.cond(D).max()
+    lrow, urow = [dict() for _ in range(k)], [dict() for _ in range(k)]
+    for i, j, v, l in zip(er, ec, ev, low):
+        (lrow if l else urow)[i][j] = v
+    for i in range(k):
+        want = dict(urow[i])
+        want.update(lrow[i])
+        want[i] = None
+        for j in want:
+            S, M, m = np.zeros((2, 2)), np.zeros((2, 2)), 1
+            for q, l in list(lrow[i].items()) + [(i, np.eye(2))]:
+                u = D[j] if q == j else urow[q].get(j)
+                if u is not None:
+                    S, M, m = S + l @ u, M + np.abs(l) @ np.abs(u), m + 1
+            a = A[(int(g[i]), int(g[j]))]
+            tol = 16 * m * np.finfo(float).eps * cond * max(M.max(), np.abs(a).max())
+            assert np.abs(S - a).max() <= tol, (i, j)
