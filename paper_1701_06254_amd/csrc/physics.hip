@@ -25,6 +25,7 @@
 int r2p_noalloc_init(int dev);
 
 constexpr int BS = 256;
+constexpr int NORM_BLOCKS = 2048;    // workgroups of the scaled norm, at most
 
 // --------------------------------------------------------- property laws
 __device__ __forceinline__ double bfac(double c, double p, double pref) {
@@ -145,7 +146,7 @@ extern "C" int r2p_model_create(const r2p_model_desc *d, r2p_model **out) {
         (rc = m->w_kind.ensure(d->nw)) || (rc = m->w_ctrl.ensure(d->nw)) ||
         (rc = m->w_target.ensure(d->nw)) || (rc = m->w_zb.ensure(d->nw)) ||
         (rc = m->w_rw.ensure(d->nw)) || (rc = m->w_skin.ensure(d->nw)) ||
-        (rc = m->red.ensure(64)) || (rc = m->pin.ensure(4096)))
+        (rc = m->red.ensure(2 * NORM_BLOCKS)) || (rc = m->pin.ensure(4096)))
         return fail(rc);
 #define H2D(dst, src, cnt)                                                              \
     if ((cnt) > 0) {                                                                    \
@@ -284,6 +285,13 @@ __device__ __forceinline__ FaceTerms face_phase(const Phys &P, int ph, double pa
     return t;
 }
 
+// Lane j's value in every lane (j the same in all of them).
+__device__ __forceinline__ double lane_value(double v, int j) {
+    long long u = __double_as_longlong(v);
+    unsigned lo = __builtin_amdgcn_readlane((int)u, j), hi = __builtin_amdgcn_readlane((int)(u >> 32), j);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
 struct PerfTerms {
     double qo, qw, qo_p, qo_s, qo_b, qw_p, qw_s, qw_b;
 };
@@ -327,14 +335,65 @@ struct AsmArgs {
     double dt;
     double2 *vp, *vs, *cw;
     double *b, *phi_o;
+    // wells
+    const int *w_ptr, *w_ctrl, *perf_cell;
+    const double *w_target;
+    double2 *wc;
+    double *wd;
+    int nwblk, ncellblk;         // workgroups of wells (a multiple of 8, first) and of cells
 };
+
+// One wavefront per well: the constraint equation (Eq 11-14) and its row.
+// The lanes take the perforations, whose terms each wait on two dependent
+// loads, side by side; the sums then run over them in their order.  (One lane
+// per well walked 50 perforations in 59 us, longer than a third of the cells.)
+__device__ __forceinline__ void assemble_well(const AsmArgs &A, int w, int lane) {
+    const Phys &P = A.P;
+    const int nxy = P.nx * P.ny, rw = P.n + w;
+    const double *x = A.x;
+    double pbh = x[2 * (long)rw];
+    double sgn = A.w_kind[w] == 0 ? 1.0 : -1.0;
+    int ctrl = A.w_ctrl[w];
+    double sum = 0.0, dsum_pb = 0.0;
+    for (int q0 = A.w_ptr[w]; q0 < A.w_ptr[w + 1]; q0 += 64) {
+        int cnt = min(64, A.w_ptr[w + 1] - q0), q = q0 + lane;
+        double sel = 0.0, sel_p = 0.0, sel_s = 0.0, sel_b = 0.0;
+        if (lane < cnt) {
+            int c = A.perf_cell[q];
+            PerfTerms t = perf_terms(P, A.w_kind[w], A.perf_wi[q], x[2 * (long)c], x[2 * (long)c + 1],
+                                     pbh, A.w_zb[w] - depth_of(P, c / nxy));
+            if (ctrl == 1) { sel = t.qw; sel_p = t.qw_p; sel_s = t.qw_s; sel_b = t.qw_b; }
+            else if (ctrl == 2) { sel = t.qo; sel_p = t.qo_p; sel_s = t.qo_s; sel_b = t.qo_b; }
+            else if (ctrl == 3) { sel = t.qo + t.qw; sel_p = t.qo_p + t.qw_p; sel_s = t.qo_s + t.qw_s; sel_b = t.qo_b + t.qw_b; }
+            A.wc[q] = ctrl != 0 ? make_double2(sel_p, sel_s) : make_double2(0.0, 0.0);
+        }
+        for (int j = 0; j < cnt; j++) {
+            sum += lane_value(sel, j);
+            dsum_pb += lane_value(sel_b, j);
+        }
+    }
+    if (lane != 0) return;
+    double F = ctrl == 0 ? pbh - A.w_target[w] : sum - sgn * A.w_target[w];
+    A.b[2 * (long)rw] = -F;
+    A.b[2 * (long)rw + 1] = -x[2 * (long)rw + 1];
+    A.wd[w] = ctrl == 0 ? 1.0 : dsum_pb;
+}
 
 // One thread per cell: accumulation, the six faces in ascending order of the
 // neighbour's index, then the perforation, exactly as the residual is summed
-// cell by cell.  Writes the 7 slot blocks, b = -F and the oil potential.
-__global__ __launch_bounds__(256) void k_assemble_cells(AsmArgs A) {
+// cell by cell.  Writes the 7 slot blocks, b = -F and the oil potential.  The
+// wells' rows run in workgroups of the same launch, ahead of the cells'.
+// Bound by its stores, 224 of the 304 bytes of a cell: as ordinary stores the
+// 14 streams displace each other's and the neighbours' lines (164 us at 2M
+// cells), as non-temporal ones they leave at 4.9 TB/s (124 us).
+__global__ __launch_bounds__(256) void k_assemble(AsmArgs A) {
     const Phys &P = A.P;
-    int c = blockIdx.x * blockDim.x + threadIdx.x;
+    if ((int)blockIdx.x < A.nwblk) {
+        int w = blockIdx.x * (blockDim.x / 64) + threadIdx.x / 64;
+        if (w < P.nw) assemble_well(A, __builtin_amdgcn_readfirstlane(w), threadIdx.x & 63);
+        return;
+    }
+    int c = xcd_block((int)blockIdx.x - A.nwblk, A.ncellblk) * blockDim.x + threadIdx.x;
     if (c >= P.n) return;
     int n = P.n, nx = P.nx, nxy = P.nx * P.ny;
     int i = c % nx, j = (c / nx) % P.ny, k = c / nxy;
@@ -407,41 +466,10 @@ __global__ __launch_bounds__(256) void k_assemble_cells(AsmArgs A) {
     A.b[2 * c + 1] = -F[1];
     for (int t = 0; t < 7; t++) {
         const double *blk = t == 0 ? D : O[t];
-        A.vp[(long)t * n + c] = make_double2(blk[0], blk[2]);
-        A.vs[(long)t * n + c] = make_double2(blk[1], blk[3]);
+        st_stream2(&A.vp[(long)t * n + c], make_double2(blk[0], blk[2]));
+        st_stream2(&A.vs[(long)t * n + c], make_double2(blk[1], blk[3]));
     }
     A.phi_o[c] = p - gamma_of(P, P.rho_o, P.c_o, p) * dc;
-}
-
-// One thread per well: the constraint equation (Eq 11-14) and its row.
-__global__ void k_assemble_wells(Phys P, const int *w_ptr, const int *w_kind, const int *w_ctrl,
-                                 const double *w_target, const double *w_zb, const int *perf_cell,
-                                 const double *perf_wi, const double *x, double2 *wc, double *wd,
-                                 double *b) {
-    int w = blockIdx.x * blockDim.x + threadIdx.x;
-    if (w >= P.nw) return;
-    int n = P.n, nxy = P.nx * P.ny;
-    int rw = n + w;
-    double pbh = x[2 * rw];
-    double sgn = w_kind[w] == 0 ? 1.0 : -1.0;
-    int ctrl = w_ctrl[w];
-    double sum = 0.0, dsum_pb = 0.0;
-    for (int q = w_ptr[w]; q < w_ptr[w + 1]; q++) {
-        int c = perf_cell[q];
-        PerfTerms t = perf_terms(P, w_kind[w], perf_wi[q], x[2 * c], x[2 * c + 1], pbh,
-                                 w_zb[w] - depth_of(P, c / nxy));
-        double sel = 0.0, sel_p = 0.0, sel_s = 0.0, sel_b = 0.0;
-        if (ctrl == 1) { sel = t.qw; sel_p = t.qw_p; sel_s = t.qw_s; sel_b = t.qw_b; }
-        else if (ctrl == 2) { sel = t.qo; sel_p = t.qo_p; sel_s = t.qo_s; sel_b = t.qo_b; }
-        else if (ctrl == 3) { sel = t.qo + t.qw; sel_p = t.qo_p + t.qw_p; sel_s = t.qo_s + t.qw_s; sel_b = t.qo_b + t.qw_b; }
-        sum += sel;
-        dsum_pb += sel_b;
-        wc[q] = ctrl != 0 ? make_double2(sel_p, sel_s) : make_double2(0.0, 0.0);
-    }
-    double F = ctrl == 0 ? pbh - w_target[w] : sum - sgn * w_target[w];
-    b[2 * rw] = -F;
-    b[2 * rw + 1] = -x[2 * rw + 1];
-    wd[w] = ctrl == 0 ? 1.0 : dsum_pb;
 }
 
 extern "C" int r2p_jacobian_create(r2p_model *m, r2p_jacobian **out) {
@@ -481,72 +509,15 @@ extern "C" int r2p_assemble_jacobian(r2p_model *m, const double *x, const double
     A.cell_perf = m->cell_perf.p; A.perf_well = m->perf_well.p; A.w_kind = m->w_kind.p;
     A.x = x; A.xold = x_old; A.dt = dt;
     A.vp = J->vp.p; A.vs = J->vs.p; A.cw = J->cw.p; A.b = b; A.phi_o = J->phi_o.p;
-    k_assemble_cells<<<r2p_blocks(m->ph.n, BS), BS, 0, s>>>(A);
+    A.w_ptr = m->w_ptr.p; A.w_ctrl = m->w_ctrl.p; A.w_target = m->w_target.p;
+    A.perf_cell = m->perf_cell.p; A.wc = J->wc.p; A.wd = J->wd.p;
+    A.ncellblk = r2p_blocks(m->ph.n, BS);
+    A.nwblk = (r2p_blocks(m->ph.nw, BS / 64) + 7) / 8 * 8;
+    if (m->ph.nw == 0) A.nwblk = 0;
+    k_assemble<<<A.nwblk + A.ncellblk, BS, 0, s>>>(A);
     R2P_LAUNCH();
-    if (m->ph.nw > 0) {
-        k_assemble_wells<<<r2p_blocks(m->ph.nw, 64), 64, 0, s>>>(
-            m->ph, m->w_ptr.p, m->w_kind.p, m->w_ctrl.p, m->w_target.p, m->w_zb.p, m->perf_cell.p,
-            m->perf_wi.p, x, J->wc.p, J->wd.p, b);
-        R2P_LAUNCH();
-    }
     J->state = 1;
     J->dec_kind = 0;
-    return 0;
-}
-
-// ------------------------------------------------------------ scaled norm
-// Non-negative doubles order like their bit patterns, so an unsigned max is
-// an exact, order-independent reduction.  NaN is flagged separately.
-__global__ void k_resnorm(Phys P, const double *phi, const double *w_target, const double *b,
-                          double dt, unsigned long long *red) {
-    __shared__ unsigned long long smax[BS / 64];
-    __shared__ int snan[BS / 64];
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    double v = 0.0;
-    int nan = 0;
-    if (i < P.n) {
-        double pv = P.dx * P.dy * P.dz * phi[i] / P.alpha;
-        double a = fabs(b[2 * i]) * dt / pv, c = fabs(b[2 * i + 1]) * dt / pv;
-        nan = (a != a) || (c != c);
-        v = a > c ? a : c;
-    } else if (i < P.n + P.nw) {
-        int w = (int)(i - P.n);
-        double t = fabs(w_target[w]);
-        v = fabs(b[2 * i]) / (t > 0.0 ? t : 1.0);
-        nan = v != v;
-    }
-    unsigned long long u = nan ? 0ull : (unsigned long long)__double_as_longlong(v);
-    for (int d = 32; d > 0; d >>= 1) {
-        unsigned long long o = __shfl_xor(u, d, 64);
-        u = o > u ? o : u;
-        nan |= __shfl_xor(nan, d, 64);
-    }
-    int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) { smax[wid] = u; snan[wid] = nan; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long mx = 0; int nn = 0;
-        for (int w = 0; w < (int)(blockDim.x >> 6); w++) { mx = smax[w] > mx ? smax[w] : mx; nn |= snan[w]; }
-        atomicMax(&red[0], mx);
-        if (nn) atomicOr(&red[1], 1ull);
-    }
-}
-
-extern "C" int r2p_residual_norm(r2p_model *m, const double *b, double dt, double *norm,
-                                 void *stream) {
-    if (!m || !b || !norm) { r2p_set_error("NULL argument"); return R2P_EINVAL; }
-    hipStream_t s = (hipStream_t)stream;
-    R2P_HIP(hipMemsetAsync(m->red.p, 0, 2 * sizeof(unsigned long long), s));
-    long tot = m->ph.n + m->ph.nw;
-    k_resnorm<<<r2p_blocks(tot, BS), BS, 0, s>>>(m->ph, m->phi.p, m->w_target.p, b, dt, m->red.p);
-    R2P_LAUNCH();
-    R2P_HIP(hipMemcpyAsync(m->pin.p, m->red.p, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    R2P_HIP(hipStreamSynchronize(s));
-    unsigned long long *h = (unsigned long long *)m->pin.p;
-    double v;
-    memcpy(&v, &h[0], sizeof(double));
-    *norm = v;
-    if (h[1]) { *norm = NAN; r2p_set_error("non-finite residual"); return R2P_ENAN; }
     return 0;
 }
 
@@ -571,29 +542,38 @@ int r2p_noalloc_init(int dev) {
     return 0;
 }
 
-// Partial maxima of the scaled residual (the same per-row values as
-// k_resnorm) per workgroup: part[blk] = the largest as bits, part[nb + blk]
-// = 1 if a row was not finite.  Every entry is written, so nothing needs
-// clearing between calls.
+// ------------------------------------------------------------ scaled norm
+// Partial maxima of the scaled residual per workgroup: part[blk] = the largest
+// as bits (non-negative doubles order like their bit patterns, so an unsigned
+// max is an exact, order-independent reduction), part[nb + blk] = 1 if a row
+// was NaN.  Every entry is written, so nothing needs clearing between calls.
+// Up to NORM_BLOCKS workgroups (8 per CU), each over several rows: bound by
+// reading b and phi.  (An atomic maximum per 256 rows on one address took 93
+// us at 2M cells, 12 ns each.)
 __global__ void k_resnorm_part(Phys P, const double *phi, const double *w_target, const double *b,
                                double dt, unsigned long long *part) {
     __shared__ unsigned long long smax[BS / 64];
     __shared__ int snan[BS / 64];
-    long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
-    double v = 0.0;
+    unsigned long long u = 0;
     int nan = 0;
-    if (i < P.n) {
-        double pv = P.dx * P.dy * P.dz * phi[i] / P.alpha;
-        double a = fabs(b[2 * i]) * dt / pv, c = fabs(b[2 * i + 1]) * dt / pv;
-        nan = (a != a) || (c != c);
-        v = a > c ? a : c;
-    } else if (i < P.n + P.nw) {
-        int w = (int)(i - P.n);
-        double t = fabs(w_target[w]);
-        v = fabs(b[2 * i]) / (t > 0.0 ? t : 1.0);
-        nan = v != v;
+    const long tot = (long)P.n + P.nw;
+#pragma unroll 2
+    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < tot; i += (long)gridDim.x * blockDim.x) {
+        double v;
+        if (i < P.n) {
+            double pv = P.dx * P.dy * P.dz * phi[i] / P.alpha;
+            double a = fabs(b[2 * i]) * dt / pv, c = fabs(b[2 * i + 1]) * dt / pv;
+            nan |= (a != a) | (c != c);
+            v = a > c ? a : c;
+        } else {
+            double t = fabs(w_target[i - P.n]);
+            v = fabs(b[2 * i]) / (t > 0.0 ? t : 1.0);
+        }
+        bool bad = v != v;
+        unsigned long long o = bad ? 0ull : (unsigned long long)__double_as_longlong(v);
+        nan |= bad;
+        u = o > u ? o : u;
     }
-    unsigned long long u = nan ? 0ull : (unsigned long long)__double_as_longlong(v);
     for (int d = 32; d > 0; d >>= 1) {
         unsigned long long o = __shfl_xor(u, d, 64);
         u = o > u ? o : u;
@@ -639,6 +619,22 @@ __global__ __launch_bounds__(1024) void k_resnorm_fin(int nb, const unsigned lon
     }
 }
 
+extern "C" int r2p_residual_norm(r2p_model *m, const double *b, double dt, double *norm,
+                                 void *stream) {
+    if (!m || !b || !norm) { r2p_set_error("NULL argument"); return R2P_EINVAL; }
+    hipStream_t s = (hipStream_t)stream;
+    int nb = std::min(r2p_blocks((long)m->ph.n + m->ph.nw, BS), NORM_BLOCKS);
+    k_resnorm_part<<<nb, BS, 0, s>>>(m->ph, m->phi.p, m->w_target.p, b, dt, m->red.p);
+    R2P_LAUNCH();
+    // straight into the pinned word: no copy between the kernel and the host
+    k_resnorm_fin<<<1, 1024, 0, s>>>(nb, m->red.p, (double *)m->pin.p);
+    R2P_LAUNCH();
+    R2P_HIP(hipStreamSynchronize(s));
+    *norm = *(volatile double *)m->pin.p;
+    if (*norm != *norm) { *norm = NAN; r2p_set_error("non-finite residual"); return R2P_ENAN; }
+    return 0;
+}
+
 extern "C" int r2p_residual_norm_noalloc(r2p_model *m, const double *b, double dt, double *norm,
                                          void *stream) {
     if (!m || !b || !norm) { r2p_set_error("NULL argument"); return R2P_EINVAL; }
@@ -655,9 +651,10 @@ extern "C" int r2p_residual_norm_noalloc(r2p_model *m, const double *b, double d
     }
     unsigned long long *part = noalloc_ptr[m->dev];
     hipStream_t s = (hipStream_t)stream;
-    k_resnorm_part<<<(int)nb, BS, 0, s>>>(m->ph, m->phi.p, m->w_target.p, b, dt, part);
+    int grid = (int)std::min(nb, (long)NORM_BLOCKS);
+    k_resnorm_part<<<grid, BS, 0, s>>>(m->ph, m->phi.p, m->w_target.p, b, dt, part);
     R2P_LAUNCH();
-    k_resnorm_fin<<<1, 1024, 0, s>>>((int)nb, part, norm);
+    k_resnorm_fin<<<1, 1024, 0, s>>>(grid, part, norm);
     R2P_LAUNCH();
     return 0;
 }

@@ -351,6 +351,12 @@ __device__ __forceinline__ double2 ld_stream2(const double2 *p) {
     v2 v = __builtin_nontemporal_load((const v2 *)p);
     return make_double2(v.x, v.y);
 }
+
+// Streaming store of a pair that the launch does not read again.
+__device__ __forceinline__ void st_stream2(double2 *p, double2 v) {
+    typedef double v2 __attribute__((ext_vector_type(2)));
+    __builtin_nontemporal_store(v2{v.x, v.y}, (v2 *)p);
+}
 template <class T>
 __device__ __forceinline__ T ld_stream(const T *p) {
     return __builtin_nontemporal_load(p);
