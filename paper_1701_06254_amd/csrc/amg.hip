@@ -924,6 +924,17 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
 // restriction that produces b, and the prolonged x + P xc by a pass over the
 // fine rows, so each entry costs one gather.
 
+// Levels of up to FUSE_ROWS rows form the residual and its restriction in one
+// kernel and the prolongation in the post-smoothing kernel: there a kernel is
+// mostly its launch and a few dependent loads (3 to 4.5 us), so two kernels a
+// level instead of four win, although the chains of loads get longer.  A cycle
+// at 243,107 cells and five levels below: 182 us unfused, 171 with all levels
+// fused (its largest, 82,086 rows, takes the same either way).  At 2M cells
+// fusing the levels of 780,824 and 259,434 rows as well makes a solve 7%
+// slower: such levels are bound by memory, and a fused kernel reads the rows
+// in the order of the aggregates and gathers two vectors.
+constexpr int FUSE_ROWS = 1 << 15;
+
 template <class T>
 struct CsrArgs {
     int n, nbs;                  // rows; workgroups of the G-lanes-per-row part
@@ -936,48 +947,85 @@ struct CsrArgs {
     T *xo;                       // down: residual b - A x; up: x + (b - A x) / d
 };
 
+// The iterate a row's entries multiply: x itself, or x plus the coarse
+// correction xc of the row's aggregate.
+template <class T>
+struct PlainX {
+    const T *x;
+    __device__ __forceinline__ T operator()(int j) const { return x[j]; }
+};
+template <class T>
+struct ProlongedX {
+    const T *x, *xc;
+    const int *agg;
+    __device__ __forceinline__ T operator()(int j) const { return x[j] + xc[agg[j]]; }
+};
+
+// Sum of entries z0 .. z1 of a row times the iterate: by a group of G lanes
+// (lane0 of G, in every lane), and by a wavefront.
+template <class T, class X>
+__device__ __forceinline__ T row_sum(const CsrArgs<T> &A, int z0, int z1, int lane0, const X &x) {
+    T acc = (T)0;
+    for (int z = z0 + lane0; z < z1; z += 2 * G) {
+        int zb = z + G < z1 ? z + G : z;
+        int ca = A.col[z], cb = A.col[zb];
+        T va = A.val[z], vb = A.val[zb];
+        T xa = x(ca), xb = x(cb);
+        acc += va * xa + (z + G < z1 ? vb * xb : (T)0);
+    }
+    acc += dpp_move<DPP_XOR1>(acc);
+    acc += dpp_move<DPP_XOR2>(acc);
+    return acc;
+}
+template <class T, class X>
+__device__ __forceinline__ T row_sum_wave(const CsrArgs<T> &A, int z0, int z1, int lane, const X &x) {
+    T acc = (T)0;
+    for (int z = z0 + lane; z < z1; z += 256) {
+        T t[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            int zz = z + 64 * u < z1 ? z + 64 * u : z;
+            T v = A.val[zz] * x(A.col[zz]);
+            t[u] = z + 64 * u < z1 ? v : (T)0;
+        }
+        acc += (t[0] + t[1]) + (t[2] + t[3]);
+    }
+    for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+    return acc;
+}
+
 // MODE: CSR_DOWN xo = b - A x; CSR_UP xo = x + (b - A x) / d; CSR_PRODUCT xo = A x.
 enum { CSR_DOWN = 0, CSR_UP = 1, CSR_PRODUCT = 2 };
-template <class T, int MODE>
-__global__ __launch_bounds__(256) void k_csr_level(CsrArgs<T> A) {
+template <class T, int MODE, class X>
+__device__ __forceinline__ void csr_level(const CsrArgs<T> &A, const X &x) {
     int i, lane0;
-    T acc = (T)0;
+    T acc;
     if ((int)blockIdx.x < A.nbs) {
         i = xcd_block(blockIdx.x, A.nbs) * (blockDim.x / G) + (int)threadIdx.x / G;
         lane0 = threadIdx.x % G;
         if (i >= A.n) return;                 // whole groups leave together
         int z0 = A.rp[i], z1 = A.rp[i + 1];
         if (z1 - z0 > HEAVY) return;
-        for (int z = z0 + lane0; z < z1; z += 2 * G) {
-            int zb = z + G < z1 ? z + G : z;
-            int ca = A.col[z], cb = A.col[zb];
-            T va = A.val[z], vb = A.val[zb];
-            T xa = A.x[ca], xb = A.x[cb];
-            acc += va * xa + (z + G < z1 ? vb * xb : (T)0);
-        }
-#pragma unroll
-        for (int d = 1; d < G; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        acc = row_sum(A, z0, z1, lane0, x);
     } else {
         int w = ((int)blockIdx.x - A.nbs) * (blockDim.x >> 6) + (threadIdx.x >> 6);
         if (w >= A.nheavy) return;
         lane0 = threadIdx.x & 63;
         i = A.heavy[w];
-        int z0 = A.rp[i], z1 = A.rp[i + 1];
-        for (int z = z0 + lane0; z < z1; z += 256) {
-            T t[4];
-#pragma unroll
-            for (int u = 0; u < 4; u++) {
-                int zz = z + 64 * u < z1 ? z + 64 * u : z;
-                T v = A.val[zz] * A.x[A.col[zz]];
-                t[u] = z + 64 * u < z1 ? v : (T)0;
-            }
-            acc += (t[0] + t[1]) + (t[2] + t[3]);
-        }
-        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        acc = row_sum_wave(A, A.rp[i], A.rp[i + 1], lane0, x);
     }
     if (lane0 == 0)
-        A.xo[i] = MODE == CSR_UP ? A.x[i] + (A.b[i] - acc) / A.l1[i]
+        A.xo[i] = MODE == CSR_UP ? x(i) + (A.b[i] - acc) / A.l1[i]
                                  : (MODE == CSR_DOWN ? A.b[i] - acc : acc);
+}
+template <class T, int MODE>
+__global__ __launch_bounds__(256) void k_csr_level(CsrArgs<T> A) {
+    csr_level<T, MODE>(A, PlainX<T>{A.x});
+}
+// Post-smoothing with the prolongation in the same pass (see FUSE_ROWS).
+template <class T>
+__global__ __launch_bounds__(256) void k_csr_up(CsrArgs<T> A, const int *agg, const T *xc) {
+    csr_level<T, CSR_UP>(A, ProlongedX<T>{A.x, xc, agg});
 }
 
 // Restriction P^T r: a group of GR lanes per coarse row (lanes stride over
@@ -1024,6 +1072,101 @@ __global__ __launch_bounds__(256) void k_restrict(int nc, int nbs, const int *mp
             }
             acc += (v[0] + v[1]) + (v[2] + v[3]);
         }
+        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+    }
+    if (lane0 == 0) {
+        bc[I] = acc;
+        if (xc) xc[I] = acc / l1c[I];
+    }
+}
+
+// Residual and restriction of a coarse level in one pass (see FUSE_ROWS):
+// a workgroup takes CB coarse rows, whose members it lists in LDS, forms the
+// members' residuals there (G lanes per row, rows longer than HEAVY by a
+// wavefront) and adds them per coarse row in k_restrict's order.  An
+// aggregate of more than BIG members takes a workgroup of its own, 256
+// members at a time.
+constexpr int CB = 256 / BIG;
+template <class T>
+__device__ __forceinline__ void member_residuals(const CsrArgs<T> &A, const int *list, int cnt, T *res,
+                                                 int *heavy, int *nheavy) {
+    const PlainX<T> x{A.x};
+    if (threadIdx.x == 0) *nheavy = 0;
+    __syncthreads();
+    for (int t = threadIdx.x / G; t < cnt; t += 256 / G) {
+        int i = list[t], z0 = A.rp[i], z1 = A.rp[i + 1];
+        if (z1 - z0 > HEAVY) {
+            if (threadIdx.x % G == 0) heavy[atomicAdd(nheavy, 1)] = t;
+            continue;
+        }
+        T r = A.b[i] - row_sum(A, z0, z1, threadIdx.x % G, x);
+        if (threadIdx.x % G == 0) res[t] = r;
+    }
+    __syncthreads();
+    for (int h = threadIdx.x / 64; h < *nheavy; h += 4) {
+        int i = list[heavy[h]];
+        T r = A.b[i] - row_sum_wave(A, A.rp[i], A.rp[i + 1], threadIdx.x & 63, x);
+        if ((threadIdx.x & 63) == 0) res[heavy[h]] = r;
+    }
+    __syncthreads();
+}
+
+template <class T>
+__global__ __launch_bounds__(256) void k_down_restrict(CsrArgs<T> A, int nc, int nbs, const int *mptr,
+                                                       const int *mem, const int *big, T *bc,
+                                                       const T *l1c, T *xc) {
+    __shared__ int list[256], heavy[256], start[CB + 1], nheavy;
+    __shared__ T res[256];
+    const int tid = threadIdx.x;
+    int I, lane0;
+    T acc = (T)0;
+    if ((int)blockIdx.x < nbs) {
+        int I0 = xcd_block(blockIdx.x, nbs) * CB;
+        // members of row tid / BIG, its place among the workgroup's
+        I = I0 + tid / BIG;
+        int a = I < nc ? mptr[I] : 0, cnt = I < nc ? mptr[I + 1] - a : 0;
+        if (cnt > BIG) cnt = 0;
+        if (tid % BIG == 0) start[tid / BIG] = cnt;
+        __syncthreads();
+        if (tid < 64) {
+            int v = tid < CB ? start[tid] : 0, sum = v;
+            for (int d = 1; d < CB; d <<= 1) {
+                int u = __shfl_up(sum, d, 64);
+                if (tid >= d) sum += u;
+            }
+            if (tid < CB) start[tid + 1] = sum;
+            if (tid == 0) start[0] = 0;
+        }
+        __syncthreads();
+        if (tid % BIG < cnt) list[start[tid / BIG] + tid % BIG] = mem[a + tid % BIG];
+        member_residuals(A, list, start[CB], res, heavy, &nheavy);
+        if (tid >= CB * GR) return;
+        I = I0 + tid / GR;
+        lane0 = tid % GR;
+        int m0 = start[tid / GR], m1 = start[tid / GR + 1];
+        for (int t = m0 + lane0; t < m1; t += 2 * GR) {
+            T rb = t + GR < m1 ? res[t + GR] : (T)0;
+            acc += res[t] + rb;
+        }
+        acc += dpp_move<DPP_XOR1>(acc);
+        if (I >= nc || mptr[I + 1] - mptr[I] > BIG) return;
+    } else {
+        I = big[(int)blockIdx.x - nbs];
+        lane0 = tid;
+        int a = mptr[I], b = mptr[I + 1];
+        for (int t = a; t < b; t += 256) {
+            int cnt = min(256, b - t);
+            if (tid < cnt) list[tid] = mem[t + tid];
+            member_residuals(A, list, cnt, res, heavy, &nheavy);
+            if (tid < cnt && tid < 64) {
+                T v[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) v[u] = tid + 64 * u < cnt ? res[tid + 64 * u] : (T)0;
+                acc += (v[0] + v[1]) + (v[2] + v[3]);
+            }
+            __syncthreads();
+        }
+        if (tid >= 64) return;
         for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
     }
     if (lane0 == 0) {
@@ -1091,23 +1234,37 @@ __global__ void k_up0(Level0<T> A, const T *x, double *xo) {
 // Coarsest solve x = A_c^-1 b with the stored inverse (column-major, so a
 // column read by 64 lanes is contiguous).  A workgroup of CS_WAVES
 // wavefronts covers 64 rows; wavefront w sums its quarter of the columns,
-// then the quarters are added in wavefront order.
+// then the quarters are added in wavefront order.  A few workgroups in all, so
+// bound by load latency: b is staged in LDS and CS_COLS columns are in flight
+// (412 rows: 12.3 us with 8 in flight and up to 7 left over one at a time, 8
+// so).
 constexpr int CS_WAVES = 4;
+constexpr int CS_COLS = 64;
 template <class T>
-__global__ __launch_bounds__(64 * CS_WAVES) void k_coarse_solve(int n, const double *invT,
-                                                                const T *b, const double *f,
-                                                                int fstride, T *x, double *xd) {
+__global__ __launch_bounds__(64 * CS_WAVES, 1) void k_coarse_solve(int n, const double *invT,
+                                                                   const T *b, const double *f,
+                                                                   int fstride, T *x, double *xd) {
     __shared__ double part[CS_WAVES][64];
-    int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    __shared__ double rhs[CS_WAVES][4096 / CS_WAVES + CS_COLS];   // n is at most 4,096
+    int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int i = blockIdx.x * 64 + lane;
     int q = (n + CS_WAVES - 1) / CS_WAVES;
-    int c0 = w * q, c1 = min(n, c0 + q);
+    int c0 = w * q, cnt = min(n, c0 + q) - c0;
     int ii = i < n ? i : n - 1;
-    double s = 0.0;
-#pragma unroll 8
-    for (int c = c0; c < c1; c++) {
-        double bc = f ? f[(long)fstride * c] : (double)b[c];
-        s += invT[(long)c * n + ii] * bc;
+    // the wavefront's part of b, zeros behind it
+    for (int c = lane; c < cnt + CS_COLS; c += 64)
+        rhs[w][c] = c < cnt ? (f ? f[(long)fstride * (c0 + c)] : (double)b[c0 + c]) : 0.0;
+    double s = 0.0, v[CS_COLS];
+    const double *col = invT + (long)c0 * n;
+    for (int c = 0; c < cnt; c += CS_COLS) {
+#pragma unroll
+        for (int u = 0; u < CS_COLS; u++) {
+            v[u] = col[ii];
+            col += c + u + 1 < cnt ? n : 0;
+        }
+        __builtin_amdgcn_sched_barrier(0);    // all loads first
+#pragma unroll
+        for (int u = 0; u < CS_COLS; u++) s += v[u] * rhs[w][c + u];
     }
     part[w][lane] = s;
     __syncthreads();
@@ -1161,18 +1318,7 @@ __global__ __launch_bounds__(BS) void k_kspmv(CsrArgs<T> A, const T *q1, double 
         bool valid = i < A.n;
         int z0 = valid ? A.rp[i] : 0, z1 = valid ? A.rp[i + 1] : 0;
         bool heavy = z1 - z0 > HEAVY;
-        T acc = (T)0;
-        if (!heavy) {
-            for (int z = z0 + lane0; z < z1; z += 2 * G) {
-                int zb = z + G < z1 ? z + G : z;
-                int ca = A.col[z], cb = A.col[zb];
-                T va = A.val[z], vb = A.val[zb];
-                T xa = A.x[ca], xb = A.x[cb];
-                acc += va * xa + (z + G < z1 ? vb * xb : (T)0);
-            }
-        }
-#pragma unroll
-        for (int d = 1; d < G; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        T acc = row_sum(A, z0, heavy ? z0 : z1, lane0, PlainX<T>{A.x});
         if (lane0 == 0 && valid && !heavy) {
             A.xo[i] = acc;
             double q = (double)acc;
@@ -1184,19 +1330,7 @@ __global__ __launch_bounds__(BS) void k_kspmv(CsrArgs<T> A, const T *q1, double 
         int lane = threadIdx.x & 63;
         if (w < A.nheavy) {
             int i = A.heavy[w];
-            int z0 = A.rp[i], z1 = A.rp[i + 1];
-            T acc = (T)0;
-            for (int z = z0 + lane; z < z1; z += 256) {
-                T t[4];
-#pragma unroll
-                for (int u = 0; u < 4; u++) {
-                    int zz = z + 64 * u < z1 ? z + 64 * u : z;
-                    T v = A.val[zz] * A.x[A.col[zz]];
-                    t[u] = z + 64 * u < z1 ? v : (T)0;
-                }
-                acc += (t[0] + t[1]) + (t[2] + t[3]);
-            }
-            for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+            T acc = row_sum_wave(A, A.rp[i], A.rp[i + 1], lane, PlainX<T>{A.x});
             if (lane == 0) {
                 A.xo[i] = acc;
                 double q = (double)acc;
@@ -1381,11 +1515,29 @@ struct Cycle {
             R2P_LAUNCH();
             return 0;
         }
-        // the level's xo holds its residual until the correction is added
-        R2P_TRY(csr_launch<CSR_DOWN>(A, vx(A), vxo(A)));
-        R2P_TRY(restrict_to(c));
-        R2P_TRY(correct(c));
-        return csr_launch<CSR_UP>(A, vx(A), out);
+        AmgLevel &C = P->lv[c + 1];
+        const bool kc = c < P->o.kcycle && c + 1 < nl - 1;
+        const bool smooth = c + 1 < nl - 1;
+        if (A.n <= FUSE_ROWS) {
+            int nbs = r2p_blocks(C.n, CB);
+            k_down_restrict<T><<<nbs + A.nbig, BS, 0, s>>>(
+                csr(A, vx(A), nullptr), C.n, nbs, A.mptr.p, A.mem.p, A.big.p, vb(C),
+                smooth ? l1s(C) : nullptr, smooth ? vx(C) : nullptr);
+            R2P_LAUNCH();
+        } else {
+            // the level's xo holds its residual until the correction is added
+            R2P_TRY(csr_launch<CSR_DOWN>(A, vx(A), vxo(A)));
+            R2P_TRY(restrict_to(c));
+        }
+        if (A.n > FUSE_ROWS || kc) {
+            R2P_TRY(correct(c));
+            return csr_launch<CSR_UP>(A, vx(A), out);
+        }
+        R2P_TRY(coarse(c + 1, vxo(C)));
+        CsrArgs<T> D = csr(A, vx(A), out);
+        k_csr_up<T><<<D.nbs + r2p_blocks(A.nheavy, BS / 64), BS, 0, s>>>(D, A.agg.p, vxo(C));
+        R2P_LAUNCH();
+        return 0;
     }
     // The cycle from level 0 (7-slot stencil) with right-hand side f (stride
     // fstride), result in xp.
