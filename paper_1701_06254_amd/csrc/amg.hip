@@ -228,84 +228,254 @@ __global__ void k_iota(int n, int *a) {
     if (i < n) a[i] = i;
 }
 
-// Member lists (CSR) of the aggregates, ascending within each list: the
-// rows are stably sorted by aggregate, then every list start is marked.
-__global__ void k_member_keys(int n, const int *agg, unsigned *key, unsigned *val) {
+// Member lists (CSR) of the aggregates, ascending within each list: every row
+// takes a slot of its aggregate (in no fixed order), and its place in the list
+// is then the number of smaller members.  Lists are a few rows long, so this
+// costs a few reads per row where a sort by aggregate takes three passes.
+__global__ void k_member_slot(int n, const int *agg, int *cnt, int *slot) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) { key[i] = (unsigned)agg[i]; val[i] = (unsigned)i; }
+    if (i < n) slot[i] = atomicAdd(&cnt[agg[i]], 1);
 }
 
-__global__ void k_member_ptr(int n, int nc, const unsigned *key, int *mptr) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n && (k == 0 || key[k] != key[k - 1])) mptr[key[k]] = k;
-    if (k == 0) mptr[nc] = n;
+__global__ void k_member_fill(int n, const int *agg, const int *mptr, const int *slot, int *list) {
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) list[mptr[agg[i]] + slot[i]] = i;
+}
+
+__global__ void k_member_order(int n, const int *agg, const int *mptr, const int *list, int *mem) {
+    int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    int i = list[t], I = agg[i], a = mptr[I], b = mptr[I + 1], r = a;
+    for (int k = a; k < b; k++) r += list[k] < i;
+    mem[r] = i;
 }
 
 // ------------------------------------------------------------- Galerkin
-// A_c = P^T A P by expand-sort-compress: every stored entry a_ij becomes the
-// term (agg(i), agg(j), a_ij); the terms are stably sorted by coarse column
-// and then by coarse row, so equal (I, J) terms stay in ascending (row,
-// stored column) order and are summed in that order.
-__global__ void k_gal_expand(int n, const int *rp, const int *agg, unsigned *keyI,
-                             const int *col, unsigned *keyJ, unsigned *idx) {
-    int i, g;
-    row_group(n, i, g);
-    if (i >= n) return;
-    unsigned I = (unsigned)agg[i];
-    for (int z = rp[i] + g; z < rp[i + 1]; z += GS) {
-        keyI[z] = I;
-        keyJ[z] = (unsigned)agg[col[z]];
-        idx[z] = (unsigned)z;
+// A_c = P^T A P row by row: the stored entries a_ij of coarse row I's members
+// (ascending fine row, then stored column) are the terms (agg(j), a_ij).  Equal
+// columns are added in that order, and the sums stand in ascending column
+// order.  A row's terms are compared with one another in LDS: the first of
+// equal columns adds them up, its place is the number of smaller columns among
+// the firsts.  Rows have 14 to 26 terms on average, and the pass reads and
+// writes each term once; two stable radix sorts of all terms moved them a
+// dozen times (13.9 million terms: 1.9 ms, 0.5 ms so).
+//
+// A group of GL lanes takes a coarse row of up to GL members and GE terms;
+// longer ones go on a list and take a workgroup each (k_gal_long).
+constexpr int GL = 16;
+constexpr int GE = 64;
+constexpr int NO_COL = 0x7fffffff;
+struct GalArgs {
+    int nc;
+    const int *mptr, *mem, *rp, *col, *agg;
+    const double *val;
+    int *rpc;                    // counting: entries of every coarse row; then their starts
+    int *colc;
+    double *valc;
+    int *list, *nlist;           // long rows; their number, and terms of freaks placed (counting, merging)
+    int *xkey, *xfkey;           // freaks' terms
+    double *xval;
+};
+
+// One of the group's terms per lane and slot, up to SL slots.
+template <bool MERGE, int SL>
+__device__ __forceinline__ void gal_row(const GalArgs &A, int I, int E, int nf, int l, int *key,
+                                        const double *val) {
+    int k[SL], rank[SL];
+    double sum[SL];
+    bool first[SL];
+#pragma unroll
+    for (int s = 0; s < SL; s++) {
+        k[s] = key[l + GL * s];
+        first[s] = l + GL * s < E;
+        sum[s] = 0.0;
+        rank[s] = 0;
+    }
+#pragma unroll 4
+    for (int f = 0; f < nf; f++) {
+        int kf = key[f];
+        double vf = MERGE ? val[f] : 0.0;
+#pragma unroll
+        for (int s = 0; s < SL; s++) {
+            bool eq = kf == k[s];
+            first[s] &= !(eq & (f < l + GL * s));
+            if (MERGE) sum[s] += eq ? vf : 0.0;
+        }
+    }
+    if (!MERGE) {
+        int cnt = 0;
+#pragma unroll
+        for (int s = 0; s < SL; s++)
+            cnt += __popc((unsigned)(__ballot(first[s]) >> (threadIdx.x & 48)) & 0xffffu);
+        if (l == 0 && E >= 0) A.rpc[I] = cnt;
+        return;
+    }
+    // the group's lanes are in one wavefront, whose LDS operations keep order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+    for (int s = 0; s < SL; s++) key[l + GL * s] = first[s] ? k[s] : NO_COL;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll 4
+    for (int f = 0; f < nf; f++) {
+        int kf = key[f];
+#pragma unroll
+        for (int s = 0; s < SL; s++) rank[s] += kf < k[s];
+    }
+    int base = E > 0 ? A.rpc[I] : 0;
+#pragma unroll
+    for (int s = 0; s < SL; s++)
+        if (first[s]) {
+            A.colc[base + rank[s]] = k[s];
+            A.valc[base + rank[s]] = sum[s];
+        }
+}
+
+template <bool MERGE>
+__global__ __launch_bounds__(256) void k_gal_rows(GalArgs A) {
+    __shared__ int key[256 / GL][GE], st[256 / GL][GL + 1], mz[256 / GL][GL];
+    __shared__ double val[MERGE ? 256 / GL : 1][MERGE ? GE : 1];
+    const int g = threadIdx.x / GL, l = threadIdx.x % GL;
+    const int I = xcd_block(blockIdx.x, gridDim.x) * (256 / GL) + g;
+    if (!MERGE && blockIdx.x == 0 && threadIdx.x == 0) A.rpc[A.nc] = 0;
+    int a = I < A.nc ? A.mptr[I] : 0, m = I < A.nc ? A.mptr[I + 1] - a : 0;
+    int z0 = 0, len = 0;
+    if (m <= GL && l < m) {
+        int i = A.mem[a + l];
+        z0 = A.rp[i];
+        len = A.rp[i + 1] - z0;
+    }
+    int inc = len;
+    for (int d = 1; d < GL; d <<= 1) {
+        int u = __shfl_up(inc, d, GL);
+        if (l >= d) inc += u;
+    }
+    st[g][l + 1] = inc;
+    if (l == 0) st[g][0] = 0;
+    mz[g][l] = z0;
+    int E = __shfl(inc, GL - 1, GL);          // -1: nothing to do here
+    if (m > GL || E > GE) {
+        if (!MERGE && l == 0) A.list[atomicAdd(&A.nlist[0], 1)] = I;
+        E = -1;
+    }
+    if (I >= A.nc) E = -1;
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < GE / GL; s++) {
+        int e = l + GL * s, k = 0;
+        if (e < E) {
+            while (e >= st[g][k + 1]) k++;
+            int z = mz[g][k] + e - st[g][k];
+            key[g][e] = A.agg[A.col[z]];
+            if (MERGE) val[g][e] = A.val[z];
+        } else {
+            key[g][e] = NO_COL;
+            if (MERGE) val[g][e] = 0.0;
+        }
+    }
+    __syncthreads();
+    int mx = max(E, __shfl_xor(E, 16, 64));
+    mx = __builtin_amdgcn_readfirstlane(max(mx, __shfl_xor(mx, 32, 64)));
+    const int nf = (mx + 3) & ~3;
+    if (mx <= GL) gal_row<MERGE, 1>(A, I, E, nf, l, key[g], val[MERGE ? g : 0]);
+    else if (mx <= 2 * GL) gal_row<MERGE, 2>(A, I, E, nf, l, key[g], val[MERGE ? g : 0]);
+    else gal_row<MERGE, GE / GL>(A, I, E, nf, l, key[g], val[MERGE ? g : 0]);
+}
+
+// A long row's terms (E of them, from m members) compared with one another by
+// a workgroup; key, fkey and val hold them.
+template <bool MERGE, class KEY, class VAL>
+__device__ __forceinline__ void gal_long_row(const GalArgs &A, int I, int a, int m, int E, KEY key,
+                                             KEY fkey, VAL val, int (*mem)[256], int *part) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // the terms, 256 members at a time: each member's first term, stored entry
+    // and length, then 16 lanes copy a member's
+    int off = 0;
+    for (int t0 = 0; t0 < m; t0 += 256) {
+        int t = t0 + tid, i = t < m ? A.mem[a + t] : 0;
+        int z0 = A.rp[i], len = t < m ? A.rp[i + 1] - z0 : 0, inc = len;
+        for (int d = 1; d < 64; d <<= 1) {
+            int u = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += u;
+        }
+        if (lane == 63) part[wv] = inc;
+        __syncthreads();
+        int st = off + inc - len;
+        for (int w = 0; w < 4; w++) {
+            st += w < wv ? part[w] : 0;
+            off += part[w];
+        }
+        mem[0][tid] = st;
+        mem[1][tid] = z0;
+        mem[2][tid] = len;
+        __syncthreads();
+        for (int q = tid / 16; q < min(m - t0, 256); q += 16)
+            for (int k = tid % 16; k < mem[2][q]; k += 16) {
+                int z = mem[1][q] + k;
+                key[mem[0][q] + k] = A.agg[A.col[z]];
+                if (MERGE) val[mem[0][q] + k] = A.val[z];
+            }
+        __syncthreads();
+    }
+    int cnt = 0;
+    for (int e = tid; e < E; e += 256) {
+        const int k = key[e];
+        unsigned first = 1;
+#pragma unroll 8
+        for (int f = 0; f < e; f++) first &= key[f] != k;
+        cnt += first;
+        if (MERGE) fkey[e] = first ? k : NO_COL;
+    }
+    if (!MERGE) {
+        for (int d = 32; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
+        if (lane == 0) part[wv] = cnt;
+        __syncthreads();
+        if (tid == 0) A.rpc[I] = part[0] + part[1] + part[2] + part[3];
+        return;
+    }
+    __syncthreads();
+    const int base = A.rpc[I];
+    for (int e = tid; e < E; e += 256) {
+        const int k = fkey[e];
+        if (k == NO_COL) continue;
+        int rank = 0;
+        double sum = 0.0;
+#pragma unroll 8
+        for (int f = 0; f < E; f++) {
+            rank += fkey[f] < k;
+            sum += key[f] == k ? val[f] : 0.0;
+        }
+        A.colc[base + rank] = k;
+        A.valc[base + rank] = sum;
     }
 }
 
-__global__ void k_gather_u(int m, const unsigned *idx, const unsigned *src, unsigned *dst) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < m) dst[k] = src[idx[k]];
-}
-
-// keyI, keyJ: the terms' coarse rows and columns in sorted order.
-__global__ void k_gal_flags(int m, const unsigned *keyI, const unsigned *keyJ, int *flag) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= m) return;
-    bool f = k == 0;
-    if (!f) f = keyI[k] != keyI[k - 1] || keyJ[k] != keyJ[k - 1];
-    flag[k] = f;
-}
-
-// The first term of every run of equal (I, J) records where its run starts;
-// the run of output entry u is then [start[u], start[u + 1]).
-__global__ void k_gal_runs(int m, int nc, const unsigned *keyI, const unsigned *keyJ,
-                           const int *uidx, int *start, int *rpc, int nnzc) {
-    int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k == 0) { rpc[nc] = nnzc; start[nnzc] = m; }
-    if (k >= m) return;
-    bool first = k == 0 || keyI[k] != keyI[k - 1] || keyJ[k] != keyJ[k - 1];
-    if (!first) return;
-    start[uidx[k]] = k;
-    if (k == 0 || keyI[k - 1] != keyI[k]) rpc[keyI[k]] = uidx[k];
-}
-
-// One thread per coarse entry: its terms summed in sorted order (ascending
-// fine row, then stored column), four terms' loads in flight at a time.
-__global__ void k_gal_sum(int nnzc, const int *start, const unsigned *idx, const unsigned *keyJ,
-                          const double *val, int *colc, double *valc) {
-    int u = blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= nnzc) return;
-    int a = start[u], b = start[u + 1];
-    double s = 0.0;
-    int t = a;
-    for (; t + 4 <= b; t += 4) {
-        unsigned i0 = idx[t], i1 = idx[t + 1], i2 = idx[t + 2], i3 = idx[t + 3];
-        double v0 = val[i0], v1 = val[i1], v2 = val[i2], v3 = val[i3];
-        s += v0;
-        s += v1;
-        s += v2;
-        s += v3;
+// The rows on the list, a workgroup each.  Up to GCH terms (all but freaks: a
+// few hundred at most at 8 million cells) stay in LDS, more take their part of
+// arrays as long as all terms.
+constexpr int GCH = 1024;
+template <bool MERGE>
+__global__ __launch_bounds__(256) void k_gal_long(GalArgs A) {
+    __shared__ int key[GCH], fkey[MERGE ? GCH : 1], mem[3][256], part[4], base;
+    __shared__ double val[MERGE ? GCH : 1];
+    const int tid = threadIdx.x, nl = A.nlist[0];
+    for (int q = blockIdx.x; q < nl; q += gridDim.x) {
+        const int I = A.list[q], a = A.mptr[I], m = A.mptr[I + 1] - a;
+        int E = 0;
+        for (int t = tid; t < m; t += 256) E += A.rp[A.mem[a + t] + 1] - A.rp[A.mem[a + t]];
+        for (int d = 32; d > 0; d >>= 1) E += __shfl_xor(E, d, 64);
+        if ((tid & 63) == 0) part[tid >> 6] = E;
+        __syncthreads();
+        E = part[0] + part[1] + part[2] + part[3];
+        __syncthreads();
+        if (E <= GCH) {
+            gal_long_row<MERGE>(A, I, a, m, E, key, fkey, val, mem, part);
+        } else {
+            if (tid == 0) base = atomicAdd(&A.nlist[MERGE ? 2 : 1], E);
+            __syncthreads();
+            gal_long_row<MERGE>(A, I, a, m, E, A.xkey + base, A.xfkey + base, A.xval + base, mem, part);
+        }
+        __syncthreads();
     }
-    for (; t < b; t++) s += val[idx[t]];
-    colc[u] = (int)keyJ[a];
-    valc[u] = s;
 }
 
 __global__ void k_l1(int n, const int *rp, const double *val, double *l1) {
@@ -672,23 +842,22 @@ static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
 // --------------------------------------------------------------- set-up
 // Everything runs in order on one stream; the host waits only where it
 // needs a count (the scans that return totals) and for the final status.
-// Member lists (CSR, ascending) of the nc aggregates of agg[0..n).
+// Member lists (CSR, ascending) of the nc aggregates of agg[0..n); uses two
+// scratch arrays of n.
 static int build_members(r2p_cpr *P, int n, const int *agg, int nc, DBuf<int> &mptr,
-                         DBuf<int> &mem, hipStream_t s) {
-    SetupWork &W = P->aws;
-    DBuf<unsigned> &key = W.u[0], &kt = W.u[1], &vt = W.u[2];
-    DBuf<int> &hist = W.i[0];
+                         DBuf<int> &mem, DBuf<int> &slot, DBuf<int> &list, hipStream_t s) {
     R2P_TRY(mptr.ensure(nc + 1));
     R2P_TRY(mem.ensure(n));
-    R2P_TRY(key.ensure(n));
-    R2P_TRY(kt.ensure(n));
-    R2P_TRY(vt.ensure(n));
-    unsigned *val = (unsigned *)mem.p;
-    k_member_keys<<<r2p_blocks(n, BS), BS, 0, s>>>(n, agg, key.p, val);
+    R2P_TRY(slot.ensure(n));
+    R2P_TRY(list.ensure(n));
+    int nb = r2p_blocks(n, BS);
+    R2P_HIP(hipMemsetAsync(mptr.p, 0, sizeof(int) * (size_t)(nc + 1), s));
+    k_member_slot<<<nb, BS, 0, s>>>(n, agg, mptr.p, slot.p);
     R2P_LAUNCH();
-    R2P_TRY(r2p_sort_pairs(key.p, val, kt.p, vt.p, n, r2p_bits_for(nc), hist, P->aiscratch,
-                           P->apin, s));
-    k_member_ptr<<<r2p_blocks(n, BS), BS, 0, s>>>(n, nc, key.p, mptr.p);
+    R2P_TRY(r2p_scan_int(mptr.p, mptr.p, nc + 1, nullptr, P->aiscratch, P->apin, s));
+    k_member_fill<<<nb, BS, 0, s>>>(n, agg, mptr.p, slot.p, list.p);
+    R2P_LAUNCH();
+    k_member_order<<<nb, BS, 0, s>>>(n, agg, mptr.p, list.p, mem.p);
     R2P_LAUNCH();
     return 0;
 }
@@ -697,44 +866,36 @@ static int galerkin(r2p_cpr *P, int n, int nnz, const int *rp, const int *col, c
                     const int *agg, int nc, DBuf<int> &rpc, DBuf<int> &colc, DBuf<double> &valc,
                     int *nnzc, hipStream_t s) {
     SetupWork &W = P->aws;
-    DBuf<unsigned> &keyI = W.u[0], &keyJz = W.u[1], &keyIs = W.u[2], &idx = W.u[3], &kt = W.u[4],
-                   &vt = W.u[5];
-    DBuf<int> &flag = W.i[0], &hist = W.i[1];
-    R2P_TRY(keyI.ensure(nnz));
-    R2P_TRY(keyJz.ensure(nnz));
-    R2P_TRY(keyIs.ensure(nnz));
-    R2P_TRY(idx.ensure(nnz));
-    R2P_TRY(kt.ensure(nnz));
-    R2P_TRY(vt.ensure(nnz));
-    R2P_TRY(flag.ensure(nnz + 1));
-    k_gal_expand<<<r2p_blocks(n, BS / GS), BS, 0, s>>>(n, rp, agg, keyI.p, col, keyJz.p, idx.p);
-    R2P_LAUNCH();
-    int bits = r2p_bits_for(nc);
-    // stable by coarse column, then stable by coarse row
-    R2P_HIP(hipMemcpyAsync(kt.p, keyJz.p, sizeof(unsigned) * nnz, hipMemcpyDeviceToDevice, s));
-    R2P_HIP(hipMemcpyAsync(keyIs.p, kt.p, sizeof(unsigned) * nnz, hipMemcpyDeviceToDevice, s));
-    R2P_TRY(r2p_sort_pairs(keyIs.p, idx.p, kt.p, vt.p, nnz, bits, hist, P->aiscratch, P->apin, s));
-    k_gather_u<<<r2p_blocks(nnz, BS), BS, 0, s>>>(nnz, idx.p, keyI.p, keyIs.p);
-    R2P_LAUNCH();
-    R2P_TRY(r2p_sort_pairs(keyIs.p, idx.p, kt.p, vt.p, nnz, bits, hist, P->aiscratch, P->apin, s));
-    // the coarse columns in sorted order, gathered once (kt is free again)
-    k_gather_u<<<r2p_blocks(nnz, BS), BS, 0, s>>>(nnz, idx.p, keyJz.p, kt.p);
-    R2P_LAUNCH();
-    k_gal_flags<<<r2p_blocks(nnz, BS), BS, 0, s>>>(nnz, keyIs.p, kt.p, flag.p);
-    R2P_LAUNCH();
-    R2P_HIP(hipMemsetAsync(flag.p + nnz, 0, sizeof(int), s));
-    int nnz_c = 0;
-    R2P_TRY(r2p_scan_int(flag.p, flag.p, nnz + 1, &nnz_c, P->aiscratch, P->apin, s));
+    DBuf<int> &mptr = W.i[0], &mem = W.i[1], &slot = W.i[2], &list = W.i[3];
+    DBuf<unsigned> &xkey = W.u[0], &xfkey = W.u[1], &longs = W.u[2], &nlong = W.u[3];
+    DBuf<double> &xval = W.d[1];              // the pass's weights, no longer needed
+    R2P_TRY(build_members(P, n, agg, nc, mptr, mem, slot, list, s));
+    R2P_TRY(xkey.ensure(nnz));
+    R2P_TRY(xfkey.ensure(nnz));
+    R2P_TRY(xval.ensure(nnz));
+    R2P_TRY(longs.ensure(nc));
+    R2P_TRY(nlong.ensure(3));
     R2P_TRY(rpc.ensure(nc + 1));
+    R2P_HIP(hipMemsetAsync(nlong.p, 0, 3 * sizeof(int), s));
+    GalArgs A;
+    A.nc = nc;
+    A.mptr = mptr.p; A.mem = mem.p; A.rp = rp; A.col = col; A.agg = agg; A.val = val;
+    A.rpc = rpc.p; A.colc = nullptr; A.valc = nullptr;
+    A.list = (int *)longs.p; A.nlist = (int *)nlong.p;
+    A.xkey = (int *)xkey.p; A.xfkey = (int *)xfkey.p; A.xval = xval.p;
+    const int nb = r2p_blocks(nc, 256 / GL), nl = std::min(nc, 1024);
+    k_gal_rows<false><<<nb, 256, 0, s>>>(A);
+    R2P_LAUNCH();
+    k_gal_long<false><<<nl, 256, 0, s>>>(A);
+    R2P_LAUNCH();
+    int nnz_c = 0;
+    R2P_TRY(r2p_scan_int(rpc.p, rpc.p, nc + 1, &nnz_c, P->aiscratch, P->apin, s));
     R2P_TRY(colc.ensure(nnz_c));
     R2P_TRY(valc.ensure(nnz_c));
-    DBuf<int> &start = W.i[2];
-    R2P_TRY(start.ensure(nnz_c + 1));
-    k_gal_runs<<<r2p_blocks(nnz, BS), BS, 0, s>>>(nnz, nc, keyIs.p, kt.p, flag.p, start.p, rpc.p,
-                                                 nnz_c);
+    A.colc = colc.p; A.valc = valc.p;
+    k_gal_rows<true><<<nb, 256, 0, s>>>(A);
     R2P_LAUNCH();
-    k_gal_sum<<<r2p_blocks(nnz_c, BS), BS, 0, s>>>(nnz_c, start.p, idx.p, kt.p, val, colc.p,
-                                                   valc.p);
+    k_gal_long<true><<<nl, 256, 0, s>>>(A);
     R2P_LAUNCH();
     *nnzc = nnz_c;
     return 0;
@@ -856,7 +1017,7 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
         if (nc >= A.n) break;   // no coarsening progress
         C.n = nc;
         C.nnz = nnzc;
-        R2P_TRY(build_members(P, A.n, A.agg.p, nc, A.mptr, A.mem, s));
+        R2P_TRY(build_members(P, A.n, A.agg.p, nc, A.mptr, A.mem, P->aws.i[0], P->aws.i[1], s));
         R2P_TRY(long_rows(P, nc, A.mptr.p, BIG, A.big, &A.nbig, s));
         R2P_TRY(long_rows(P, nc, C.rp.p, HEAVY, C.heavy, &C.nheavy, s));
         l++;
