@@ -135,7 +135,9 @@ __global__ void k_weights(int n, const int *rp, const int *col, const double *va
         w[z] = wz;
         if (wz > mx) mx = wz;
     }
-    for (int d = 1; d < GS; d <<= 1) mx = fmax(mx, __shfl_xor(mx, d, 64));
+    mx = fmax(mx, dpp_move<DPP_XOR1>(mx));
+    mx = fmax(mx, dpp_move<DPP_XOR2>(mx));
+    mx = fmax(mx, dpp_move<DPP_HALF_MIRROR>(mx));
     if (g == 0) {
         M[i] = mx;
         match[i] = -1;
@@ -169,11 +171,9 @@ __device__ __forceinline__ void strongest(int n, const int *rp, const int *col, 
             if (s > best) { best = s; best_j = j; }
         }
     }
-    for (int d = 1; d < GS; d <<= 1) {
-        double s2 = __shfl_xor(best, d, 64);
-        int j2 = __shfl_xor(best_j, d, 64);
-        take_stronger(best, best_j, s2, j2);
-    }
+    take_stronger(best, best_j, dpp_move<DPP_XOR1>(best), dpp_move<DPP_XOR1>(best_j));
+    take_stronger(best, best_j, dpp_move<DPP_XOR2>(best), dpp_move<DPP_XOR2>(best_j));
+    take_stronger(best, best_j, dpp_move<DPP_HALF_MIRROR>(best), dpp_move<DPP_HALF_MIRROR>(best_j));
     if (g == 0) out[i] = best_j;
 }
 

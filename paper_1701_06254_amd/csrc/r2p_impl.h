@@ -147,16 +147,18 @@ constexpr int RAS_MAIN = 4;
 constexpr int RAS_MENT = RAS_MAIN * RAS_ROWS;      // main entries of a slice
 // Where the entries of the row at position p are.
 struct RasRow {
-    long b, x;
-    // xb[sl]: the slice's overflow start, less the pairs before it
+    long b;                   // its first main entry
+    const int *x;             // &xb[sl]: the slice's overflow start, less the pairs before it
+    int r2;                   // its first lane
     __host__ __device__ RasRow(const int *xb, int p) {
-        int sl = p / RAS_ROWS, r = p % RAS_ROWS;
-        b = (long)sl * RAS_MENT + 2 * r;
-        x = (long)xb[sl] + 2 * r;
+        int sl = p / RAS_ROWS;
+        r2 = 2 * (p % RAS_ROWS);
+        b = (long)sl * RAS_MENT + r2;
+        x = xb + sl;
     }
     __host__ __device__ long operator()(int e) const {
-        // b; the next position's lanes, from their first pair; the overflow
-        long o = e < RAS_MAIN ? b : (e < 2 * RAS_MAIN ? b + 2 - RAS_MENT : x);
+        // its lanes; the next position's lanes, from their first pair; the overflow
+        long o = e < RAS_MAIN ? b : (e < 2 * RAS_MAIN ? b + 2 - RAS_MENT : (long)*x + r2);
         return o + (long)(e >> 1) * RAS_SLICE + (e & 1);
     }
 };
@@ -199,6 +201,7 @@ struct RasDyn {
     DBuf<int> suboff;                     // ns+1: first local row of every subdomain
     DBuf<int> indeg, queue;               // mtot: level computation (set-up only)
     DBuf<unsigned char> apred;            // nadj: coupling e of row l is a predecessor of l
+    DBuf<int4> succ4;                     // mtot: up to four successors of every row (set-up only)
     DBuf<int> nlnat, nunat;               // mtot: predecessor / successor counts (natural)
     DBuf<int> pos;                        // mtot: position of local row
     DBuf<int> perm;                       // npos: local row (natural) at position, -1 unused
@@ -216,6 +219,7 @@ struct RasDyn {
     DBuf<int> lsw, usw;                   // the same for the sweep, with each column's source of y
     DBuf<int> lsrc, usrc;                 // entries: block source (set-up only)
     DBuf<int> dsrc_pos;                   // npos: diagonal block source per position
+    DBuf<double> tval;                    // L entries (p, q): A_qp, laid out as the factors (set-up only)
     DBuf<int> ldiag;                      // L entries: entry of U_qp in row q (set-up only)
     DBuf<int> xptr;                       // npos+1: extra ILU(0) matches per position
     DBuf<int4> xl;                        // extra matches (set-up only)

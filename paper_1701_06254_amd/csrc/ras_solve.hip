@@ -84,16 +84,27 @@ __device__ __forceinline__ bool before(int h, int g, int n, int order, const dou
 // in-degree above 255, the in-degrees live in LDS as packed bytes (a 32-bit
 // LDS atomic subtracts 1 from one byte; a counter >= 1 never borrows);
 // otherwise in global memory.
+//
+// A round is a chain: the row from the queue, its successors, their counters,
+// the queue, a barrier.  The queue's first LEV_Q rows sit in LDS, and up to
+// four successors come as one 16-byte word (SUCC_MORE in it: the row has more,
+// see its couplings).  16 subdomains of 135,000 rows in 487 levels: 1.75 ms
+// beside the AMG set-up; 4.2 to 5.1 with the couplings looked up through aptr,
+// adj and apred and the queue in memory; 2.07 with the words of the rows just
+// counted down requested ahead.
 constexpr int LEV_LDS_WORDS = 38912;              // 152 KiB of packed counters
 constexpr int LEV_LDS_ROWS = 4 * LEV_LDS_WORDS;
+constexpr int LEV_Q = 1008;
+constexpr int SUCC_MORE = -2;
 __global__ __launch_bounds__(WG) void k_levels(const int *suboff, const int *aptr, const int *adj,
-                                               const unsigned char *apred, const int *npred,
-                                               int *indeg, int *queue, int *lev, int *nlev) {
+                                               const unsigned char *apred, const int4 *succ4,
+                                               const int *npred, int *indeg, int *queue, int *lev,
+                                               int *nlev) {
     __shared__ unsigned cnt[LEV_LDS_WORDS];
-    __shared__ int tail, maxd;
+    __shared__ int lq[2][LEV_Q], tail[3], maxd;
     int sub = blockIdx.x;
     int a = suboff[sub], b = suboff[sub + 1];
-    if (threadIdx.x == 0) { tail = a; maxd = 0; }
+    if (threadIdx.x == 0) { tail[0] = tail[1] = tail[2] = 0; maxd = 0; }
     __syncthreads();
     int md = 0;
     for (int l = a + (int)threadIdx.x; l < b; l += WG) md = max(md, npred[l]);
@@ -110,81 +121,92 @@ __global__ __launch_bounds__(WG) void k_levels(const int *suboff, const int *apt
             cnt[w] = v;
         }
     }
+    // the rows of round t are entries 0 .. tail[t mod 3] of its queue: in
+    // lq[t & 1], past LEV_Q in queue[] behind those of the rounds before
+    int qs = a;
+    auto push = [&](int t, int base, int h) {
+        int k = atomicAdd(&tail[t % 3], 1);
+        if (k < LEV_Q) lq[t & 1][k] = h;
+        else queue[base + k] = h;
+    };
     for (int l = a + (int)threadIdx.x; l < b; l += WG) {
         int d = npred[l];
         if (!in_lds) indeg[l] = d;
-        if (d == 0) queue[atomicAdd(&tail, 1)] = l;
+        if (d == 0) push(0, qs, l);
     }
     __syncthreads();
-    int qs = a, qe = tail, t = 0;
-    __syncthreads();
-    while (qs < qe) {
-        for (int q = qs + (int)threadIdx.x; q < qe; q += WG) {
-            int l = queue[q];
+    auto count_down = [&](int h) {           // true for the last predecessor
+        if (!in_lds) return atomicSub(&indeg[h], 1) == 1;
+        int r = h - a, sh = 8 * (r & 3);
+        return ((atomicSub(&cnt[r >> 2], 1u << sh) >> sh) & 255u) == 1u;
+    };
+    int t = 0;
+    for (int n = tail[0]; n > 0;) {
+        if (threadIdx.x == 0) tail[(t + 2) % 3] = 0;
+        for (int q = threadIdx.x; q < n; q += WG) {
+            int l = q < LEV_Q ? lq[t & 1][q] : queue[qs + q];
             lev[l] = t;
-            int e0 = aptr[l], e1 = aptr[l + 1];
-            // the first AE couplings' loads and decrements are in flight
-            // together; a longer row does the rest in turn
-            constexpr int AE = 8;
-            int hh[AE];
-            bool succ[AE];
-#pragma unroll
-            for (int k = 0; k < AE; k++) {
-                bool in = e0 + k < e1;
-                hh[k] = in ? adj[e0 + k] : l;
-                succ[k] = in && !apred[e0 + k];
+            int4 s = succ4[l];
+            if (s.x == SUCC_MORE) {
+                for (int e = aptr[l]; e < aptr[l + 1]; e++)
+                    if (!apred[e] && count_down(adj[e])) push(t + 1, qs + n, adj[e]);
+                continue;
             }
-            int last[AE];
+            int h[4] = {s.x, s.y, s.z, s.w};
+            bool last[4];
+            if (in_lds) {
+                unsigned old[4];
 #pragma unroll
-            for (int k = 0; k < AE; k++) {
-                last[k] = 0;
-                if (succ[k]) {
-                    if (in_lds) {
-                        int r = hh[k] - a, sh = 8 * (r & 3);
-                        last[k] = ((atomicSub(&cnt[r >> 2], 1u << sh) >> sh) & 255u) == 1u;
-                    } else {
-                        last[k] = atomicSub(&indeg[hh[k]], 1) == 1;
-                    }
+                for (int k = 0; k < 4; k++) {
+                    // a missing successor: nothing off the row's own counter
+                    int r = (h[k] >= 0 ? h[k] : l) - a;
+                    old[k] = atomicSub(&cnt[r >> 2], h[k] >= 0 ? 1u << (8 * (r & 3)) : 0u);
                 }
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+                    last[k] = h[k] >= 0 && ((old[k] >> (8 * ((h[k] - a) & 3))) & 255u) == 1u;
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; k++) last[k] = h[k] >= 0 && count_down(h[k]);
             }
 #pragma unroll
-            for (int k = 0; k < AE; k++)
-                if (last[k]) queue[atomicAdd(&tail, 1)] = hh[k];
-            for (int e = e0 + AE; e < e1; e++) {
-                if (apred[e]) continue;
-                int h = adj[e];
-                bool done;
-                if (in_lds) {
-                    int r = h - a, sh = 8 * (r & 3);
-                    done = ((atomicSub(&cnt[r >> 2], 1u << sh) >> sh) & 255u) == 1u;
-                } else {
-                    done = atomicSub(&indeg[h], 1) == 1;
-                }
-                if (done) queue[atomicAdd(&tail, 1)] = h;
-            }
+            for (int k = 0; k < 4; k++)
+                if (last[k]) push(t + 1, qs + n, h[k]);
         }
         __syncthreads();
-        qs = qe;
-        qe = tail;
+        qs += n;
         t++;
-        __syncthreads();
+        n = tail[t % 3];
     }
     if (threadIdx.x == 0) nlev[sub] = t;
 }
 
+// Predecessors and successors of every row, the direction of its couplings,
+// and its successors as one word (see k_levels).
 __global__ void k_pred_count(int mtot, int n, int order, const double *phi, const int *glob_nat,
                              const int *aptr, const int *adj, unsigned char *apred, int *nl,
-                             int *nu) {
+                             int *nu, int4 *succ4) {
     int l = blockIdx.x * blockDim.x + threadIdx.x;
     if (l >= mtot) return;
-    int g = glob_nat[l], a = 0;
+    int g = glob_nat[l], a = 0, c = 0;
+    int4 s = make_int4(-1, -1, -1, -1);
     for (int e = aptr[l]; e < aptr[l + 1]; e++) {
-        bool p = before(glob_nat[adj[e]], g, n, order, phi);
+        int h = adj[e];
+        bool p = before(glob_nat[h], g, n, order, phi);
         apred[e] = p;
         a += p;
+        if (!p) {
+            s.x = c == 0 ? h : s.x;
+            s.y = c == 1 ? h : s.y;
+            s.z = c == 2 ? h : s.z;
+            s.w = c == 3 ? h : s.w;
+            c++;
+        }
     }
+    if (c > 4) s.x = SUCC_MORE;
     nl[l] = a;
-    nu[l] = aptr[l + 1] - aptr[l] - a;
+    nu[l] = c;
+    succ4[l] = s;
 }
 
 // A row that takes two positions.
@@ -410,14 +432,16 @@ __global__ void k_fill_entries(int npos, int n, int order, const double *phi, co
 // loop, with the same expressions, so the factors are the same.
 struct FactArgs {
     BlkSrc B;
-    int npos;
+    int npos, n, nx, nxy;
+    const int *cell_perf;
     const int *lbase, *nlev, *soff;
     const int *xlb, *xub, *glob;
     const int *nl, *nu, *dsrc, *lcol, *ucol, *lsrc, *usrc;
-    int *ldiag;                  // per L entry: entry index of U_qp in row q
+    int *ldiag;                  // per L entry: entry of U_qp in row q, or -2: it stays A_qp, see tval
     int *xptr;                   // npos+1: first extra match of every position
     int4 *xl;                    // extra matches: (e, e2, entry index in row q's U, 0)
     double *lval, *uval, *dinv;
+    double *tval;                // per L entry (p, q): A_qp
     int *status;
 };
 
@@ -432,6 +456,10 @@ __device__ __forceinline__ void st_blk(double *arr, long k, const double *v) {
     *(double2 *)&arr[ras_val(k, 1)] = make_double2(v[2], v[3]);
 }
 
+// Every row's blocks.  U entries change only by extra matches, which wells and
+// perforated cells have: for another row q, U_qp of an L entry (p, q) is A_qp
+// for good, and is put beside A_pq.  The factorisation then reads it with the
+// row's own data, where following ldiag costs two lines of row q.
 __global__ void k_bilu_gather(FactArgs A) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= A.npos || A.glob[p] < 0) return;
@@ -439,8 +467,17 @@ __global__ void k_bilu_gather(FactArgs A) {
     const RasRow rl(A.xlb, p), ru(A.xub, p);
     double v[4];
     for (int e = 0; e < nlp; e++) {
-        load_block(A.B, A.lsrc[rl(e)], v);
-        st_blk(A.lval, rl(e), v);
+        const long k = rl(e);
+        const int src = A.lsrc[k];
+        load_block(A.B, src, v);
+        st_blk(A.lval, k, v);
+        if (src < 0) continue;
+        const int sl = src / A.n;                 // 1 .. 6: a cell's neighbour
+        const int q = src - sl * A.n + slot_offset(sl, A.nx, A.nxy);
+        if (A.cell_perf[q] >= 0) continue;
+        load_block(A.B, ((sl - 1) ^ 1) * A.n + A.n + q, v);
+        st_blk(A.tval, k, v);
+        A.ldiag[k] = -2;
     }
     for (int e = 0; e < nup; e++) {
         load_block(A.B, A.usrc[ru(e)], v);
@@ -449,103 +486,77 @@ __global__ void k_bilu_gather(FactArgs A) {
     load_block(A.B, A.dsrc[p], &A.dinv[4 * (long)p]);
 }
 
-// Pass 0 counts the extra matches of every position and records the
-// diagonal match of every L entry; pass 1 writes the extra matches.
-__device__ __forceinline__ void bilu_sym_long(const FactArgs &A, int p, int nlp, int nup,
-                                              const RasRow &rl, const RasRow &ru, int pass) {
-    int cnt = 0, out = pass ? A.xptr[p] : 0;
-    for (int e = 0; e < nlp; e++) {
-        long k = rl(e);
-        int q = A.lcol[k];
-        const RasRow rq(A.xub, q);
-        int nuq = A.nu[q];
-        for (int e2 = e + 1; e2 <= nlp + nup; e2++) {
-            int cj = e2 < nlp ? A.lcol[rl(e2)] : (e2 == nlp ? p : A.ucol[ru(e2 - nlp - 1)]);
-            for (int y = 0; y < nuq; y++) {
-                long ky = rq(y);
-                if (A.ucol[ky] != cj) continue;
-                if (e2 == nlp) {
-                    if (pass == 0) A.ldiag[k] = (int)ky;
-                } else {
-                    if (pass) A.xl[out + cnt] = make_int4(e, e2, (int)ky, 0);
-                    cnt++;
-                }
-                break;
-            }
-        }
-    }
-    if (pass == 0) A.xptr[p] = cnt;
-}
-
-// Rows whose own entries and whose predecessors' U parts each fit in SE
-// slots (every cell row) hold them in registers: the predecessors' U column
-// lists are all requested before the matching starts, and the matches come
-// out in the same order (by L entry, then by later entry) as the general
-// loop's.
-constexpr int SE = 8;
-
-__global__ void k_bilu_sym(FactArgs A, int pass) {
+// Where U_qp sits in row q, for the L entries (p, q) that need it, and the matches of other
+// later entries.  Those need a triangle p - q - j, so p is a well or a
+// perforated cell (the 7-point grid has none): such positions go on a list
+// for k_bilu_sym_well.
+__global__ void k_bilu_sym(FactArgs A, int *list, int *nlist) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= A.npos) return;
-    if (A.glob[p] < 0) {
-        if (pass == 0) A.xptr[p] = 0;
+    const int g = A.glob[p];
+    if (g >= 0 && (g >= A.n || A.cell_perf[g] >= 0)) {
+        list[atomicAdd(nlist, 1)] = p;
         return;
     }
-    int nlp = A.nl[p], nup = A.nu[p];
-    const RasRow rl(A.xlb, p), ru(A.xub, p);
-    if (nlp + nup > SE) {
-        bilu_sym_long(A, p, nlp, nup, rl, ru, pass);
-        return;
+    A.xptr[p] = 0;
+    if (g < 0) return;
+    const int nlp = A.nl[p];
+    const RasRow rl(A.xlb, p);
+    for (int e = 0; e < nlp; e++) {
+        if (A.ldiag[rl(e)] == -2) continue;
+        int qe = A.lcol[rl(e)];
+        const RasRow rq(A.xub, qe);
+        for (int yy = 0; yy < A.nu[qe]; yy++)
+            if (A.ucol[rq(yy)] == p) A.ldiag[rl(e)] = (int)rq(yy);
     }
-    // the row's entries in order: L columns, p itself, U columns
-    int c[SE + 1];
-#pragma unroll
-    for (int k = 0; k <= SE; k++) {
-        c[k] = -1;
-        if (k < nlp) c[k] = A.lcol[rl(k)];
-        else if (k == nlp) c[k] = p;
-        else if (k <= nlp + nup) c[k] = A.ucol[ru(k - nlp - 1)];
-    }
-    int nuq[SE];
-#pragma unroll
-    for (int e = 0; e < SE; e++) nuq[e] = e < nlp ? A.nu[c[e]] : 0;
-    bool fits = true;
-#pragma unroll
-    for (int e = 0; e < SE; e++) fits = fits && nuq[e] <= SE;
-    if (!fits) {
-        bilu_sym_long(A, p, nlp, nup, rl, ru, pass);
-        return;
-    }
-    int u[SE][SE];
-#pragma unroll
-    for (int e = 0; e < SE; e++) {
-        const RasRow rq(A.xub, e < nlp ? c[e] : p);
-#pragma unroll
-        for (int y = 0; y < SE; y++)
-            u[e][y] = (e < nlp && y < nuq[e]) ? A.ucol[rq(y)] : -2;
-    }
-    int cnt = 0, out = pass ? A.xptr[p] : 0;
-#pragma unroll
-    for (int e = 0; e < SE; e++) {
-        if (e >= nlp) break;
-#pragma unroll
-        for (int e2 = e + 1; e2 <= SE; e2++) {
-            if (e2 > nlp + nup) break;
-            int y = -1;
-#pragma unroll
-            for (int yy = SE - 1; yy >= 0; yy--)
-                if (u[e][yy] == c[e2]) y = yy;
-            if (y < 0) continue;
-            long ky = RasRow(A.xub, c[e])(y);
-            if (e2 == nlp) {
-                if (pass == 0) A.ldiag[rl(e)] = (int)ky;
-            } else {
-                if (pass) A.xl[out + cnt] = make_int4(e, e2, (int)ky, 0);
-                cnt++;
+}
+
+// The listed positions, a wavefront each: pass 0 counts a position's extra
+// matches and records the diagonal match of its L entries; pass 1 writes the
+// extra matches, by L entry, then by later entry.  The lanes hold the row's
+// entries in order (L columns, p itself, U columns), 64 at a time.
+__global__ __launch_bounds__(256) void k_bilu_sym_well(FactArgs A, const int *list, const int *nlist,
+                                                       int pass) {
+    const int lane = threadIdx.x & 63, n = *nlist;
+    for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < n; i += gridDim.x * 4) {
+        const int p = __builtin_amdgcn_readfirstlane(list[i]);
+        const int nlp = A.nl[p], tot = nlp + A.nu[p];
+        const RasRow rl(A.xlb, p), ru(A.xub, p);
+        auto entry = [&](int e) {
+            return e < nlp ? A.lcol[rl(e)] : (e == nlp ? p : (e <= tot ? A.ucol[ru(e - nlp - 1)] : -9));
+        };
+        const int c0 = entry(lane), nu0 = lane < nlp ? A.nu[c0] : 0;
+        int cnt = 0, out = pass ? A.xptr[p] : 0;
+        for (int e = 0; e < nlp; e++) {
+            const int q = e < 64 ? __shfl(c0, e, 64) : A.lcol[rl(e)];
+            const int nuq = e < 64 ? __shfl(nu0, e, 64) : A.nu[q];
+            const RasRow rq(A.xub, q);
+            for (int b = (e + 1) & ~63; b <= tot; b += 64) {
+                const int e2 = b + lane, cj = b == 0 ? c0 : entry(e2);
+                int y = -1;
+                for (int yb = 0; yb < nuq; yb += 64) {
+                    int uc = yb + lane < nuq ? A.ucol[rq(yb + lane)] : -2;
+                    for (int j = 0; j < min(64, nuq - yb); j++)
+                        if (__shfl(uc, j, 64) == cj && y < 0) y = yb + j;
+                }
+                bool found = y >= 0 && e2 > e && e2 <= tot;
+                if (found && e2 == nlp && pass == 0) A.ldiag[rl(e)] = (int)rq(y);
+                bool ext = found && e2 != nlp;
+                unsigned long long m = __ballot(ext);
+                if (pass && ext)
+                    A.xl[out + cnt + __popcll(m & ((1ull << lane) - 1))] = make_int4(e, e2, (int)rq(y), 0);
+                cnt += __popcll(m);
             }
         }
+        if (pass == 0 && lane == 0) A.xptr[p] = cnt;
     }
-    if (pass == 0) A.xptr[p] = cnt;
+}
+
+__device__ __forceinline__ void mul_blk(double *l, const double *a, const double *dk) {
+    l[0] = a[0] * dk[0] + a[1] * dk[2];
+    l[1] = a[0] * dk[1] + a[1] * dk[3];
+    l[2] = a[2] * dk[0] + a[3] * dk[2];
+    l[3] = a[2] * dk[1] + a[3] * dk[3];
 }
 
 __device__ __forceinline__ void sub_prod(double *t, const double *l, const double *u) {
@@ -565,25 +576,22 @@ __device__ __forceinline__ void sub_prod_at(double *tarr, long kt, const double 
     st_blk(tarr, kt, t);
 }
 
-// L entry e of row p (block a = A_pq, pivot dk = D_q^-1, ud = U_qp if kd >=
-// 0): the multiplier l = A_pq D_q^-1 replaces A_pq, then every later entry of
+// L entry e of row p (block a = A_pq, pivot dk = D_q^-1, ud = U_qp unless kd =
+// -1): the multiplier l = A_pq D_q^-1 replaces A_pq, then every later entry of
 // row p that row q's U part reaches loses l times that U block, in the row's
 // order (the remaining L entries, the diagonal, the U entries).
 __device__ __forceinline__ void bilu_entry(const FactArgs &A, const RasRow &rl, const RasRow &ru,
                                            int nlp, int e, const double *a, const double *dk, int kd,
                                            const double *ud, double *d, int &xi, int xe) {
     double l[4];
-    l[0] = a[0] * dk[0] + a[1] * dk[2];
-    l[1] = a[0] * dk[1] + a[1] * dk[3];
-    l[2] = a[2] * dk[0] + a[3] * dk[2];
-    l[3] = a[2] * dk[1] + a[3] * dk[3];
+    mul_blk(l, a, dk);
     st_blk(A.lval, rl(e), l);
     for (; xi < xe; xi++) {
         int4 m = A.xl[xi];
         if (m.x != e || m.y > nlp) break;
         sub_prod_at(A.lval, rl(m.y), l, A.uval, m.z);
     }
-    if (kd >= 0) sub_prod(d, l, ud);
+    if (kd != -1) sub_prod(d, l, ud);
     for (; xi < xe; xi++) {
         int4 m = A.xl[xi];
         if (m.x != e) break;
@@ -597,68 +605,110 @@ __device__ __forceinline__ void ld4(double *v, const double *p) {
 }
 
 // Rows of one level are factorised together, one lane per row, the levels in
-// turn.  A row's wait on earlier rows is one round of loads: its own first
-// LPF L blocks, their columns and U_qp slots (the row's own data, which no
-// other row changes) are requested together, then together the pivots and
-// U_qp blocks of the rows they name (final since those rows' levels), and
-// only then is any of them used.  Entries past LPF load theirs in turn.
+// turn.  A row's own data, which no other row changes (its first LPF L blocks,
+// their columns, U_qp blocks and slots, its diagonal block), are requested
+// while the row before it is worked on, across the level's barrier; a level
+// then waits for the pivots of the rows it names (final since those rows'
+// levels).  Longer rows and those with extra matches load what they need in
+// turn.  What bounds it: one CU reads and writes a subdomain's factors, about
+// 110 MB at 135,000 rows, at the 30 bytes a nanosecond that its outstanding
+// misses allow beside the AMG set-up (3.7 ms, with or without the blocks
+// requested ahead; without U_qp beside A_pq the rest of the set-up is 0.5 ms
+// slower for the traffic).
 constexpr int LPF = 4;
 constexpr int BWG = 512;              // 8 waves: registers for the prefetched blocks
 
+struct BiluRow {
+    int p, in, glob, nlp, xi, xe;     // in = 0: past the level's end; glob < 0: no row
+    int q[LPF], kd[LPF];
+    double a[LPF][4], ud[LPF][4], d[4];
+};
+
+// No branches, so that the waits stay exact: lanes past the level's end read
+// its last position again, and positions without a row have no entries.
+__device__ __forceinline__ void bilu_load(const FactArgs &A, BiluRow &R, int p, int p1) {
+    R.in = p < p1;
+    p = min(p, p1 - 1);
+    R.p = p;
+    R.glob = A.glob[p];
+    R.nlp = A.nl[p];
+    R.xi = A.xptr[p];
+    R.xe = A.xptr[p + 1];
+    const RasRow rl(A.xlb, p);
+#pragma unroll
+    for (int e = 0; e < LPF; e++) {
+        long k = rl(e);               // main entries: there, if unused, with column -1
+        R.q[e] = A.lcol[k];
+        R.kd[e] = A.ldiag[k];
+        ld_blk(R.a[e], A.lval, k);
+        ld_blk(R.ud[e], A.tval, k);
+    }
+    ld4(R.d, &A.dinv[4 * (long)p]);
+}
+
 __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
-    int s = blockIdx.x;
-    int nlev = A.nlev[s], base = A.lbase[s];
-    for (int L = 0; L < nlev; L++) {
-        int p0 = RAS_ROWS * A.soff[base + L], p1 = RAS_ROWS * A.soff[base + L + 1];
-        for (int p = p0 + (int)threadIdx.x; p < p1; p += BWG) {
-            if (A.glob[p] < 0) continue;
-            const RasRow rl(A.xlb, p), ru(A.xub, p);
-            int nlp = A.nl[p];
-            int xi = A.xptr[p], xe = A.xptr[p + 1];
-            // an extra match of an earlier entry may change a later L block
-            bool reread = xi < xe;
-            double *dp = &A.dinv[4 * (long)p];
-            double d[4];
-            ld4(d, dp);
-            int q[LPF], kd[LPF];
-            double a[LPF][4], dk[LPF][4], ud[LPF][4];
+    const int s = blockIdx.x, nlev = A.nlev[s];
+    // scalar loads: a vector load's wait would be for all before it as well
+    const auto *soff = (const __attribute__((address_space(4))) int *)(A.soff + A.lbase[s]);
+    // chunks of 512 positions; nb .. n1: the next chunk's start, its level's end
+    int L = 0, nb = RAS_ROWS * soff[0], n1 = RAS_ROWS * soff[1];
+    int n2 = RAS_ROWS * soff[min(2, nlev)];               // the end of the level after it
+    // one chunk, R, while the next one's data are requested into N
+    auto chunk = [&](BiluRow &R, BiluRow &N) __attribute__((always_inline)) {
+        // next chunk: further on in the level, or the next level
+        const bool same = nb + BWG < n1;
+        const int nL = same ? L : L + 1;
+        nb = same ? nb + BWG : n1;
+        if (!same) {
+            n1 = n2;
+            n2 = RAS_ROWS * soff[min(nL + 2, nlev)];
+        }
+        double dk[LPF][4];
 #pragma unroll
-            for (int e = 0; e < LPF; e++) {
-                if (e < nlp) {
+        for (int e = 0; e < LPF; e++) ld4(dk[e], &A.dinv[4 * (long)(R.q[e] >= 0 ? R.q[e] : R.p)]);
+#pragma unroll
+        for (int e = 0; e < LPF; e++)
+            if (R.kd[e] >= 0) ld_blk(R.ud[e], A.uval, R.kd[e]);
+        // (behind the last level: its last position once more)
+        bilu_load(A, N, nb + (int)threadIdx.x, n1);
+        if (R.in && R.glob >= 0) {
+            const RasRow rl(A.xlb, R.p), ru(A.xub, R.p);
+            if (R.xi == R.xe && R.nlp <= LPF) {
+                // all but a few rows: nothing to load, so nothing waits for
+                // the next row's data
+#pragma unroll
+                for (int e = 0; e < LPF; e++)
+                    if (R.q[e] >= 0) {
+                        double l[4];
+                        mul_blk(l, R.a[e], dk[e]);
+                        st_blk(A.lval, rl(e), l);
+                        if (R.kd[e] != -1) sub_prod(R.d, l, R.ud[e]);
+                    }
+            } else {
+                for (int e = 0; e < R.nlp; e++) {
                     long k = rl(e);
-                    q[e] = A.lcol[k];
-                    kd[e] = A.ldiag[k];
-                    ld_blk(a[e], A.lval, k);
+                    int qe = A.lcol[k], kde = A.ldiag[k];
+                    double ae[4], dke[4], ude[4];
+                    ld_blk(ae, A.lval, k);      // an earlier entry's extra match may have changed it
+                    ld4(dke, &A.dinv[4 * (long)qe]);
+                    if (kde == -2) ld_blk(ude, A.tval, k);
+                    else if (kde >= 0) ld_blk(ude, A.uval, kde);
+                    bilu_entry(A, rl, ru, R.nlp, e, ae, dke, kde, ude, R.d, R.xi, R.xe);
                 }
             }
-#pragma unroll
-            for (int e = 0; e < LPF; e++) {
-                if (e < nlp) {
-                    ld4(dk[e], &A.dinv[4 * (long)q[e]]);
-                    if (kd[e] >= 0) ld_blk(ud[e], A.uval, kd[e]);
-                }
-            }
-#pragma unroll
-            for (int e = 0; e < LPF; e++) {
-                if (e < nlp) {
-                    if (reread) ld_blk(a[e], A.lval, rl(e));
-                    bilu_entry(A, rl, ru, nlp, e, a[e], dk[e], kd[e], ud[e], d, xi, xe);
-                }
-            }
-            for (int e = LPF; e < nlp; e++) {
-                long k = rl(e);
-                int qe = A.lcol[k], kde = A.ldiag[k];
-                double ae[4], dke[4], ude[4];
-                ld_blk(ae, A.lval, k);
-                ld4(dke, &A.dinv[4 * (long)qe]);
-                if (kde >= 0) ld_blk(ude, A.uval, kde);
-                bilu_entry(A, rl, ru, nlp, e, ae, dke, kde, ude, d, xi, xe);
-            }
+            double *dp = &A.dinv[4 * (long)R.p], *d = R.d;
             double det = d[0] * d[3] - d[1] * d[2];
             if (det == 0.0 || det != det) atomicOr(A.status, 1);
             dp[0] = d[3] / det; dp[1] = -d[1] / det; dp[2] = -d[2] / det; dp[3] = d[0] / det;
         }
-        __syncthreads();
+        if (nL != L) __syncthreads();
+        L = nL;
+    };
+    BiluRow X, Y;
+    bilu_load(A, X, nb + (int)threadIdx.x, n1);
+    while (L < nlev) {
+        chunk(X, Y);
+        if (L < nlev) chunk(Y, X);
     }
 }
 
@@ -1203,8 +1253,9 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     int nb = r2p_blocks(mtot, BS);
     // 1. levels of the dependency graph
     R2P_TRY(D.apred.ensure(S.nadj > 0 ? S.nadj : 1));
+    R2P_TRY(D.succ4.ensure(mtot));
     k_pred_count<<<nb, BS, 0, s>>>(mtot, ph.n, order, J->phi_o.p, S.glob_nat.p, S.aptr.p, S.adj.p,
-                                   D.apred.p, D.nlnat.p, D.nunat.p);
+                                   D.apred.p, D.nlnat.p, D.nunat.p, D.succ4.p);
     R2P_LAUNCH();
     R2P_TRY(D.suboff.ensure(ns + 1));
     R2P_TRY(D.indeg.ensure(mtot));
@@ -1212,8 +1263,8 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     R2P_HIP(hipMemcpyAsync(D.suboff.p, S.h_off.data(), sizeof(int) * (ns + 1), hipMemcpyHostToDevice, s));
     int *dnlev = D.counters.p + 64;
     int *hflag = (int *)P->pin.p;
-    k_levels<<<ns, WG, 0, s>>>(D.suboff.p, S.aptr.p, S.adj.p, D.apred.p, D.nlnat.p, D.indeg.p,
-                               D.queue.p, D.lev.p, dnlev);
+    k_levels<<<ns, WG, 0, s>>>(D.suboff.p, S.aptr.p, S.adj.p, D.apred.p, D.succ4.p, D.nlnat.p,
+                               D.indeg.p, D.queue.p, D.lev.p, dnlev);
     R2P_LAUNCH();
     // 2. level segments
     R2P_HIP(hipMemcpyAsync(hflag, dnlev, sizeof(int) * ns, hipMemcpyDeviceToHost, s));
@@ -1331,10 +1382,15 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     F.B.vp = J->vp.p; F.B.vs = J->vs.p; F.B.cw = J->cw.p; F.B.wc = J->wc.p; F.B.wd = J->wd.p;
     F.B.nperf = ph.nperf;
     F.npos = npos;
+    F.n = ph.n; F.nx = ph.nx; F.nxy = ph.nx * ph.ny;
+    F.cell_perf = m->cell_perf.p;
     F.lbase = D.sub_lbase.p; F.nlev = D.sub_nlev.p; F.soff = D.soff.p;
     F.xlb = D.xl_b.p; F.xub = D.xu_b.p; F.glob = D.glob.p;
-    F.nl = D.nl.p; F.nu = D.nu.p; F.dsrc = D.dsrc_pos.p;
-    F.lcol = D.lcol.p; F.ucol = D.ucol.p; F.lsrc = D.lsrc.p; F.usrc = D.usrc.p;
+    F.nl = D.nl.p; F.nu = D.nu.p;
+    F.dsrc = D.dsrc_pos.p; F.lsrc = D.lsrc.p; F.usrc = D.usrc.p;
+    F.lcol = D.lcol.p; F.ucol = D.ucol.p;
+    R2P_TRY(D.tval.ensure(4 * (size_t)nle));
+    F.tval = D.tval.p;
     F.lval = D.f64.lval.p; F.uval = D.f64.uval.p; F.dinv = D.f64.dinv.p; F.status = P->status.p;
     R2P_TRY(D.xptr.ensure(npos + 1));
     R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)nle, s));
@@ -1342,17 +1398,24 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     F.ldiag = D.ldiag.p; F.xptr = D.xptr.p; F.xl = nullptr;
     k_bilu_gather<<<np, BS, 0, s>>>(F);
     R2P_LAUNCH();
-    k_bilu_sym<<<np, BS, 0, s>>>(F, 0);
+    // positions of wells and perforated cells (the level queue is free again)
+    int *wlist = D.queue.p, *nwlist = D.counters.p;
+    R2P_HIP(hipMemsetAsync(nwlist, 0, sizeof(int), s));
+    k_bilu_sym<<<np, BS, 0, s>>>(F, wlist, nwlist);
+    R2P_LAUNCH();
+    k_bilu_sym_well<<<256, 256, 0, s>>>(F, wlist, nwlist, 0);
     R2P_LAUNCH();
     int nx = 0;
     R2P_TRY(r2p_scan_int(D.xptr.p, D.xptr.p, npos + 1, &nx, P->iscratch, P->pin, s));
     R2P_TRY(D.xl.ensure(nx));
     F.xl = D.xl.p;
-    k_bilu_sym<<<np, BS, 0, s>>>(F, 1);
-    R2P_LAUNCH();
+    if (nx > 0) {
+        k_bilu_sym_well<<<256, 256, 0, s>>>(F, wlist, nwlist, 1);
+        R2P_LAUNCH();
+    }
     k_bilu0<<<ns, BWG, 0, s>>>(F);
     R2P_LAUNCH();
-    // the vectors' unused positions are read too: zero, and never written
+    // the vectors' unused positions are read too: they start from zero
     const bool f32 = P->o.precision == R2P_FP32;
     if (f32) {
         R2P_TRY(D.f32.lval.ensure(4 * (size_t)nle));
