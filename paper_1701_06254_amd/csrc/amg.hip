@@ -529,6 +529,18 @@ struct LuPanel {
     int (*si)[T / 64];
 };
 
+// take() for the candidates of lanes i and i ^ D (one of them the lane's own),
+// D 16 or 32.
+template <int D, class F>
+__device__ __forceinline__ void take_swapped(double v, int i, const F &take) {
+    int2 t = __builtin_bit_cast(int2, v), a, b;
+    int ia, ib;
+    if (D == 16) { rows_swap16(t.x, a.x, b.x); rows_swap16(t.y, a.y, b.y); rows_swap16(i, ia, ib); }
+    else { rows_swap32(t.x, a.x, b.x); rows_swap32(t.y, a.y, b.y); rows_swap32(i, ia, ib); }
+    take(__builtin_bit_cast(double, a), ia);
+    take(__builtin_bit_cast(double, b), ib);
+}
+
 // Pivots kk .. kk + 7 (below nb) with at most W panel columns left; false
 // when a pivot is zero or not a number (the same in every thread).
 template <int T, int RPT, int NB, int W>
@@ -552,8 +564,8 @@ __device__ __forceinline__ bool lu_steps(LuPanel<T, RPT, NB> &S, int n, int k0, 
         take(dpp_move<DPP_XOR2>(best), dpp_move<DPP_XOR2>(bi));
         take(dpp_move<DPP_HALF_MIRROR>(best), dpp_move<DPP_HALF_MIRROR>(bi));
         take(dpp_move<DPP_ROR8>(best), dpp_move<DPP_ROR8>(bi));
-        take(__shfl_xor(best, 16, 64), __shfl_xor(bi, 16, 64));
-        take(__shfl_xor(best, 32, 64), __shfl_xor(bi, 32, 64));
+        take_swapped<16>(best, bi, take);
+        take_swapped<32>(best, bi, take);
         if (lane == 0) { S.sv[buf][wid] = best; S.si[buf][wid] = bi; }
         __syncthreads();
         best = S.sv[buf][lane & (T / 64 - 1)];
@@ -623,51 +635,55 @@ __global__ __launch_bounds__(T) void k_lu_panel(int n, int k0, double *a, double
 }
 
 // The columns right of a panel: a workgroup takes 64 columns and LU_R rows.
-// It solves its columns of U (unit lower triangle of the panel; a wavefront
-// takes 16 of the columns, its lanes a quarter of the remaining rows each;
-// written to u by the first row of workgroups), then subtracts the panel's
-// multiples from its rows that are still active.
+// Every wavefront solves the columns of U (unit lower triangle of the panel), a
+// column to a lane and all of it in registers (written to u by the first row
+// of workgroups), then subtracts the panel's multiples from its rows that are
+// still active.  About 450 rows: 22.5 us with U in LDS and each wavefront on 16
+// of the columns, 14.4 us so.
 constexpr int LU_R = 32;
 template <int NB>
 __global__ __launch_bounds__(256, 2) void k_lu_update(int n, int k0, double *a, double *u,
                                                       const int *pos, const int *row,
                                                       const int *status) {
-    __shared__ double lt[NB][NB + 1], ut[NB][64], ls[LU_R][NB];
+    __shared__ double lt[NB][NB], ls[LU_R][NB];
     if (*status) return;
-    const int cx = threadIdx.x & 63, ty = threadIdx.x >> 6;
+    const int cx = threadIdx.x & 63, ty = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j0 = k0 + NB + blockIdx.x * 64, j = j0 + cx, i0 = blockIdx.y * LU_R;
+    const int jj = min(j, n - 1);
+    // lt[k][i]: multiplier of panel row i for pivot k
     for (int e = threadIdx.x; e < NB * NB; e += 256)
-        lt[e / NB][e % NB] = a[(long)row[k0 + e / NB] * n + k0 + e % NB];
+        lt[e % NB][e / NB] = a[(long)row[k0 + e / NB] * n + k0 + e % NB];
     for (int e = threadIdx.x; e < LU_R * NB; e += 256) {
         int i = i0 + e / NB;
         ls[e / NB][e % NB] = i < n ? a[(long)i * n + k0 + e % NB] : 0.0;
     }
-    for (int k = ty; k < NB; k += 4) ut[k][cx] = j < n ? a[(long)row[k0 + k] * n + j] : 0.0;
-    __syncthreads();
-    {
-        const int col = 16 * ty + (cx & 15), g = cx >> 4;
-        for (int k = 0; k < NB; k++) {
-            double v = ut[k][col];
-            for (int i = k + 1 + g; i < NB; i += 4) ut[i][col] -= lt[i][k] * v;
-            // the next row of U is read by other lanes of this wavefront
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
+    double uk[NB], t[LU_R / 4];
+    bool act[LU_R / 4];
+#pragma unroll
+    for (int k = 0; k < NB; k++) uk[k] = a[(long)row[k0 + k] * n + jj];
+#pragma unroll
+    for (int q = 0; q < LU_R / 4; q++) {
+        int i = i0 + 4 * q + ty;
+        act[q] = i < n && pos[min(i, n - 1)] >= k0 + NB;
+        t[q] = a[(long)min(i, n - 1) * n + jj];
     }
     __syncthreads();
+#pragma unroll
+    for (int k = 0; k < NB; k++)
+#pragma unroll
+        for (int i = k + 1; i < NB; i++) uk[i] -= lt[k][i] * uk[k];
     if (j >= n) return;
-    double uk[NB];
+    if (blockIdx.y == 0) {
 #pragma unroll
-    for (int k = 0; k < NB; k++) uk[k] = ut[k][cx];
-    if (blockIdx.y == 0)
-        for (int k = ty; k < NB; k += 4) u[(long)(k0 + k) * n + j] = ut[k][cx];
-    for (int q = ty; q < LU_R; q += 4) {
-        int i = i0 + q;
-        if (i >= n || pos[i] < k0 + NB) continue;
-        double t = a[(long)i * n + j];
+        for (int k = 0; k < NB; k++)
+            if (k % 4 == ty) u[(long)(k0 + k) * n + j] = uk[k];
+    }
 #pragma unroll
-        for (int k = 0; k < NB; k++) t -= ls[q][k] * uk[k];
-        a[(long)i * n + j] = t;
+    for (int q = 0; q < LU_R / 4; q++) {
+        if (!act[q]) continue;
+#pragma unroll
+        for (int k = 0; k < NB; k++) t[q] -= ls[4 * q + ty][k] * uk[k];
+        a[(long)(i0 + 4 * q + ty) * n + j] = t[q];
     }
 }
 
@@ -1151,7 +1167,7 @@ __device__ __forceinline__ T row_sum_wave(const CsrArgs<T> &A, int z0, int z1, i
         }
         acc += (t[0] + t[1]) + (t[2] + t[3]);
     }
-    for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+    acc = wave_sum_up(acc);
     return acc;
 }
 
@@ -1216,8 +1232,7 @@ __global__ __launch_bounds__(256) void k_restrict(int nc, int nbs, const int *mp
             T ra = r[ma], rb = r[mb];
             acc += ra + (t + GR < b ? rb : (T)0);
         }
-#pragma unroll
-        for (int d = 1; d < GR; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        acc += dpp_move<DPP_XOR1>(acc);
     } else {
         int w = ((int)blockIdx.x - nbs) * (blockDim.x >> 6) + (threadIdx.x >> 6);
         if (w >= nbig) return;
@@ -1233,7 +1248,7 @@ __global__ __launch_bounds__(256) void k_restrict(int nc, int nbs, const int *mp
             }
             acc += (v[0] + v[1]) + (v[2] + v[3]);
         }
-        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        acc = wave_sum_up(acc);
     }
     if (lane0 == 0) {
         bc[I] = acc;
@@ -1328,7 +1343,7 @@ __global__ __launch_bounds__(256) void k_down_restrict(CsrArgs<T> A, int nc, int
             __syncthreads();
         }
         if (tid >= 64) return;
-        for (int d = 1; d < 64; d <<= 1) acc += __shfl_xor(acc, d, 64);
+        acc = wave_sum_up(acc);
     }
     if (lane0 == 0) {
         bc[I] = acc;
@@ -1451,10 +1466,8 @@ __global__ __launch_bounds__(64 * CS_WAVES, 1) void k_coarse_solve(int n, const 
 // Workgroup sum of (s0, s1) into part[blockIdx.x], part[gridDim.x + blockIdx.x].
 __device__ __forceinline__ void block_partials(double s0, double s1, double *part) {
     __shared__ double red[2][BS / 64];
-    for (int d = 32; d > 0; d >>= 1) {
-        s0 += __shfl_xor(s0, d, 64);
-        s1 += __shfl_xor(s1, d, 64);
-    }
+    s0 = wave_sum_down(s0);
+    s1 = wave_sum_down(s1);
     int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) { red[0][wv] = s0; red[1][wv] = s1; }
     __syncthreads();
@@ -1520,10 +1533,8 @@ __global__ __launch_bounds__(1024) void k_kfin(int nb, const double *part, int s
         for (int u = 0; u < 8; u++) { s0 += a0[u]; s1 += a1[u]; }
     }
     for (; b < nb; b += st) { s0 += part[b]; s1 += part[nb + b]; }
-    for (int d = 32; d > 0; d >>= 1) {
-        s0 += __shfl_xor(s0, d, 64);
-        s1 += __shfl_xor(s1, d, 64);
-    }
+    s0 = wave_sum_down(s0);
+    s1 = wave_sum_down(s1);
     int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (lane == 0) { red[0][wv] = s0; red[1][wv] = s1; }
     __syncthreads();

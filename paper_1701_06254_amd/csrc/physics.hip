@@ -784,7 +784,7 @@ __global__ __launch_bounds__(256) void k_spmv(SpmvArgs A) {
             double2 v = A.wc[q];
             y0 += v.x * A.x[2 * c] + v.y * A.x[2 * c + 1];
         }
-        for (int d = 1; d < 64; d <<= 1) y0 += __shfl_xor(y0, d, 64);
+        y0 = wave_sum_up(y0);
         if (lane == 0) {
             long rw = A.n + w;
             y0 += A.wd[w] * A.x[2 * rw] + 0.0 * A.x[2 * rw + 1];
@@ -846,7 +846,7 @@ __global__ __launch_bounds__(256) void k_pcol_residual(SpmvArgs A) {
         double y0 = 0.0;
         for (int q = A.w_ptr[w] + lane; q < A.w_ptr[w + 1]; q += 64)
             y0 += A.wc[q].x * A.x[A.perf_cell[q]];
-        for (int d = 1; d < 64; d <<= 1) y0 += __shfl_xor(y0, d, 64);
+        y0 = wave_sum_up(y0);
         if (lane == 0) {
             long rw = A.n + w;
             A.y[2 * rw] = A.f[2 * rw] - y0;

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(BS) void k_mdot(const double *V, long ld, int nv, c
     for (int k = 0; k <= NV; k++) {
         if (k < nv || k == NV) {
             double v = acc[k];
-            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+            v = wave_sum_down(v);
             if (lane == 0) red[wid][k < nv ? k : nv] = v;
         }
     }
@@ -138,7 +138,7 @@ __global__ __launch_bounds__(BS) void k_mdot_sum(int nb, const double *part, dou
         for (int u = 0; u < 4; u++) v += a[u];
     }
     for (; b < nb; b += BS) v += pk[b];
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    v = wave_sum_down(v);
     if (lane == 0) red[wid] = v;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const double *V, long ld, int nv, 
     for (int k = 0; k <= NV; k++) {
         if (k < nv || k == NV) {
             double v = acc[k];
-            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+            v = wave_sum_down(v);
             if (lane == 0) red[wid][k < nv ? k : nv] = v;
         }
     }
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(BS) void k_mdot2(const double *V, long ld, int nv, 
     for (int k = 0; k < NV; k++) {
         if (k < nv) {
             double v = acg[k];
-            for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+            v = wave_sum_down(v);
             if (lane == 0) red[wid][nv + 1 + k] = v;
         }
     }
