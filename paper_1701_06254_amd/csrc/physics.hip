@@ -385,7 +385,7 @@ __device__ __forceinline__ void assemble_well(const AsmArgs &A, int w, int lane)
 // wells' rows run in workgroups of the same launch, ahead of the cells'.
 // Bound by its stores, 224 of the 304 bytes of a cell: as ordinary stores the
 // 14 streams displace each other's and the neighbours' lines (164 us at 2M
-// cells), as non-temporal ones they leave at 4.9 TB/s (124 us).
+// cells), as non-temporal ones they leave at 4.9 TB/s (134 us).
 __global__ __launch_bounds__(256) void k_assemble(AsmArgs A) {
     const Phys &P = A.P;
     if ((int)blockIdx.x < A.nwblk) {
