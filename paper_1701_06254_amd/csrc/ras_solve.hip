@@ -443,6 +443,8 @@ struct FactArgs {
     double *lval, *uval, *dinv;
     double *tval;                // per L entry (p, q): A_qp
     int *status;
+    int *prog;                   // as in SweepArgs, zeroed by k_bilu_gather
+    int ns, nhelp;
 };
 
 // Block k of a factor array.
@@ -462,6 +464,7 @@ __device__ __forceinline__ void st_blk(double *arr, long k, const double *v) {
 // row's own data, where following ldiag costs two lines of row q.
 __global__ void k_bilu_gather(FactArgs A) {
     int p = blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < A.ns) A.prog[PROG_STRIDE * p] = 0;
     if (p >= A.npos || A.glob[p] < 0) return;
     int nlp = A.nl[p], nup = A.nu[p];
     const RasRow rl(A.xlb, p), ru(A.xub, p);
@@ -604,87 +607,238 @@ __device__ __forceinline__ void ld4(double *v, const double *p) {
     v[0] = a.x; v[1] = a.y; v[2] = b.x; v[3] = b.y;
 }
 
-// Rows of one level are factorised together, one lane per row, the levels in
-// turn.  A row's own data, which no other row changes (its first LPF L blocks,
-// their columns, U_qp blocks and slots, its diagonal block), are requested
-// while the row before it is worked on, across the level's barrier; a level
-// then waits for the pivots of the rows it names (final since those rows'
-// levels).  Longer rows and those with extra matches load what they need in
-// turn.  What bounds it: one CU reads and writes a subdomain's factors, about
-// 110 MB at 135,000 rows, at the 30 bytes a nanosecond that its outstanding
-// misses allow beside the AMG set-up (3.7 ms, with or without the blocks
-// requested ahead; without U_qp beside A_pq the rest of the set-up is 0.5 ms
-// slower for the traffic).
+// The wavefronts take the subdomain's slices in turn, two lanes per position as
+// in the sweep, and a slice runs once the slices of all levels before it are
+// finished (a count in LDS; a wavefront waits for slices before its own only, so
+// the lowest unfinished one always runs).  A row's own data, which no other row
+// changes (its main L blocks, their columns, U_qp blocks and slots, its
+// diagonal block), are requested while the wavefront's slice before it is worked
+// on, in whole contiguous loads; the slice then waits for the count and for the
+// pivots of the rows it names.  Lane 2r + h works on entries h and 2 + h and on
+// row h of the diagonal block; the partner's products come by DPP and are
+// subtracted in the order of the entries, a long row's second position's after
+// its own.  Rows with extra matches or still more entries are worked on by their
+// first lane alone, which loads what it needs in turn.
+// What bounds it: one CU reads and writes a subdomain's factors, about 61 MB at
+// 143,000 positions, with two slices' data in flight per wavefront, so what a
+// load takes; helper workgroups on the XCD read ahead into its L2 as for the
+// sweep.  16 such subdomains beside the AMG set-up: 3.0 to 3.7 ms with a lane per
+// row and a barrier per level; 3.1 in this form with long rows left to one lane,
+// 2.5 with them, 2.04 with 4 helpers each (2: 2.27; 8: 2.05; 32 slices ahead
+// instead of 64: 2.30).  2,000 cells: 100 us before, 53 now.  16 wavefronts of
+// 128 registers spill (5.7 ms), 8 take 2.56 ms without helpers.
 constexpr int LPF = 4;
-constexpr int BWG = 512;              // 8 waves: registers for the prefetched blocks
+static_assert(LPF == RAS_MAIN, "the main entries are held in registers");
+constexpr int BWG = 768;
+constexpr int BNW = BWG / 64;
 
 struct BiluRow {
-    int p, in, glob, nlp, xi, xe;     // in = 0: past the level's end; glob < 0: no row
-    int q[LPF], kd[LPF];
-    double a[LPF][4], ud[LPF][4], d[4];
+    int p, glob, nlp, xi, xe;     // glob < 0: no row
+    int q[2], kd[2];              // entries h, 2 + h
+    double2 a0[2], u0[2];         // blocks of entry h: row h, row 1 - h
+    double2 a1[2], u1[2];         // rows h of the blocks of entries 2 and 3
+    double2 d;                    // row h
 };
 
-// No branches, so that the waits stay exact: lanes past the level's end read
-// its last position again, and positions without a row have no entries.
-__device__ __forceinline__ void bilu_load(const FactArgs &A, BiluRow &R, int p, int p1) {
-    R.in = p < p1;
-    p = min(p, p1 - 1);
+// No branches, so that the waits stay exact: positions without a row have no
+// entries.
+__device__ __forceinline__ void bilu_load(const FactArgs &A, BiluRow &R, int sl, int lane) {
+    const int p = RAS_ROWS * sl + (lane >> 1);
     R.p = p;
     R.glob = A.glob[p];
     R.nlp = A.nl[p];
     R.xi = A.xptr[p];
     R.xe = A.xptr[p + 1];
-    const RasRow rl(A.xlb, p);
+    const long k = (long)sl * RAS_MENT + lane;     // entry h; 64 further: entry 2 + h
+    const double2 *lv = (const double2 *)A.lval + 2 * (long)sl * RAS_MENT + lane;
+    const double2 *tv = (const double2 *)A.tval + 2 * (long)sl * RAS_MENT + lane;
 #pragma unroll
-    for (int e = 0; e < LPF; e++) {
-        long k = rl(e);               // main entries: there, if unused, with column -1
-        R.q[e] = A.lcol[k];
-        R.kd[e] = A.ldiag[k];
-        ld_blk(R.a[e], A.lval, k);
-        ld_blk(R.ud[e], A.tval, k);
+    for (int i = 0; i < 2; i++) {
+        R.q[i] = A.lcol[k + 64 * i];
+        R.kd[i] = A.ldiag[k + 64 * i];
+        R.a0[i] = lv[64 * i];
+        R.u0[i] = tv[64 * i];
+        R.a1[i] = lv[128 + 64 * i];
+        R.u1[i] = tv[128 + 64 * i];
     }
-    ld4(R.d, &A.dinv[4 * (long)p]);
+    R.d = ((const double2 *)A.dinv)[(long)sl * 64 + lane];
+}
+
+__device__ __forceinline__ double2 sel2(bool c, double2 x, double2 y) {
+    return make_double2(c ? x.x : y.x, c ? x.y : y.y);
+}
+
+// Product of the block row l with block u given as its rows h and 1 - h.
+__device__ __forceinline__ double2 row_prod(double2 l, double2 uh, double2 uo, bool h) {
+    double x = h ? l.y : l.x, y = h ? l.x : l.y;       // (a sum of two commutes)
+    return make_double2(x * uh.x + y * uo.x, x * uh.y + y * uo.y);
+}
+
+constexpr int PSPIN = 1 << 16;    // bound of a helper's wait for its subdomain
+// Read one dword of every 128-byte line of [p, p + bytes) (all addresses
+// inside the range); the values are summed only so that the loads stay.
+__device__ __forceinline__ unsigned touch(const void *p, long bytes) {
+    if (bytes < 4) return 0;
+    const char *c = (const char *)p;
+    const char *line0 = (const char *)((unsigned long)c & ~127ul);
+    long last = (long)(c + bytes - 4 - line0);          // offset of the range's last dword
+    long lines = last / 128 + 1;
+    unsigned acc = 0;
+    for (long i = threadIdx.x; i < lines; i += blockDim.x) {
+        const char *a = line0 + i * 128;
+        a = a < c ? c : a;
+        a = a > c + bytes - 4 ? c + bytes - 4 : a;
+        acc += *(const unsigned *)((unsigned long)a & ~3ul);
+    }
+    return acc;
+}
+
+// Helper j of H of subdomain s: reads the data of the slices up to BPD ahead of
+// the factorisation into the XCD's L2, in chunks of BPC.
+constexpr int BPC = 8, BPD = 64, BHELP = 4;
+__device__ unsigned bilu_prefetch(const FactArgs &A, int s, int j, int H) {
+    const int s0 = A.soff[A.lbase[s]], nsl = A.soff[A.lbase[s] + A.nlev[s]] - s0;
+    unsigned acc = 0;
+    for (int c = j; c * BPC < nsl; c += H) {
+        const int i0 = c * BPC;
+        const long f = s0 + i0, m = min(BPC, nsl - i0);
+        if (threadIdx.x == 0)
+            for (int spin = 0; spin < PSPIN; spin++) {
+                int done = __hip_atomic_load(&A.prog[PROG_STRIDE * s], __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+                if (i0 - done <= BPD) break;
+                __builtin_amdgcn_s_sleep(8);
+            }
+        __syncthreads();
+        acc += touch(A.lcol + f * RAS_MENT, 4L * RAS_MENT * m);
+        acc += touch(A.ldiag + f * RAS_MENT, 4L * RAS_MENT * m);
+        acc += touch(A.lval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
+        acc += touch(A.tval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
+        acc += touch(A.dinv + 4 * f * RAS_ROWS, 32L * RAS_ROWS * m);
+        acc += touch(A.glob + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        acc += touch(A.nl + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        acc += touch(A.xptr + f * RAS_ROWS, 4L * RAS_ROWS * m);
+    }
+    return acc;
 }
 
 __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
+    __shared__ int count;
+    if ((int)blockIdx.x >= A.ns) {
+        // a helper, on its subdomain's XCD (see k_ras_sweep)
+        const int hb = blockIdx.x - A.ns;
+        unsigned acc = bilu_prefetch(A, hb % A.ns, hb / A.ns, A.nhelp);
+        if (A.nhelp < 0) A.prog[0] = (int)acc;     // never taken; keeps the reads
+        return;
+    }
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
     const int s = blockIdx.x, nlev = A.nlev[s];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const bool h = lane & 1;
     // scalar loads: a vector load's wait would be for all before it as well
     const auto *soff = (const __attribute__((address_space(4))) int *)(A.soff + A.lbase[s]);
-    // chunks of 512 positions; nb .. n1: the next chunk's start, its level's end
-    int L = 0, nb = RAS_ROWS * soff[0], n1 = RAS_ROWS * soff[1];
-    int n2 = RAS_ROWS * soff[min(2, nlev)];               // the end of the level after it
-    // one chunk, R, while the next one's data are requested into N
-    auto chunk = [&](BiluRow &R, BiluRow &N) __attribute__((always_inline)) {
-        // next chunk: further on in the level, or the next level
-        const bool same = nb + BWG < n1;
-        const int nL = same ? L : L + 1;
-        nb = same ? nb + BWG : n1;
-        if (!same) {
-            n1 = n2;
-            n2 = RAS_ROWS * soff[min(nL + 2, nlev)];
+    const int s0 = soff[0], s1 = soff[nlev];
+    int sl = s0 + wave, seen = 0;
+    if (sl >= s1) return;
+    // the level of slice sl: its first slice and the next level's
+    int L = 0, lo = s0, hi = soff[1];
+    auto level_of = [&](int t) {
+        while (t >= hi) {
+            L++;
+            lo = hi;
+            hi = soff[L + 1];
         }
-        double dk[LPF][4];
+    };
+    level_of(sl);
+    // one slice, R, while the wavefront's next one's data are requested into N
+    auto slice = [&](BiluRow &R, BiluRow &N) __attribute__((always_inline)) {
+        const int need = lo - s0;
+        while (seen < need)
+            seen = __builtin_amdgcn_readfirstlane(
+                __hip_atomic_load(&count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+        double dk[2][4];
 #pragma unroll
-        for (int e = 0; e < LPF; e++) ld4(dk[e], &A.dinv[4 * (long)(R.q[e] >= 0 ? R.q[e] : R.p)]);
+        for (int i = 0; i < 2; i++) ld4(dk[i], &A.dinv[4 * (long)(R.q[i] >= 0 ? R.q[i] : R.p)]);
+        // block rows h, 1 - h of the lane's second entry: the partner holds one
+        double2 a2[2], u2[2];
+        {
+            double2 t = sel2(h, R.a1[0], R.a1[1]);
+            a2[0] = sel2(h, R.a1[1], R.a1[0]);
+            a2[1] = make_double2(dpp_move<DPP_XOR1>(t.x), dpp_move<DPP_XOR1>(t.y));
+            t = sel2(h, R.u1[0], R.u1[1]);
+            u2[0] = sel2(h, R.u1[1], R.u1[0]);
+            u2[1] = make_double2(dpp_move<DPP_XOR1>(t.x), dpp_move<DPP_XOR1>(t.y));
+        }
+        // U_qp that extra matches change
 #pragma unroll
-        for (int e = 0; e < LPF; e++)
-            if (R.kd[e] >= 0) ld_blk(R.ud[e], A.uval, R.kd[e]);
-        // (behind the last level: its last position once more)
-        bilu_load(A, N, nb + (int)threadIdx.x, n1);
-        if (R.in && R.glob >= 0) {
-            const RasRow rl(A.xlb, R.p), ru(A.xub, R.p);
-            if (R.xi == R.xe && R.nlp <= LPF) {
-                // all but a few rows: nothing to load, so nothing waits for
-                // the next row's data
+        for (int i = 0; i < 2; i++)
+            if (R.kd[i] >= 0) {
+                const double2 *u = (const double2 *)A.uval;
+                double2 x = u[ras_val(R.kd[i], h) >> 1], y = u[ras_val(R.kd[i], 1 - h) >> 1];
+                if (i == 0) { R.u0[0] = x; R.u0[1] = y; }
+                else { u2[0] = x; u2[1] = y; }
+            }
+        // (behind the wavefront's last slice: that one once more)
+        const int nx = sl + BNW < s1 ? sl + BNW : sl;
+        bilu_load(A, N, nx, lane);
+        // entries of a row whose main entries are all (NOT_PLAIN if there are
+        // more, or extra matches), -1 for no row
+        constexpr int NOT_PLAIN = 2 * LPF + 1;
+        const bool row = R.glob >= 0;
+        const int info = !row ? -1 : (R.xi == R.xe ? min(R.nlp, NOT_PLAIN) : NOT_PLAIN);
+        const bool plain = info < NOT_PLAIN;
+        // the second position of a plain row, with its entries LPF ..
+        const int info2 = dpp_move<DPP_XOR2>(info);
+        const bool second = (lane & 2) && !row && info2 > LPF && info2 < NOT_PLAIN;
+        const int nst = second ? info2 - LPF : (plain ? info : 0);
+        // entry h (rows h, 1 - h), entry 2 + h
+        double2 l0[2], l1[2], p0[2], p1[2];
+        const double2 zero = make_double2(0.0, 0.0);
 #pragma unroll
-                for (int e = 0; e < LPF; e++)
-                    if (R.q[e] >= 0) {
-                        double l[4];
-                        mul_blk(l, R.a[e], dk[e]);
-                        st_blk(A.lval, rl(e), l);
-                        if (R.kd[e] != -1) sub_prod(R.d, l, R.ud[e]);
-                    }
-            } else {
+        for (int j = 0; j < 2; j++) {
+            const double2 a = R.a0[j], b = a2[j];
+            l0[j] = make_double2(a.x * dk[0][0] + a.y * dk[0][2], a.x * dk[0][1] + a.y * dk[0][3]);
+            l1[j] = make_double2(b.x * dk[1][0] + b.y * dk[1][2], b.x * dk[1][1] + b.y * dk[1][3]);
+            // subtracting zero changes nothing
+            p0[j] = sel2(R.kd[0] != -1, row_prod(l0[j], R.u0[0], R.u0[1], h), zero);
+            p1[j] = sel2(R.kd[1] != -1, row_prod(l1[j], u2[0], u2[1], h), zero);
+        }
+        auto other = [](double2 v) {
+            return make_double2(dpp_move<DPP_XOR1>(v.x), dpp_move<DPP_XOR1>(v.y));
+        };
+        const double2 r0 = other(p0[1]), r1 = other(p1[1]), rl = other(l1[1]);
+        double2 d = R.d;
+        const double2 d0 = other(d);
+        auto sub = [&](double2 v) { d.x -= v.x; d.y -= v.y; };
+        const double2 w0 = sel2(h, r0, p0[0]), w1 = sel2(h, p0[0], r0);
+        const double2 w2 = sel2(h, r1, p1[0]), w3 = sel2(h, p1[0], r1);
+        sub(w0);
+        sub(w1);
+        sub(w2);
+        sub(w3);
+        const bool lng = plain && info > LPF;
+        if (__ballot(lng)) {
+            auto next = [&](double2 v) {
+                double2 t = make_double2(dpp_move<DPP_XOR2>(v.x), dpp_move<DPP_XOR2>(v.y));
+                sub(sel2(lng, t, zero));
+            };
+            next(w0);
+            next(w1);
+            next(w2);
+            next(w3);
+        }
+        {
+            double2 *lv = (double2 *)A.lval + 2 * (long)sl * RAS_MENT + lane;
+            if ((int)h < nst) { lv[0] = l0[0]; lv[64] = l0[1]; }
+            if (2 < nst) lv[128] = sel2(h, rl, l1[0]);
+            if (3 < nst) lv[192] = sel2(h, l1[0], rl);
+        }
+        if (__ballot(row && !plain)) {
+            double D[4] = {R.d.x, R.d.y, d0.x, d0.y};      // the first lane's view
+            if (row && !plain && !h) {
+                const RasRow rl(A.xlb, R.p), ru(A.xub, R.p);
                 for (int e = 0; e < R.nlp; e++) {
                     long k = rl(e);
                     int qe = A.lcol[k], kde = A.ldiag[k];
@@ -693,22 +847,36 @@ __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
                     ld4(dke, &A.dinv[4 * (long)qe]);
                     if (kde == -2) ld_blk(ude, A.tval, k);
                     else if (kde >= 0) ld_blk(ude, A.uval, kde);
-                    bilu_entry(A, rl, ru, R.nlp, e, ae, dke, kde, ude, R.d, R.xi, R.xe);
+                    bilu_entry(A, rl, ru, R.nlp, e, ae, dke, kde, ude, D, R.xi, R.xe);
                 }
             }
-            double *dp = &A.dinv[4 * (long)R.p], *d = R.d;
-            double det = d[0] * d[3] - d[1] * d[2];
-            if (det == 0.0 || det != det) atomicOr(A.status, 1);
-            dp[0] = d[3] / det; dp[1] = -d[1] / det; dp[2] = -d[2] / det; dp[3] = d[0] / det;
+            const double2 D1 = other(make_double2(D[2], D[3]));
+            if (!plain) d = h ? D1 : make_double2(D[0], D[1]);
         }
-        if (nL != L) __syncthreads();
-        L = nL;
+        const double2 o = other(d);
+        const double t = d.x * o.y - d.y * o.x, det = h ? -t : t;
+        if (row) {
+            if (det == 0.0 || det != det) atomicOr(A.status, 1);
+            const double2 z = make_double2(h ? -d.x : o.y, h ? o.x : -d.y);
+            ((double2 *)A.dinv)[(long)sl * 64 + lane] = make_double2(z.x / det, z.y / det);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        // one lane adds (an atomicAdd here comes with instructions that combine lanes)
+        if (lane == 0)
+            asm volatile("ds_add_u32 %0, %1"
+                         :: "v"((unsigned)(size_t)(__attribute__((address_space(3))) int *)&count), "v"(1)
+                         : "memory");
+        if (wave == 0)      // (see sweep_step)
+            __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], seen, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_WORKGROUP);
+        level_of(nx);
+        sl += BNW;
     };
     BiluRow X, Y;
-    bilu_load(A, X, nb + (int)threadIdx.x, n1);
-    while (L < nlev) {
-        chunk(X, Y);
-        if (L < nlev) chunk(Y, X);
+    bilu_load(A, X, sl, lane);
+    while (sl < s1) {
+        slice(X, Y);
+        if (sl < s1) slice(Y, X);
     }
 }
 
@@ -1068,26 +1236,7 @@ __device__ __forceinline__ void sweep_dir(const SweepArgs<T> &A, T *ring, int *c
 // ------------------------------------------------------- prefetch helpers
 constexpr int PCH = 8;            // slices per helper chunk
 constexpr int PDS = 128;          // slices a chunk is read ahead of the sweep (about 0.8 MB)
-constexpr int PSPIN = 1 << 16;    // bound of a helper's wait for the sweep
 constexpr int MAX_HELP = 8;       // helper workgroups per subdomain
-
-// Read one dword of every 128-byte line of [p, p + bytes) (all addresses
-// inside the range); the values are summed only so that the loads stay.
-__device__ __forceinline__ unsigned touch(const void *p, long bytes) {
-    if (bytes < 4) return 0;
-    const char *c = (const char *)p;
-    const char *line0 = (const char *)((unsigned long)c & ~127ul);
-    long last = (long)(c + bytes - 4 - line0);          // offset of the range's last dword
-    long lines = last / 128 + 1;
-    unsigned acc = 0;
-    for (long i = threadIdx.x; i < lines; i += blockDim.x) {
-        const char *a = line0 + i * 128;
-        a = a < c ? c : a;
-        a = a > c + bytes - 4 ? c + bytes - 4 : a;
-        acc += *(const unsigned *)((unsigned long)a & ~3ul);
-    }
-    return acc;
-}
 
 // Helper j of subdomain s, one direction: chunks j, j + H, ... of PCH
 // slices in the sweep's order; each waits (bounded) until the sweep has
@@ -1396,6 +1545,8 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)nle, s));
     R2P_HIP(hipMemsetAsync(D.xptr.p + npos, 0, sizeof(int), s));
     F.ldiag = D.ldiag.p; F.xptr = D.xptr.p; F.xl = nullptr;
+    F.prog = D.prog.p; F.ns = ns;
+    F.nhelp = ns % 8 == 0 ? std::max(0, std::min(BHELP, 256 / ns - 1)) : 0;
     k_bilu_gather<<<np, BS, 0, s>>>(F);
     R2P_LAUNCH();
     // positions of wells and perforated cells (the level queue is free again)
@@ -1413,7 +1564,7 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
         k_bilu_sym_well<<<256, 256, 0, s>>>(F, wlist, nwlist, 1);
         R2P_LAUNCH();
     }
-    k_bilu0<<<ns, BWG, 0, s>>>(F);
+    k_bilu0<<<ns * (1 + F.nhelp), BWG, 0, s>>>(F);
     R2P_LAUNCH();
     // the vectors' unused positions are read too: they start from zero
     const bool f32 = P->o.precision == R2P_FP32;

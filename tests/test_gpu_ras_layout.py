@@ -24,7 +24,7 @@ pytestmark = pytest.mark.gpu
 CASES = [(32, 31, 1, 1, 1, 0, 0, 0.0), (34, 33, 2, 1, 1, 0, 0, 0.0), (67, 1, 1, 2, 1, 1, 0, 0.0),
          (9, 7, 5, 2, 2, 0, 1, 50.0), (12, 11, 7, 3, 2, 2, 1, 50.0), (3, 3, 30, 1, 1, 0, 1, 5.0),
          (5, 4, 8, 2, 1, 1, 1, 50.0), (5, 4, 9, 1, 1, 1, 0, 50.0), (1, 1, 2, 1, 1, 0, 1, 5.0),
-         (64, 64, 40, 1, 1, 0, 1, 50.0)]
+         (64, 64, 40, 1, 1, 0, 1, 50.0), (24, 18, 7, 4, 2, 1, 1, 50.0)]
 
 
 @pytest.mark.parametrize("precision", [0, 1])
