@@ -64,38 +64,37 @@ HostPinned::~HostPinned() {
 }
 
 // ------------------------------------------------------------------ scan
-// Three passes: per-tile sums, a scan of the tile sums by one workgroup, then
-// per-tile scans offset by the scanned sums.  Tiles of 4096 ints (1024 lanes
-// x 4), fixed summation order, so the result is deterministic.
+// Per-tile sums, a scan of the tile sums, then per-tile scans offset by the
+// scanned sums, in tiles of 4096 ints (1024 lanes x 4).  A set-up makes dozens
+// of scans and most are short, so launches are what they cost: up to SCAN_FEW
+// tiles one workgroup does it all (3.5 us instead of three kernels of 2.1 to
+// 2.5 us each and the gaps between them), up to SCAN_MID tiles every workgroup
+// of the last pass adds up the tile sums before its own, at most 4 KB.
 constexpr int SCAN_BS = 1024;
 constexpr int SCAN_PER = 4;
 constexpr int SCAN_TILE = SCAN_BS * SCAN_PER;
+constexpr int SCAN_FEW = 4;       // SCAN_FEW * SCAN_BS / 64 wavefront sums: one per lane
+constexpr int SCAN_MID = 1024;
 
-__device__ inline int block_excl_scan(int v, int *lds, int *total) {
-    // inclusive within the wavefront
-    int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int x = v;
+__device__ inline int wave_incl_scan(int x) {
+    int lane = threadIdx.x & 63;
     for (int d = 1; d < 64; d <<= 1) {
         int y = __shfl_up(x, d, 64);
         if (lane >= d) x += y;
     }
+    return x;
+}
+
+__device__ inline int block_excl_scan(int v, int *lds, int *total) {
+    int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    int x = wave_incl_scan(v);
     if (lane == 63) lds[wid] = x;
     __syncthreads();
-    int nw = blockDim.x >> 6;
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < nw; w++) {
-            int t = lds[w];
-            lds[w] = acc;
-            acc += t;
-        }
-        lds[nw] = acc;
-    }
+    int w = wave_incl_scan(lane < nw ? lds[lane] : 0);      // in every wavefront
+    if (total) *total = __shfl(w, nw - 1, 64);
+    int before = __shfl(w, wid > 0 ? wid - 1 : 0, 64);
     __syncthreads();
-    int r = x - v + lds[wid];
-    if (total) *total = lds[nw];
-    __syncthreads();
-    return r;
+    return x - v + (wid > 0 ? before : 0);
 }
 
 __global__ void k_scan_tiles(const int *in, int n, int *tsum) {
@@ -127,7 +126,10 @@ __global__ void k_scan_sums(int *tsum, int nt, int *total) {
     if (threadIdx.x == 0) *total = tot;
 }
 
-__global__ void k_scan_apply(const int *in, int *out, int n, const int *tsum) {
+// OWN: tsum holds the tiles' sums, not yet scanned; the last workgroup writes
+// the total.
+template <bool OWN>
+__global__ void k_scan_apply(const int *in, int *out, int n, const int *tsum, int *total) {
     __shared__ int lds[SCAN_BS / 64 + 1];
     long base = (long)blockIdx.x * SCAN_TILE + (long)threadIdx.x * SCAN_PER;
     int v[SCAN_PER];
@@ -136,12 +138,56 @@ __global__ void k_scan_apply(const int *in, int *out, int n, const int *tsum) {
         v[k] = base + k < n ? in[base + k] : 0;
         s += v[k];
     }
-    int off = block_excl_scan(s, lds, nullptr) + tsum[blockIdx.x];
+    int before, tot;
+    if (OWN) {
+        int t = 0;
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += SCAN_BS) t += tsum[k];
+        block_excl_scan(t, lds, &before);
+    } else {
+        before = tsum[blockIdx.x];
+    }
+    int off = block_excl_scan(s, lds, &tot) + before;
+    if (OWN && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = before + tot;
     for (int k = 0; k < SCAN_PER; k++)
         if (base + k < n) {
             out[base + k] = off;
             off += v[k];
         }
+}
+
+// Up to SCAN_FEW tiles by one workgroup: all tiles' wavefront sums meet in LDS
+// once.
+__global__ __launch_bounds__(SCAN_BS) void k_scan_one(const int *in, int *out, int n, int *total) {
+    constexpr int NW = SCAN_BS / 64;
+    static_assert(SCAN_FEW * NW == 64, "a wavefront sum per lane");
+    __shared__ int lds[64];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    int v[SCAN_FEW][SCAN_PER], s[SCAN_FEW], x[SCAN_FEW];
+    for (int t = 0; t < SCAN_FEW; t++)
+        for (int k = 0; k < SCAN_PER; k++) {
+            int i = t * SCAN_TILE + (int)threadIdx.x * SCAN_PER + k;
+            v[t][k] = i < n ? in[i] : 0;
+        }
+    for (int t = 0; t < SCAN_FEW; t++) {
+        s[t] = 0;
+        for (int k = 0; k < SCAN_PER; k++) s[t] += v[t][k];
+        x[t] = wave_incl_scan(s[t]);
+        if (lane == 63) lds[t * NW + wid] = x[t];
+    }
+    __syncthreads();
+    const int w = wave_incl_scan(lds[lane]);
+    if (threadIdx.x == 63) *total = w;
+    for (int t = 0; t < SCAN_FEW; t++) {
+        int q = t * NW + wid, before = __shfl(w, q > 0 ? q - 1 : 0, 64);
+        int off = x[t] - s[t] + (q > 0 ? before : 0);
+        for (int k = 0; k < SCAN_PER; k++) {
+            int i = t * SCAN_TILE + (int)threadIdx.x * SCAN_PER + k;
+            if (i < n) {
+                out[i] = off;
+                off += v[t][k];
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------------ radix sort
@@ -282,21 +328,31 @@ int r2p_scan_int(const int *in, int *out, int n, int *total_host, DBuf<int> &tmp
                  hipStream_t s) {
     int nt = r2p_blocks(n > 0 ? n : 1, SCAN_TILE);
     R2P_TRY(tmp.ensure(nt + 1));
-    if (n > 0) {
+    int *total = tmp.p + nt;
+    if (total_host) {
+        // straight into the pinned word: no copy between the kernel and the host
+        R2P_TRY(pin.ensure(64));
+        total = (int *)pin.p;
+    }
+    if (nt <= SCAN_FEW) {
+        k_scan_one<<<1, SCAN_BS, 0, s>>>(in, out, n, total);
+        R2P_LAUNCH();
+    } else if (nt <= SCAN_MID) {
         k_scan_tiles<<<nt, SCAN_BS, 0, s>>>(in, n, tmp.p);
         R2P_LAUNCH();
-        k_scan_sums<<<1, SCAN_BS, 0, s>>>(tmp.p, nt, tmp.p + nt);
-        R2P_LAUNCH();
-        k_scan_apply<<<nt, SCAN_BS, 0, s>>>(in, out, n, tmp.p);
+        k_scan_apply<true><<<nt, SCAN_BS, 0, s>>>(in, out, n, tmp.p, total);
         R2P_LAUNCH();
     } else {
-        R2P_HIP(hipMemsetAsync(tmp.p + nt, 0, sizeof(int), s));
+        k_scan_tiles<<<nt, SCAN_BS, 0, s>>>(in, n, tmp.p);
+        R2P_LAUNCH();
+        k_scan_sums<<<1, SCAN_BS, 0, s>>>(tmp.p, nt, total);
+        R2P_LAUNCH();
+        k_scan_apply<false><<<nt, SCAN_BS, 0, s>>>(in, out, n, tmp.p, nullptr);
+        R2P_LAUNCH();
     }
     if (total_host) {
-        R2P_TRY(pin.ensure(64));
-        R2P_HIP(hipMemcpyAsync(pin.p, tmp.p + nt, sizeof(int), hipMemcpyDeviceToHost, s));
         R2P_HIP(hipStreamSynchronize(s));
-        *total_host = *(int *)pin.p;
+        *total_host = *(volatile int *)pin.p;
     }
     return 0;
 }
