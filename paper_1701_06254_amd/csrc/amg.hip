@@ -503,11 +503,11 @@ __global__ void k_castv(long n, const double *a, T *b) {
 // ------------------------------------------------------------- coarsest
 // One workgroup per row of the dense matrix.
 __global__ void k_to_dense(int n, const int *rp, const int *col, const double *val, double *a,
-                           int *pos) {
+                           int *pos, int *chosen) {
     int i = blockIdx.x;
     double *row = a + (long)i * n;
     for (int j = threadIdx.x; j < n; j += blockDim.x) row[j] = 0.0;
-    if (threadIdx.x == 0) pos[i] = i;
+    if (threadIdx.x == 0) pos[i] = chosen[i] = i;
     __syncthreads();
     // a row's columns are distinct
     for (int z = rp[i] + (int)threadIdx.x; z < rp[i + 1]; z += blockDim.x) row[col[z]] = val[z];
@@ -696,7 +696,8 @@ __global__ __launch_bounds__(256, 2) void k_lu_update(int n, int k0, double *a, 
 }
 
 // L below U in position order: u[k][j] = a[row[k]][j], j < k.
-__global__ void k_lu_gather(int n, const double *a, const int *row, double *u) {
+__global__ void k_lu_gather(int n, const double *a, const int *row, const int *status, double *u) {
+    if (*status) return;             // singular: no row was chosen from the failed pivot on
     int k = blockIdx.x;
     const double *src = a + (long)row[k] * n;
     for (int j = threadIdx.x; j < k; j += blockDim.x) u[(long)k * n + j] = src[j];
@@ -837,7 +838,7 @@ static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
     R2P_TRY(P->cinv.ensure((size_t)n * n));
     R2P_TRY(P->lupos.ensure(n));
     R2P_TRY(P->lurow.ensure(n));
-    k_to_dense<<<n, BS, 0, s>>>(n, C.rp.p, C.col.p, C.val.p, P->lu.p, P->lupos.p);
+    k_to_dense<<<n, BS, 0, s>>>(n, C.rp.p, C.col.p, C.val.p, P->lu.p, P->lupos.p, P->lurow.p);
     R2P_LAUNCH();
     // one workgroup holds a panel's rows: fewer columns where a thread holds
     // two or four rows
@@ -846,7 +847,7 @@ static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
     else if (n <= 1024) R2P_TRY((dense_lu<1024, 1, 32>(P, n, s)));
     else if (n <= 2048) R2P_TRY((dense_lu<1024, 2, 16>(P, n, s)));
     else R2P_TRY((dense_lu<1024, 4, 8>(P, n, s)));
-    k_lu_gather<<<n, BS, 0, s>>>(n, P->lu.p, P->lurow.p, P->luu.p);
+    k_lu_gather<<<n, BS, 0, s>>>(n, P->lu.p, P->lurow.p, P->astatus.p, P->luu.p);
     R2P_LAUNCH();
 #define R2P_INV(NR, AH) \
     k_dense_inv_col<NR, AH><<<n, 64, 0, s>>>(n, P->luu.p, P->lupos.p, P->astatus.p, P->cinv.p)
