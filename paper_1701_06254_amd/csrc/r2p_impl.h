@@ -226,7 +226,7 @@ struct RasDyn {
     DBuf<int> sub_lbase;                  // ns: first segment of the subdomain
     DBuf<int> sub_nlev;                   // ns
     DBuf<int> counters;                   // scratch
-    DBuf<int> prog;                       // ns: slices finished, read by the prefetch helpers
+    DBuf<int> prog;                       // ns: slice a sweep is at, read by the prefetch helpers
     DBuf<int> swin;                       // ns: ring window of every subdomain's sweep
     RasFactors<double> f64;
     RasFactors<float> f32;

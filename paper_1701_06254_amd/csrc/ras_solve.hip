@@ -866,8 +866,8 @@ __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
             asm volatile("ds_add_u32 %0, %1"
                          :: "v"((unsigned)(size_t)(__attribute__((address_space(3))) int *)&count), "v"(1)
                          : "memory");
-        if (wave == 0)      // (see sweep_step)
-            __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], seen, __ATOMIC_RELAXED,
+        if (wave == 0)      // the slice it is at (see sweep_step)
+            __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], sl - s0, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_WORKGROUP);
         level_of(nx);
         sl += BNW;
@@ -934,8 +934,8 @@ struct SweepArgs {
     const int *lcol, *ucol;      // main entries: slice, lane, pair; overflow as in RasRow
     const T *lval, *uval, *dinv, *rl;
     T *y;
-    int *prog;                   // PROG_STRIDE ns: slices finished by each sweep (forward, then
-                                 // backward), one counter per 256 bytes
+    int *prog;                   // PROG_STRIDE ns: slice each sweep is at (forward, then backward),
+                                 // one counter per 256 bytes
     int ns;                      // subdomains (sweep workgroups)
     int nhelp;                   // prefetch workgroups per subdomain (workgroups ns .. ns (1 + nhelp))
 };
@@ -1189,12 +1189,17 @@ __device__ __forceinline__ void sweep_step(const SweepArgs<T> &A, T *ring, int *
     load_cols<T, FWD>(C[U], A, sl4, lane);
     load_task<T, FWD>(cur, A, task_slice<FWD, NCW>(sa, sb, wave, k + 2, nt),
                       __builtin_amdgcn_readlane(M[(U + 2) & 3], 1), lane);
-    // a store the helpers poll.  Workgroup scope is enough: it goes through to
-    // the XCD's L2, where the helpers' polls read, and nothing of the sweep's
-    // results depends on when they see it.
+    // a store the helpers poll: the slice this wavefront is at, which moves on
+    // inside a level too and ends less than NCW slices before the last one, so
+    // that no helper waits for a sweep that is over.  (The count a level waits
+    // for stands still while a level runs: level 0 of a rough pressure field has
+    // thousands of rows, and with it the helpers of its last slices ran into
+    // their spin bound, over 14 ms a chunk.)  Workgroup scope is enough: it goes
+    // through to the XCD's L2, where the helpers' polls read, and nothing of the
+    // sweep's results depends on when they see it.
     if (wave == 0)
-        __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], seen, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(&A.prog[PROG_STRIDE * blockIdx.x], (FWD ? 0 : sb - sa) + NCW * k,
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -1235,12 +1240,12 @@ __device__ __forceinline__ void sweep_dir(const SweepArgs<T> &A, T *ring, int *c
 
 // ------------------------------------------------------- prefetch helpers
 constexpr int PCH = 8;            // slices per helper chunk
-constexpr int PDS = 128;          // slices a chunk is read ahead of the sweep (about 0.8 MB)
+constexpr int PDS = 128;          // slices (at least Sweep<T>::ncw) a chunk is read ahead of the sweep (about 0.8 MB)
 constexpr int MAX_HELP = 8;       // helper workgroups per subdomain
 
 // Helper j of subdomain s, one direction: chunks j, j + H, ... of PCH
-// slices in the sweep's order; each waits (bounded) until the sweep has
-// finished all but PDS of the slices before it, then reads the chunk's
+// slices in the sweep's order; each waits (bounded) until the sweep is at
+// most PDS slices behind it, then reads the chunk's
 // metadata, columns, factor blocks and right-hand side (backward: the forward
 // result and the inverse diagonal blocks).
 template <class T, bool FWD>
@@ -1259,7 +1264,7 @@ __device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int
             for (int spin = 0; spin < PSPIN; spin++) {
                 int pr = __hip_atomic_load(&A.prog[PROG_STRIDE * s], __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
-                // slices the sweep has finished in this direction
+                // the slice the sweep is at in this direction
                 int done = FWD ? pr : max(pr - nsl, -1);
                 if (i0 - done <= PDS) break;
                 __builtin_amdgcn_s_sleep(8);
