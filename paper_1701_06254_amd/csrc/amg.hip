@@ -239,7 +239,12 @@ __global__ void k_iota(int n, int *a) {
 // Member lists (CSR) of the aggregates, ascending within each list: every row
 // takes a slot of its aggregate (in no fixed order), and its place in the list
 // is then the number of smaller members.  Lists are a few rows long, so this
-// costs a few reads per row where a sort by aggregate takes three passes.
+// costs a few reads per row where a sort by aggregate takes three passes.  The
+// reads grow with the square of a list's length, and one matching round can
+// leave a hub that thousands of rows join: a list of more than FEW members is
+// reported in *hub (a pinned word, zeroed by the host) and left out, and the
+// host has all lists sorted (k_member_keys).
+constexpr int FEW = 1024;
 __global__ void k_member_slot(int n, const int *agg, int *cnt, int *slot) {
     int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) slot[i] = atomicAdd(&cnt[agg[i]], 1);
@@ -250,12 +255,22 @@ __global__ void k_member_fill(int n, const int *agg, const int *mptr, const int 
     if (i < n) list[mptr[agg[i]] + slot[i]] = i;
 }
 
-__global__ void k_member_order(int n, const int *agg, const int *mptr, const int *list, int *mem) {
+__global__ void k_member_order(int n, const int *agg, const int *mptr, const int *list, int *mem,
+                               int *hub) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
     int i = list[t], I = agg[i], a = mptr[I], b = mptr[I + 1], r = a;
+    if (b - a > FEW) {
+        if (t == a) *hub = 1;
+        return;
+    }
     for (int k = a; k < b; k++) r += list[k] < i;
     mem[r] = i;
+}
+
+__global__ void k_member_keys(int n, const int *agg, unsigned *key, unsigned *val) {
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) { key[i] = (unsigned)agg[i]; val[i] = (unsigned)i; }
 }
 
 // ------------------------------------------------------------- Galerkin
@@ -269,7 +284,12 @@ __global__ void k_member_order(int n, const int *agg, const int *mptr, const int
 // dozen times (13.9 million terms: 1.9 ms, 0.5 ms so).
 //
 // A group of GL lanes takes a coarse row of up to GL members and GE terms;
-// longer ones go on a list and take a workgroup each (k_gal_long).
+// longer ones go on a list and take a workgroup each (k_gal_long).  Comparing
+// all terms of a row grows with their square: a product with a row of more than
+// FEW terms, which takes very strong contrasts or one matching round, is
+// reported in *hub, nothing of it is merged, and the host has all its terms
+// sorted (k_gal_expand).  (One matching round at 2M cells leaves a row of 930,916
+// terms.)
 constexpr int GL = 16;
 constexpr int GE = 64;
 constexpr int NO_COL = 0x7fffffff;
@@ -280,9 +300,8 @@ struct GalArgs {
     int *rpc;                    // counting: entries of every coarse row; then their starts
     int *colc;
     double *valc;
-    int *list, *nlist;           // long rows; their number, and terms of freaks placed (counting, merging)
-    int *xkey, *xfkey;           // freaks' terms
-    double *xval;
+    int *list, *nlist;           // long rows; their number
+    int *hub;                    // set if a row has more than FEW terms
 };
 
 // One of the group's terms per lane and slot, up to SL slots.
@@ -389,101 +408,159 @@ __global__ __launch_bounds__(256) void k_gal_rows(GalArgs A) {
     else gal_row<MERGE, GE / GL>(A, I, E, nf, l, key[g], val[MERGE ? g : 0]);
 }
 
-// A long row's terms (E of them, from m members) compared with one another by
-// a workgroup; key, fkey and val hold them.
-template <bool MERGE, class KEY, class VAL>
-__device__ __forceinline__ void gal_long_row(const GalArgs &A, int I, int a, int m, int E, KEY key,
-                                             KEY fkey, VAL val, int (*mem)[256], int *part) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    // the terms, 256 members at a time: each member's first term, stored entry
-    // and length, then 16 lanes copy a member's
-    int off = 0;
-    for (int t0 = 0; t0 < m; t0 += 256) {
-        int t = t0 + tid, i = t < m ? A.mem[a + t] : 0;
-        int z0 = A.rp[i], len = t < m ? A.rp[i + 1] - z0 : 0, inc = len;
-        for (int d = 1; d < 64; d <<= 1) {
-            int u = __shfl_up(inc, d, 64);
-            if (lane >= d) inc += u;
+// The rows on the list, a workgroup each: their terms, in LDS, compared with
+// one another.  2M cells with a standard deviation of ln k of 2: up to 4,037
+// such rows a pass and up to 909 terms a row (of 1: 2,653 and 566; of 4: 3,545
+// and 1,670).
+template <bool MERGE>
+__global__ __launch_bounds__(256) void k_gal_long(GalArgs A) {
+    __shared__ int key[FEW], fkey[MERGE ? FEW : 1], mem[3][256], part[4];
+    __shared__ double val[MERGE ? FEW : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nl = A.nlist[0];
+    for (int q = blockIdx.x; q < nl; q += gridDim.x) {
+        const int I = A.list[q], a = A.mptr[I], m = A.mptr[I + 1] - a;
+        int E = FEW + 1;
+        if (m <= FEW) {              // (a longer member list is not there)
+            E = 0;
+            for (int t = tid; t < m; t += 256) E += A.rp[A.mem[a + t] + 1] - A.rp[A.mem[a + t]];
+            for (int d = 32; d > 0; d >>= 1) E += __shfl_xor(E, d, 64);
+            if (lane == 0) part[wv] = E;
+            __syncthreads();
+            E = part[0] + part[1] + part[2] + part[3];
+            __syncthreads();
         }
-        if (lane == 63) part[wv] = inc;
-        __syncthreads();
-        int st = off + inc - len;
-        for (int w = 0; w < 4; w++) {
-            st += w < wv ? part[w] : 0;
-            off += part[w];
-        }
-        mem[0][tid] = st;
-        mem[1][tid] = z0;
-        mem[2][tid] = len;
-        __syncthreads();
-        for (int q = tid / 16; q < min(m - t0, 256); q += 16)
-            for (int k = tid % 16; k < mem[2][q]; k += 16) {
-                int z = mem[1][q] + k;
-                key[mem[0][q] + k] = A.agg[A.col[z]];
-                if (MERGE) val[mem[0][q] + k] = A.val[z];
+        if (E > FEW) {
+            if (tid == 0) {
+                *A.hub = 1;
+                A.rpc[I] = 0;
             }
-        __syncthreads();
-    }
-    int cnt = 0;
-    for (int e = tid; e < E; e += 256) {
-        const int k = key[e];
-        unsigned first = 1;
-#pragma unroll 8
-        for (int f = 0; f < e; f++) first &= key[f] != k;
-        cnt += first;
-        if (MERGE) fkey[e] = first ? k : NO_COL;
-    }
-    if (!MERGE) {
-        for (int d = 32; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
-        if (lane == 0) part[wv] = cnt;
-        __syncthreads();
-        if (tid == 0) A.rpc[I] = part[0] + part[1] + part[2] + part[3];
-        return;
-    }
-    __syncthreads();
-    const int base = A.rpc[I];
-    for (int e = tid; e < E; e += 256) {
-        const int k = fkey[e];
-        if (k == NO_COL) continue;
-        int rank = 0;
-        double sum = 0.0;
-#pragma unroll 8
-        for (int f = 0; f < E; f++) {
-            rank += fkey[f] < k;
-            sum += key[f] == k ? val[f] : 0.0;
+            continue;
         }
-        A.colc[base + rank] = k;
-        A.valc[base + rank] = sum;
+        // the terms, 256 members at a time: each member's first term, stored
+        // entry and length, then 16 lanes copy a member's
+        int off = 0;
+        for (int t0 = 0; t0 < m; t0 += 256) {
+            int t = t0 + tid, i = t < m ? A.mem[a + t] : 0;
+            int z0 = A.rp[i], len = t < m ? A.rp[i + 1] - z0 : 0, inc = len;
+            for (int d = 1; d < 64; d <<= 1) {
+                int u = __shfl_up(inc, d, 64);
+                if (lane >= d) inc += u;
+            }
+            if (lane == 63) part[wv] = inc;
+            __syncthreads();
+            int st = off + inc - len;
+            for (int w = 0; w < 4; w++) {
+                st += w < wv ? part[w] : 0;
+                off += part[w];
+            }
+            mem[0][tid] = st;
+            mem[1][tid] = z0;
+            mem[2][tid] = len;
+            __syncthreads();
+            for (int r = tid / 16; r < min(m - t0, 256); r += 16)
+                for (int k = tid % 16; k < mem[2][r]; k += 16) {
+                    int z = mem[1][r] + k;
+                    key[mem[0][r] + k] = A.agg[A.col[z]];
+                    if (MERGE) val[mem[0][r] + k] = A.val[z];
+                }
+            __syncthreads();
+        }
+        int cnt = 0;
+        for (int e = tid; e < E; e += 256) {
+            const int k = key[e];
+            unsigned first = 1;
+#pragma unroll 8
+            for (int f = 0; f < e; f++) first &= key[f] != k;
+            cnt += first;
+            if (MERGE) fkey[e] = first ? k : NO_COL;
+        }
+        if (!MERGE) {
+            for (int d = 32; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
+            if (lane == 0) part[wv] = cnt;
+            __syncthreads();
+            if (tid == 0) A.rpc[I] = part[0] + part[1] + part[2] + part[3];
+            __syncthreads();
+            continue;
+        }
+        __syncthreads();
+        const int base = A.rpc[I];
+        for (int e = tid; e < E; e += 256) {
+            const int k = fkey[e];
+            if (k == NO_COL) continue;
+            int rank = 0;
+            double sum = 0.0;
+#pragma unroll 8
+            for (int f = 0; f < E; f++) {
+                rank += fkey[f] < k;
+                sum += key[f] == k ? val[f] : 0.0;
+            }
+            A.colc[base + rank] = k;
+            A.valc[base + rank] = sum;
+        }
+        __syncthreads();
     }
 }
 
-// The rows on the list, a workgroup each.  Up to GCH terms (all but freaks: a
-// few hundred at most at 8 million cells) stay in LDS, more take their part of
-// arrays as long as all terms.
-constexpr int GCH = 1024;
-template <bool MERGE>
-__global__ __launch_bounds__(256) void k_gal_long(GalArgs A) {
-    __shared__ int key[GCH], fkey[MERGE ? GCH : 1], mem[3][256], part[4], base;
-    __shared__ double val[MERGE ? GCH : 1];
-    const int tid = threadIdx.x, nl = A.nlist[0];
-    for (int q = blockIdx.x; q < nl; q += gridDim.x) {
-        const int I = A.list[q], a = A.mptr[I], m = A.mptr[I + 1] - a;
-        int E = 0;
-        for (int t = tid; t < m; t += 256) E += A.rp[A.mem[a + t] + 1] - A.rp[A.mem[a + t]];
-        for (int d = 32; d > 0; d >>= 1) E += __shfl_xor(E, d, 64);
-        if ((tid & 63) == 0) part[tid >> 6] = E;
-        __syncthreads();
-        E = part[0] + part[1] + part[2] + part[3];
-        __syncthreads();
-        if (E <= GCH) {
-            gal_long_row<MERGE>(A, I, a, m, E, key, fkey, val, mem, part);
-        } else {
-            if (tid == 0) base = atomicAdd(&A.nlist[MERGE ? 2 : 1], E);
-            __syncthreads();
-            gal_long_row<MERGE>(A, I, a, m, E, A.xkey + base, A.xfkey + base, A.xval + base, mem, part);
-        }
-        __syncthreads();
+// The product by sorting all terms, stably by coarse column and then by coarse
+// row: equal (I, J) terms stay in ascending (row, stored column) order, and are
+// summed in that order.
+__global__ void k_gal_expand(int n, const int *rp, const int *agg, unsigned *keyI, const int *col,
+                             unsigned *keyJ, unsigned *idx) {
+    int i, g;
+    row_group(n, i, g);
+    if (i >= n) return;
+    unsigned I = (unsigned)agg[i];
+    for (int z = rp[i] + g; z < rp[i + 1]; z += GS) {
+        keyI[z] = I;
+        keyJ[z] = (unsigned)agg[col[z]];
+        idx[z] = (unsigned)z;
     }
+}
+
+__global__ void k_gather_u(int m, const unsigned *idx, const unsigned *src, unsigned *dst) {
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < m) dst[k] = src[idx[k]];
+}
+
+// keyI, keyJ: the terms' coarse rows and columns in sorted order.
+__device__ __forceinline__ bool first_of_run(int k, const unsigned *keyI, const unsigned *keyJ) {
+    return k == 0 || keyI[k] != keyI[k - 1] || keyJ[k] != keyJ[k - 1];
+}
+__global__ void k_gal_flags(int m, const unsigned *keyI, const unsigned *keyJ, int *flag) {
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < m) flag[k] = first_of_run(k, keyI, keyJ);
+}
+
+// The first term of every run of equal (I, J) records where its run starts;
+// the run of output entry u is then [start[u], start[u + 1]).
+__global__ void k_gal_runs(int m, int nc, const unsigned *keyI, const unsigned *keyJ,
+                           const int *uidx, int *start, int *rpc, int nnzc) {
+    int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k == 0) { rpc[nc] = nnzc; start[nnzc] = m; }
+    if (k >= m || !first_of_run(k, keyI, keyJ)) return;
+    start[uidx[k]] = k;
+    if (k == 0 || keyI[k - 1] != keyI[k]) rpc[keyI[k]] = uidx[k];
+}
+
+// One thread per coarse entry, four terms' loads in flight at a time.
+__global__ void k_gal_sum(int nnzc, const int *start, const unsigned *idx, const unsigned *keyJ,
+                          const double *val, int *colc, double *valc) {
+    int u = blockIdx.x * blockDim.x + threadIdx.x;
+    if (u >= nnzc) return;
+    int a = start[u], b = start[u + 1];
+    double s = 0.0;
+    int t = a;
+    for (; t + 4 <= b; t += 4) {
+        unsigned i0 = idx[t], i1 = idx[t + 1], i2 = idx[t + 2], i3 = idx[t + 3];
+        double v0 = val[i0], v1 = val[i1], v2 = val[i2], v3 = val[i3];
+        s += v0;
+        s += v1;
+        s += v2;
+        s += v3;
+    }
+    for (; t < b; t++) s += val[idx[t]];
+    colc[u] = (int)keyJ[a];
+    valc[u] = s;
 }
 
 __global__ void k_l1(int n, const int *rp, const double *val, double *l1) {
@@ -867,10 +944,22 @@ static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
 // --------------------------------------------------------------- set-up
 // Everything runs in order on one stream; the host waits only where it
 // needs a count (the scans that return totals) and for the final status.
+// The pinned word that kernels set for a list or row of more than FEW entries
+// (beside the one that takes the scans' totals), cleared; the stream is idle for
+// it when the host has waited for a scan.
+static int hub_word(r2p_cpr *P, volatile int *&hub) {
+    R2P_TRY(P->apin.ensure(64));
+    hub = (volatile int *)P->apin.p + 8;
+    *hub = 0;
+    return 0;
+}
+
 // Member lists (CSR, ascending) of the nc aggregates of agg[0..n); uses two
-// scratch arrays of n.
+// scratch arrays of n.  With *hub set, which the host sees after its next wait,
+// only mptr is there (see sort_members).
 static int build_members(r2p_cpr *P, int n, const int *agg, int nc, DBuf<int> &mptr,
-                         DBuf<int> &mem, DBuf<int> &slot, DBuf<int> &list, hipStream_t s) {
+                         DBuf<int> &mem, DBuf<int> &slot, DBuf<int> &list, volatile int *hub,
+                         hipStream_t s) {
     R2P_TRY(mptr.ensure(nc + 1));
     R2P_TRY(mem.ensure(n));
     R2P_TRY(slot.ensure(n));
@@ -882,8 +971,59 @@ static int build_members(r2p_cpr *P, int n, const int *agg, int nc, DBuf<int> &m
     R2P_TRY(r2p_scan_int(mptr.p, mptr.p, nc + 1, nullptr, P->aiscratch, P->apin, s));
     k_member_fill<<<nb, BS, 0, s>>>(n, agg, mptr.p, slot.p, list.p);
     R2P_LAUNCH();
-    k_member_order<<<nb, BS, 0, s>>>(n, agg, mptr.p, list.p, mem.p);
+    k_member_order<<<nb, BS, 0, s>>>(n, agg, mptr.p, list.p, mem.p, (int *)hub);
     R2P_LAUNCH();
+    return 0;
+}
+
+// The lists' members by a stable sort of the rows by aggregate.
+static int sort_members(r2p_cpr *P, int n, const int *agg, int nc, DBuf<int> &mem, hipStream_t s) {
+    SetupWork &W = P->aws;
+    DBuf<unsigned> &key = W.u[0], &kt = W.u[1], &vt = W.u[2];
+    R2P_TRY(key.ensure(n));
+    R2P_TRY(kt.ensure(n));
+    R2P_TRY(vt.ensure(n));
+    unsigned *val = (unsigned *)mem.p;
+    k_member_keys<<<r2p_blocks(n, BS), BS, 0, s>>>(n, agg, key.p, val);
+    R2P_LAUNCH();
+    return r2p_sort_pairs(key.p, val, kt.p, vt.p, n, r2p_bits_for(nc), W.i[0], P->aiscratch,
+                          P->apin, s);
+}
+
+// The product by sorting its terms.
+static int galerkin_sorted(r2p_cpr *P, int n, int nnz, const int *rp, const int *col,
+                           const double *val, const int *agg, int nc, DBuf<int> &rpc,
+                           DBuf<int> &colc, DBuf<double> &valc, int *nnzc, hipStream_t s) {
+    SetupWork &W = P->aws;
+    DBuf<unsigned> &keyI = W.u[0], &keyJ = W.u[1], &keyS = W.u[2], &idx = W.u[3], &kt = W.u[4],
+                   &vt = W.u[5];
+    DBuf<int> &flag = W.i[0], &hist = W.i[1], &start = W.i[2];
+    for (DBuf<unsigned> *b : {&keyI, &keyJ, &keyS, &idx, &kt, &vt}) R2P_TRY(b->ensure(nnz));
+    R2P_TRY(flag.ensure(nnz + 1));
+    k_gal_expand<<<r2p_blocks(n, BS / GS), BS, 0, s>>>(n, rp, agg, keyI.p, col, keyJ.p, idx.p);
+    R2P_LAUNCH();
+    const int bits = r2p_bits_for(nc), nb = r2p_blocks(nnz, BS);
+    R2P_HIP(hipMemcpyAsync(keyS.p, keyJ.p, sizeof(unsigned) * (size_t)nnz, hipMemcpyDeviceToDevice, s));
+    R2P_TRY(r2p_sort_pairs(keyS.p, idx.p, kt.p, vt.p, nnz, bits, hist, P->aiscratch, P->apin, s));
+    k_gather_u<<<nb, BS, 0, s>>>(nnz, idx.p, keyI.p, keyS.p);
+    R2P_LAUNCH();
+    R2P_TRY(r2p_sort_pairs(keyS.p, idx.p, kt.p, vt.p, nnz, bits, hist, P->aiscratch, P->apin, s));
+    // the coarse columns in sorted order (kt is free again)
+    k_gather_u<<<nb, BS, 0, s>>>(nnz, idx.p, keyJ.p, kt.p);
+    R2P_LAUNCH();
+    k_gal_flags<<<nb, BS, 0, s>>>(nnz, keyS.p, kt.p, flag.p);
+    R2P_LAUNCH();
+    R2P_HIP(hipMemsetAsync(flag.p + nnz, 0, sizeof(int), s));
+    int nnz_c = 0;
+    R2P_TRY(r2p_scan_int(flag.p, flag.p, nnz + 1, &nnz_c, P->aiscratch, P->apin, s));
+    R2P_TRY(colc.ensure(nnz_c));
+    R2P_TRY(valc.ensure(nnz_c));
+    R2P_TRY(start.ensure(nnz_c + 1));
+    k_gal_runs<<<nb, BS, 0, s>>>(nnz, nc, keyS.p, kt.p, flag.p, start.p, rpc.p, nnz_c);
+    R2P_LAUNCH();
+    k_gal_sum<<<r2p_blocks(nnz_c, BS), BS, 0, s>>>(nnz_c, start.p, idx.p, kt.p, val, colc.p, valc.p);
+    R2P_LAUNCH();
+    *nnzc = nnz_c;
     return 0;
 }
 
@@ -892,22 +1032,20 @@ static int galerkin(r2p_cpr *P, int n, int nnz, const int *rp, const int *col, c
                     int *nnzc, hipStream_t s) {
     SetupWork &W = P->aws;
     DBuf<int> &mptr = W.i[0], &mem = W.i[1], &slot = W.i[2], &list = W.i[3];
-    DBuf<unsigned> &xkey = W.u[0], &xfkey = W.u[1], &longs = W.u[2], &nlong = W.u[3];
-    DBuf<double> &xval = W.d[1];              // the pass's weights, no longer needed
-    R2P_TRY(build_members(P, n, agg, nc, mptr, mem, slot, list, s));
-    R2P_TRY(xkey.ensure(nnz));
-    R2P_TRY(xfkey.ensure(nnz));
-    R2P_TRY(xval.ensure(nnz));
+    DBuf<unsigned> &longs = W.u[0], &nlong = W.u[1];
+    volatile int *hub;
+    R2P_TRY(hub_word(P, hub));
+    R2P_TRY(build_members(P, n, agg, nc, mptr, mem, slot, list, hub, s));
     R2P_TRY(longs.ensure(nc));
-    R2P_TRY(nlong.ensure(3));
+    R2P_TRY(nlong.ensure(1));
     R2P_TRY(rpc.ensure(nc + 1));
-    R2P_HIP(hipMemsetAsync(nlong.p, 0, 3 * sizeof(int), s));
+    R2P_HIP(hipMemsetAsync(nlong.p, 0, sizeof(int), s));
     GalArgs A;
     A.nc = nc;
     A.mptr = mptr.p; A.mem = mem.p; A.rp = rp; A.col = col; A.agg = agg; A.val = val;
     A.rpc = rpc.p; A.colc = nullptr; A.valc = nullptr;
     A.list = (int *)longs.p; A.nlist = (int *)nlong.p;
-    A.xkey = (int *)xkey.p; A.xfkey = (int *)xfkey.p; A.xval = xval.p;
+    A.hub = (int *)hub;
     const int nb = r2p_blocks(nc, 256 / GL), nl = std::min(nc, 1024);
     k_gal_rows<false><<<nb, 256, 0, s>>>(A);
     R2P_LAUNCH();
@@ -915,6 +1053,7 @@ static int galerkin(r2p_cpr *P, int n, int nnz, const int *rp, const int *col, c
     R2P_LAUNCH();
     int nnz_c = 0;
     R2P_TRY(r2p_scan_int(rpc.p, rpc.p, nc + 1, &nnz_c, P->aiscratch, P->apin, s));
+    if (*hub) return galerkin_sorted(P, n, nnz, rp, col, val, agg, nc, rpc, colc, valc, nnzc, s);
     R2P_TRY(colc.ensure(nnz_c));
     R2P_TRY(valc.ensure(nnz_c));
     A.colc = colc.p; A.valc = valc.p;
@@ -1042,8 +1181,12 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
         if (nc >= A.n) break;   // no coarsening progress
         C.n = nc;
         C.nnz = nnzc;
-        R2P_TRY(build_members(P, A.n, A.agg.p, nc, A.mptr, A.mem, P->aws.i[0], P->aws.i[1], s));
+        volatile int *hub;
+        R2P_TRY(hub_word(P, hub));
+        R2P_TRY(build_members(P, A.n, A.agg.p, nc, A.mptr, A.mem, P->aws.i[0], P->aws.i[1], hub, s));
         R2P_TRY(long_rows(P, nc, A.mptr.p, BIG, A.big, &A.nbig, s));
+        A.hub = *hub != 0;
+        if (A.hub) R2P_TRY(sort_members(P, A.n, A.agg.p, nc, A.mem, s));
         R2P_TRY(long_rows(P, nc, C.rp.p, HEAVY, C.heavy, &C.nheavy, s));
         l++;
     }
@@ -1118,7 +1261,8 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
 // fused (its largest, 82,086 rows, takes the same either way).  At 2M cells
 // fusing the levels of 780,824 and 259,434 rows as well makes a solve 7%
 // slower: such levels are bound by memory, and a fused kernel reads the rows
-// in the order of the aggregates and gathers two vectors.
+// in the order of the aggregates and gathers two vectors.  Nor are levels with an
+// aggregate of more than FEW members, whose rows one workgroup would take.
 constexpr int FUSE_ROWS = 1 << 15;
 
 template <class T>
@@ -1699,7 +1843,8 @@ struct Cycle {
         AmgLevel &C = P->lv[c + 1];
         const bool kc = c < P->o.kcycle && c + 1 < nl - 1;
         const bool smooth = c + 1 < nl - 1;
-        if (A.n <= FUSE_ROWS) {
+        const bool fuse = A.n <= FUSE_ROWS && !A.hub;
+        if (fuse) {
             int nbs = r2p_blocks(C.n, CB);
             k_down_restrict<T><<<nbs + A.nbig, BS, 0, s>>>(
                 csr(A, vx(A), nullptr), C.n, nbs, A.mptr.p, A.mem.p, A.big.p, vb(C),
@@ -1710,7 +1855,7 @@ struct Cycle {
             R2P_TRY(csr_launch<CSR_DOWN>(A, vx(A), vxo(A)));
             R2P_TRY(restrict_to(c));
         }
-        if (A.n > FUSE_ROWS || kc) {
+        if (!fuse || kc) {
             R2P_TRY(correct(c));
             return csr_launch<CSR_UP>(A, vx(A), out);
         }
