@@ -1583,6 +1583,9 @@ __global__ __launch_bounds__(64 * CS_WAVES, 1) void k_coarse_solve(int n, const 
     // the wavefront's part of b, zeros behind it
     for (int c = lane; c < cnt + CS_COLS; c += 64)
         rhs[w][c] = c < cnt ? (f ? f[(long)fstride * (c0 + c)] : (double)b[c0 + c]) : 0.0;
+    // written by some lanes, read by others of the same wavefront, whose LDS
+    // operations keep order
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     double s = 0.0, v[CS_COLS];
     const double *col = invT + (long)c0 * n;
     for (int c = 0; c < cnt; c += CS_COLS) {
