@@ -219,7 +219,6 @@ struct RasDyn {
     DBuf<int> lsw, usw;                   // the same for the sweep, with each column's source of y
     DBuf<int> lsrc, usrc;                 // entries: block source (set-up only)
     DBuf<int> dsrc_pos;                   // npos: diagonal block source per position
-    DBuf<double> tval;                    // L entries (p, q): A_qp, laid out as the factors (set-up only)
     DBuf<int> ldiag;                      // L entries: entry of U_qp in row q (set-up only)
     DBuf<int> xptr;                       // npos+1: extra ILU(0) matches per position
     DBuf<int4> xl;                        // extra matches (set-up only)
@@ -275,7 +274,12 @@ struct Krylov;
 
 struct r2p_cpr {
     r2p_cpr_opts o{};
-    Krylov *kry = nullptr;   // Krylov basis and work vectors of the solves with this handle
+    Krylov *kry = nullptr;   // work vectors of the solves with this handle
+    // The Krylov basis of a solve, which has no content between solves.  During
+    // the set-up of the factors it holds A_qp of every L entry (p, q), laid out
+    // as the factors: 32 bytes an entry, 0.3 GB at 2M cells and 9 GB at 65.5M,
+    // less than the basis for restarts of 10 and more.
+    DBuf<double> basis;
     SetupWork ws;
     r2p_jacobian *J = nullptr;
     int ready = 0;

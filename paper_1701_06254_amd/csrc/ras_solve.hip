@@ -1543,8 +1543,8 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     F.nl = D.nl.p; F.nu = D.nu.p;
     F.dsrc = D.dsrc_pos.p; F.lsrc = D.lsrc.p; F.usrc = D.usrc.p;
     F.lcol = D.lcol.p; F.ucol = D.ucol.p;
-    R2P_TRY(D.tval.ensure(4 * (size_t)nle));
-    F.tval = D.tval.p;
+    R2P_TRY(P->basis.ensure(4 * (size_t)nle));
+    F.tval = P->basis.p;
     F.lval = D.f64.lval.p; F.uval = D.f64.uval.p; F.dinv = D.f64.dinv.p; F.status = P->status.p;
     R2P_TRY(D.xptr.ensure(npos + 1));
     R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)nle, s));

@@ -299,7 +299,7 @@ __global__ void k_undecouple(int n, long N, const double4 *dec, const double *rd
 }
 
 struct Krylov {
-    DBuf<double> V, Z, part, h, r, bd, w;
+    DBuf<double> Z, part, h, r, bd, w;   // (the basis itself: r2p_cpr::basis)
     HostPinned pin;
     double *pin_dev = nullptr;        // device address of pin
     long N = 0;
@@ -547,8 +547,8 @@ static int solve_bicgstab(r2p_jacobian *J, r2p_cpr *P, Krylov &K, double bnorm, 
                           hipStream_t s) {
     const Phys &ph = J->m->ph;
     long N = 2L * (ph.n + ph.nw);
-    R2P_TRY(K.V.ensure((size_t)8 * N));
-    double *r = K.V.p, *rh = r + N, *p = rh + N, *v = p + N, *pp = v + N, *sv = pp + N,
+    R2P_TRY(P->basis.ensure((size_t)8 * N));
+    double *r = P->basis.p, *rh = r + N, *p = rh + N, *v = p + N, *pp = v + N, *sv = pp + N,
            *sp = sv + N, *t = sp + N;
     int nb = r2p_blocks(N, BS);
     R2P_HIP(hipMemcpyAsync(r, K.bd.p, sizeof(double) * N, hipMemcpyDeviceToDevice, s));
@@ -635,7 +635,7 @@ extern "C" int r2p_solve(r2p_jacobian *J, r2p_cpr *P, const double *b, double *y
     long N = 2L * (ph.n + ph.nw);
     int m = o->restart;
     Krylov &K = krylov_for(P);
-    R2P_TRY(K.V.ensure((size_t)(m + 1) * N));
+    R2P_TRY(P->basis.ensure((size_t)(m + 1) * N));
     R2P_TRY(K.Z.ensure((size_t)m * N));
     R2P_TRY(K.r.ensure(N));
     R2P_TRY(K.bd.ensure(N));
@@ -689,20 +689,20 @@ extern "C" int r2p_solve(r2p_jacobian *J, r2p_cpr *P, const double *b, double *y
             return true;
         };
         while (total < o->maxit) {
-            k_mupdate<<<nblk, BS, 0, s>>>(nullptr, N, 0, K.h.p, K.r.p, N, 1.0 / beta, K.V.p);
+            k_mupdate<<<nblk, BS, 0, s>>>(nullptr, N, 0, K.h.p, K.r.p, N, 1.0 / beta, P->basis.p);
             R2P_LAUNCH();
             int k = 0;
             bool stop = false;
             for (int j = 0; j < m && total < o->maxit; j++) {
-                double *vj = K.V.p + (size_t)j * N, *zj = K.Z.p + (size_t)j * N;
-                double *w = K.V.p + (size_t)(j + 1) * N;
+                double *vj = P->basis.p + (size_t)j * N, *zj = K.Z.p + (size_t)j * N;
+                double *w = P->basis.p + (size_t)(j + 1) * N;
                 R2P_TRY(r2p_cpr_apply_impl(P, vj, zj, s));
                 R2P_TRY(r2p_spmv_impl(J, zj, w, nullptr, s));
                 double hh[MAXV], hn;
                 if (delayed) {
                     // t = V^T w, w.w, q = V^T v_j in one pass
                     double gv[MAXG];
-                    R2P_TRY(mdot2(K, K.V.p, j + 1, w, N, s, gv));
+                    R2P_TRY(mdot2(K, P->basis.p, j + 1, w, N, s, gv));
                     const double *t = gv, *q = gv + j + 2;
                     double ww = gv[j + 1];
                     Coef2 c{};
@@ -730,28 +730,28 @@ extern "C" int r2p_solve(r2p_jacobian *J, r2p_cpr *P, const double *b, double *y
                     c.hj = hj;
                     c.inv_nj = 1.0 / nj;
                     c.inv_hn = hn > 0.0 ? 1.0 / hn : 0.0;
-                    k_mupdate2<<<nblk, BS, 0, s>>>(K.V.p, N, j, c, w, N, w);
+                    k_mupdate2<<<nblk, BS, 0, s>>>(P->basis.p, N, j, c, w, N, w);
                     R2P_LAUNCH();
                 } else {
-                    R2P_TRY(mdot(K, K.V.p, j + 1, w, N, s, hh));
+                    R2P_TRY(mdot(K, P->basis.p, j + 1, w, N, s, hh));
                     double ww = hh[j + 1], hs = 0.0;
                     for (int i = 0; i <= j; i++) hs += hh[i] * hh[i];
                     double wn2 = ww - hs;
                     if (wn2 > 0.49 * ww) {
                         hn = sqrt(wn2);
-                        k_mupdate<<<nblk, BS, 0, s>>>(K.V.p, N, j + 1, K.h.p, w, N, 1.0 / hn, w);
+                        k_mupdate<<<nblk, BS, 0, s>>>(P->basis.p, N, j + 1, K.h.p, w, N, 1.0 / hn, w);
                         R2P_LAUNCH();
                     } else {
                         // second Gram-Schmidt pass
                         inf.reorth++;
                         double h2[MAXV];
-                        R2P_TRY(mdot(K, K.V.p, j + 1, w, N, s, h2, K.h.p));
+                        R2P_TRY(mdot(K, P->basis.p, j + 1, w, N, s, h2, K.h.p));
                         double hs2 = 0.0;
                         for (int i = 0; i <= j; i++) { hh[i] += h2[i]; hs2 += h2[i] * h2[i]; }
                         double wn = h2[j + 1] - hs2;
                         hn = wn > 0.0 ? sqrt(wn) : 0.0;
                         if (hn > 0.0) {
-                            k_mupdate<<<nblk, BS, 0, s>>>(K.V.p, N, j + 1, K.h.p, w, N, 1.0 / hn, w);
+                            k_mupdate<<<nblk, BS, 0, s>>>(P->basis.p, N, j + 1, K.h.p, w, N, 1.0 / hn, w);
                             R2P_LAUNCH();
                         }
                     }
