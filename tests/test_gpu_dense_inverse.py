@@ -43,3 +43,38 @@ def test_single_level_cycle_is_the_dense_solve(nx, ny, nz):
     ref = np.linalg.solve(A, f)
     tol = 4 * n * np.finfo(float).eps * np.linalg.cond(A)
     assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("nx,ny,nz", SIZES)
+def test_with_row_exchanges(nx, ny, nz):
+    """At a rough state A_pp is far from diagonally dominant: the LU exchanges
+    rows, also between panels, so positions and rows differ."""
+    import scipy.linalg as la
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1701_06254_amd import r2p
+    n = nx * ny * nz
+    w = workloads.make_tiny(nx, ny, nz)
+    w["wells"] = w["wells"][:1]
+    m = r2p.Model(w)
+    x = torch.as_tensor(workloads.random_state(w, np.random.default_rng(n), p_spread=50.0), device="cuda")
+    J = r2p.Jacobian(m)
+    J.assemble(x, x, 5.0)
+    P = r2p.Cpr().setup(J, r2p.cpr_opts(px=1, py=1, max_levels=1, max_coarse=2048))
+    L = P.amg_levels()
+    assert len(L) == 1 and L[0]["n"] == n
+    A = np.zeros((n, n))
+    rows = np.repeat(np.arange(n), np.diff(L[0]["rp"]))
+    A[rows, L[0]["col"]] = L[0]["val"]
+    piv, k = la.lu_factor(A)[1], np.arange(n)
+    if n > 30:
+        assert (piv != k).any()
+    width = 32 if n <= 1024 else (16 if n <= 2048 else 8)
+    if n > 2 * width:
+        assert (piv // width != k // width).any()
+    f = np.random.default_rng(n).standard_normal(n)
+    got = P.amg_vcycle(torch.as_tensor(f, device="cuda")).cpu().numpy()
+    ref = np.linalg.solve(A, f)
+    tol = 4 * n * np.finfo(float).eps * np.linalg.cond(A)
+    assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
