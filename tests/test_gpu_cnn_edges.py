@@ -85,3 +85,30 @@ def test_features_at_any_alignment(shape):
     shifted = torch.zeros(V * 32 + 1, dtype=torch.int16, device="cuda")
     shifted[1:] = f_t.reshape(-1)
     assert torch.equal(net.forward(shifted[1:], shape), ref)
+
+
+@pytest.mark.parametrize("shape", [(600, 1, 3, 2), (300, 3, 1, 2), (1, 50, 48, 97)])
+def test_weight_gradient_over_several_tiles(shape):
+    """More than twice as many tiles of 2 x 8 x 32 voxels as the device has
+    CUs: a workgroup requests its next tile while it works on one and carries
+    its sums across them, the last round uneven.  A sum is built in at most
+    this many FP32 additions one after another, each off by 2^-24 of the sum of
+    magnitudes: 32 products and one addition per row of a tile, the tiles of a
+    workgroup, then the workgroups in eighths."""
+    from oracle import cnn
+    from paper_1701_06254_amd import r2p
+    nb, nz, ny, nx = shape
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = nb * -(-nz // 2) * -(-ny // 8) * -(-nx // 32)
+    assert tiles > 2 * cus and tiles % cus
+    rng = np.random.default_rng(sum(shape))
+    g_t, g = _bits(rng.normal(size=shape + (32,)))
+    x_t, x = _bits(rng.normal(size=shape + (32,)))
+    dw = torch.full((27 * 32 * 32,), float("nan"), dtype=torch.float32, device="cuda")
+    db = torch.full((32,), float("nan"), dtype=torch.float32, device="cuda")
+    r2p.cnn_conv_dw(g_t, x_t, shape, dw, db)
+    chain = -(-tiles // cus) * 16 * 33 + cus // 8 + 8
+    for got, ref, mag in zip((dw, db), cnn.conv_grad_weight(g, x),
+                             cnn.conv_grad_weight(np.abs(g), np.abs(x))):
+        err = np.abs(got.cpu().numpy().astype(np.float64) - ref.reshape(-1))
+        assert np.all(err <= chain * 2.0 ** -24 * mag.reshape(-1))
