@@ -599,10 +599,10 @@ __global__ void k_to_dense(int n, const int *rp, const int *col, const double *v
 // ascending order, as the unblocked algorithm does, so the factors are the
 // same.
 // What bounds it: a chain of n pivot steps.  One workgroup doing the whole
-// matrix read it from L2 at every step (about 450 rows: 6.8 ms); with the
+// matrix read it from L2 at every step (about 400 rows: 6.8 ms); with the
 // panel in registers a step is one reduction, two barriers and at most NB
 // multiply-subtracts, and the rest of the matrix is updated once per panel by
-// the whole chip (the same matrix: 13 panels of 40 us, 12 updates of 22 us).
+// the whole chip (the same matrix: 13 panels of 41 us, 12 updates of 14 us).
 // The state of a panel workgroup: RPT rows per thread, their panel columns
 // from the current pivot's on in registers (column kk of the panel is r[q][0]
 // when its turn comes), and the rows' positions.
@@ -723,7 +723,7 @@ __global__ __launch_bounds__(T) void k_lu_panel(int n, int k0, double *a, double
 // Every wavefront solves the columns of U (unit lower triangle of the panel), a
 // column to a lane and all of it in registers (written to u by the first row
 // of workgroups), then subtracts the panel's multiples from its rows that are
-// still active.  About 450 rows: 22.5 us with U in LDS and each wavefront on 16
+// still active.  About 400 rows: 22.5 us with U in LDS and each wavefront on 16
 // of the columns, 14.4 us so.
 constexpr int LU_R = 32;
 template <int NB>
@@ -787,7 +787,7 @@ __global__ void k_lu_gather(int n, const double *a, const int *row, const int *s
 // taken in blocks of 64, so that the registers a row needs are fixed, and
 // requested AH rows before they are used.  What bounds it is the chain of
 // 2 n rows: a step is one row's products, one butterfly and one update (about
-// 450 rows: 0.20 ms; 1.0 ms with each row requested at its use and the
+// 400 rows: 0.20 ms; 1.0 ms with each row requested at its use and the
 // iterate in LDS, 0.28 ms with every register masked at every step, 0.39 ms
 // with two columns per wavefront).  Written column-major,
 // invT[c*n + i] = (A^-1)_ic, so the coarse solve reads it coalesced.
