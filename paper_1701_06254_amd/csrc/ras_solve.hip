@@ -447,7 +447,7 @@ struct FactArgs {
     double *tval;                // per L entry (p, q): A_qp
     int *status;
     int *prog;                   // as in SweepArgs, zeroed by k_bilu_gather
-    int ns, nhelp;
+    int ns, nsp, nhelp;          // as in SweepArgs
 };
 
 // Block k of a factor array.
@@ -678,22 +678,59 @@ __device__ __forceinline__ double2 row_prod(double2 l, double2 uh, double2 uo, b
 }
 
 constexpr int PSPIN = 1 << 16;    // bound of a helper's wait for its subdomain
-// Read one dword of every 128-byte line of [p, p + bytes) (all addresses
-// inside the range); the values are summed only so that the loads stay.
-__device__ __forceinline__ unsigned touch(const void *p, long bytes) {
-    if (bytes < 4) return 0;
-    const char *c = (const char *)p;
-    const char *line0 = (const char *)((unsigned long)c & ~127ul);
-    long last = (long)(c + bytes - 4 - line0);          // offset of the range's last dword
-    long lines = last / 128 + 1;
-    unsigned acc = 0;
-    for (long i = threadIdx.x; i < lines; i += blockDim.x) {
-        const char *a = line0 + i * 128;
-        a = a < c ? c : a;
-        a = a > c + bytes - 4 ? c + bytes - 4 : a;
-        acc += *(const unsigned *)((unsigned long)a & ~3ul);
+// Read one dword of every 128-byte line of N ranges, together, so that a chunk
+// costs one trip to memory; the values are summed only so that the loads stay.
+// The ranges lie in allocations aligned to a line, so the line of a range's
+// first byte starts inside its allocation.
+template <int N>
+struct Lines {
+    const char *p[N];
+    int n[N];
+    __device__ __forceinline__ void set(int k, const void *q, long bytes) {
+        p[k] = (const char *)((unsigned long)q & ~127ul);
+        n[k] = (int)(((const char *)q + bytes - 1 - p[k]) / 128) + 1;
     }
-    return acc;
+    __device__ __forceinline__ unsigned touch() const {
+        int total = 0;
+#pragma unroll
+        for (int k = 0; k < N; k++) total += n[k];
+        unsigned acc = 0;
+        for (int i = threadIdx.x; i < total; i += blockDim.x) {
+            const char *a = p[0] + 128l * i;
+            int r = i;
+#pragma unroll
+            for (int k = 0; k + 1 < N; k++)
+                if (r >= n[k]) {
+                    r -= n[k];
+                    a = p[k + 1] + 128l * r;
+                } else {
+                    r = -1;          // found: below every later count
+                }
+            acc += *(const unsigned *)a;
+        }
+        return acc;
+    }
+};
+
+// A helper's wait before it reads slices i0 .. i0 + m - 1 of its subdomain: until
+// the subdomain is at most `ahead` slices behind them.  One lane polls (the
+// word's line is written at every step), the workgroup waits for it.  False when
+// the subdomain is past them: a helper that is late goes on to the next chunk.
+__device__ __forceinline__ bool helper_wait(const int *prog, int from, int i0, int m, int ahead) {
+    __shared__ int at;
+    if (threadIdx.x == 0) {
+        int done = 0;
+        for (int spin = 0; spin < PSPIN; spin++) {
+            done = max(__hip_atomic_load(prog, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - from, -1);
+            if (i0 - done <= ahead) break;
+            __builtin_amdgcn_s_sleep(8);
+        }
+        at = done;
+    }
+    __syncthreads();
+    bool take = at < i0 + m;
+    __syncthreads();
+    return take;
 }
 
 // Helper j of H of subdomain s: reads the data of the slices up to BPD ahead of
@@ -705,38 +742,34 @@ __device__ unsigned bilu_prefetch(const FactArgs &A, int s, int j, int H) {
     for (int c = j; c * BPC < nsl; c += H) {
         const int i0 = c * BPC;
         const long f = s0 + i0, m = min(BPC, nsl - i0);
-        if (threadIdx.x == 0)
-            for (int spin = 0; spin < PSPIN; spin++) {
-                int done = __hip_atomic_load(&A.prog[PROG_STRIDE * s], __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_AGENT);
-                if (i0 - done <= BPD) break;
-                __builtin_amdgcn_s_sleep(8);
-            }
-        __syncthreads();
-        acc += touch(A.lcol + f * RAS_MENT, 4L * RAS_MENT * m);
-        acc += touch(A.ldiag + f * RAS_MENT, 4L * RAS_MENT * m);
-        acc += touch(A.lval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
-        acc += touch(A.tval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
-        acc += touch(A.dinv + 4 * f * RAS_ROWS, 32L * RAS_ROWS * m);
-        acc += touch(A.glob + f * RAS_ROWS, 4L * RAS_ROWS * m);
-        acc += touch(A.nl + f * RAS_ROWS, 4L * RAS_ROWS * m);
-        acc += touch(A.xptr + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        if (!helper_wait(&A.prog[PROG_STRIDE * s], 0, i0, (int)m, BPD)) continue;
+        Lines<8> l;
+        l.set(0, A.lval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
+        l.set(1, A.tval + 4 * f * RAS_MENT, 32L * RAS_MENT * m);
+        l.set(2, A.dinv + 4 * f * RAS_ROWS, 32L * RAS_ROWS * m);
+        l.set(3, A.lcol + f * RAS_MENT, 4L * RAS_MENT * m);
+        l.set(4, A.ldiag + f * RAS_MENT, 4L * RAS_MENT * m);
+        l.set(5, A.glob + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        l.set(6, A.nl + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        l.set(7, A.xptr + f * RAS_ROWS, 4L * RAS_ROWS * m);
+        acc += l.touch();
     }
     return acc;
 }
 
 __global__ __launch_bounds__(BWG) void k_bilu0(FactArgs A) {
     __shared__ int count;
-    if ((int)blockIdx.x >= A.ns) {
+    const int s = blockIdx.x % A.nsp, hj = (int)blockIdx.x / A.nsp - 1;
+    if (s >= A.ns) return;
+    if (hj >= 0) {
         // a helper, on its subdomain's XCD (see k_ras_sweep)
-        const int hb = blockIdx.x - A.ns;
-        unsigned acc = bilu_prefetch(A, hb % A.ns, hb / A.ns, A.nhelp);
+        unsigned acc = bilu_prefetch(A, s, hj, A.nhelp);
         if (A.nhelp < 0) A.prog[0] = (int)acc;     // never taken; keeps the reads
         return;
     }
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
-    const int s = blockIdx.x, nlev = A.nlev[s];
+    const int nlev = A.nlev[s];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const bool h = lane & 1;
     // scalar loads: a vector load's wait would be for all before it as well
@@ -940,7 +973,9 @@ struct SweepArgs {
     int *prog;                   // PROG_STRIDE ns: slice each sweep is at (forward, then backward),
                                  // one counter per 256 bytes
     int ns;                      // subdomains (sweep workgroups)
-    int nhelp;                   // prefetch workgroups per subdomain (workgroups ns .. ns (1 + nhelp))
+    int nsp, nhelp;              // ns to a multiple of 8; prefetch workgroups per subdomain: workgroup
+                                 // nsp (1 + j) + s is helper j of subdomain s
+    int ahead;                   // slices a helper reads ahead of its sweep
 };
 
 // LDS ring of the results of recently finished rows: position p sits in
@@ -1256,15 +1291,15 @@ __device__ __forceinline__ void sweep_dir(const SweepArgs<T> &A, T *ring, int *c
 }
 
 // ------------------------------------------------------- prefetch helpers
-constexpr int PCH = 8;            // slices per helper chunk
-constexpr int PDS = 128;          // slices (at least Sweep<T>::ncw) a chunk is read ahead of the sweep (about 0.8 MB)
+template <class T>
+constexpr int PCH = sizeof(T) == 4 ? 16 : 8;   // slices per helper chunk
 constexpr int MAX_HELP = 8;       // helper workgroups per subdomain
 
 // Helper j of subdomain s, one direction: chunks j, j + H, ... of PCH
 // slices in the sweep's order; each waits (bounded) until the sweep is at
-// most PDS slices behind it, then reads the chunk's
-// metadata, columns, factor blocks and right-hand side (backward: the forward
-// result and the inverse diagonal blocks).
+// most A.ahead slices behind it, then reads the chunk's metadata, columns,
+// factor blocks and right-hand side (backward: the forward result and the
+// inverse diagonal blocks), about 400 lines in one trip.
 template <class T, bool FWD>
 __device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int sa, int sb) {
     const int4 *meta = FWD ? A.mL : A.mU;
@@ -1272,27 +1307,17 @@ __device__ unsigned prefetch_dir(const SweepArgs<T> &A, int s, int j, int H, int
     const T *vals = FWD ? A.lval : A.uval;
     int nsl = sb - sa;
     unsigned acc = 0;
-    for (int c = j; c * PCH < nsl; c += H) {
-        int i0 = c * PCH, i1 = min(i0 + PCH, nsl);
-        long f = FWD ? sa + i0 : sb - i1, m = i1 - i0;       // lowest slice of the chunk, slices
-        // one lane polls (the counter's line is written at every step of the
-        // sweep), the workgroup waits for it
-        if (threadIdx.x == 0) {
-            for (int spin = 0; spin < PSPIN; spin++) {
-                int pr = __hip_atomic_load(&A.prog[PROG_STRIDE * s], __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                // the slice the sweep is at in this direction
-                int done = FWD ? pr : max(pr - nsl, -1);
-                if (i0 - done <= PDS) break;
-                __builtin_amdgcn_s_sleep(8);
-            }
-        }
-        __syncthreads();
-        acc += touch(meta + f, 16L * m);
-        acc += touch(cols + f * RAS_MENT, 4L * RAS_MENT * m);
-        acc += touch(vals + 4 * f * RAS_MENT, 4L * (long)sizeof(T) * RAS_MENT * m);
-        acc += touch((FWD ? A.rl : (const T *)A.y) + 2 * f * RAS_ROWS, 2L * (long)sizeof(T) * RAS_ROWS * m);
-        if (!FWD) acc += touch(A.dinv + 4 * f * RAS_ROWS, 4L * (long)sizeof(T) * RAS_ROWS * m);
+    for (int c = j; c * PCH<T> < nsl; c += H) {
+        int i0 = c * PCH<T>, i1 = min(i0 + PCH<T>, nsl), m = i1 - i0;
+        if (!helper_wait(&A.prog[PROG_STRIDE * s], FWD ? 0 : nsl, i0, m, A.ahead)) continue;
+        long f = FWD ? sa + i0 : sb - i1;       // lowest slice of the chunk
+        Lines<FWD ? 4 : 5> l;
+        l.set(0, vals + 4 * f * RAS_MENT, 4L * (long)sizeof(T) * RAS_MENT * m);
+        l.set(1, cols + f * RAS_MENT, 4L * RAS_MENT * m);
+        l.set(2, (FWD ? A.rl : (const T *)A.y) + 2 * f * RAS_ROWS, 2L * (long)sizeof(T) * RAS_ROWS * m);
+        l.set(3, meta + f, 16L * m);
+        if constexpr (!FWD) l.set(4, A.dinv + 4 * f * RAS_ROWS, 4L * (long)sizeof(T) * RAS_ROWS * m);
+        acc += l.touch();
     }
     return acc;
 }
@@ -1304,22 +1329,20 @@ __global__ __launch_bounds__(Sweep<T>::wg) void k_ras_sweep(SweepArgs<T> A) {
     constexpr int R = RingSize<T>::rows;
     __shared__ __attribute__((aligned(16))) T ring[2 * R];
     __shared__ int count;            // finished slices, forward then backward
-    if ((int)blockIdx.x >= A.ns) {
-        // a helper: subdomain (b - ns) mod ns, on the same XCD as its sweep
-        // (workgroup b goes to XCD b mod 8 and ns is a multiple of 8)
-        int hb = blockIdx.x - A.ns, hs = hb % A.ns;
-        int hn = A.nlev[hs], hbase = A.lbase[hs];
-        int hsa = A.soff[hbase], hsb = A.soff[hbase + hn];
-        unsigned acc = prefetch_dir<T, true>(A, hs, hb / A.ns, A.nhelp, hsa, hsb);
-        acc += prefetch_dir<T, false>(A, hs, hb / A.ns, A.nhelp, hsa, hsb);
+    const int s = blockIdx.x % A.nsp, hj = (int)blockIdx.x / A.nsp - 1;
+    if (s >= A.ns) return;
+    int nlev = A.nlev[s], base = A.lbase[s];
+    int sa = A.soff[base], sb = A.soff[base + nlev];
+    if (hj >= 0) {
+        // a helper, on the same XCD as its subdomain's sweep (workgroup b goes
+        // to XCD b mod 8, and nsp is a multiple of 8)
+        unsigned acc = prefetch_dir<T, true>(A, s, hj, A.nhelp, sa, sb);
+        acc += prefetch_dir<T, false>(A, s, hj, A.nhelp, sa, sb);
         if (A.nhelp < 0) A.prog[0] = (int)acc;     // never taken; keeps the reads
         return;
     }
-    int s = blockIdx.x;
-    int nlev = A.nlev[s], base = A.lbase[s];
     for (int i = threadIdx.x; i < 2 * R; i += Sweep<T>::wg) ring[i] = (T)0;
     if (threadIdx.x == 0) count = 0;
-    int sa = A.soff[base], sb = A.soff[base + nlev];
     __syncthreads();
     int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned lane = threadIdx.x & 63;
@@ -1402,6 +1425,15 @@ __global__ void k_sweep_cols(int ns, const int *lbase, const int *nlevs, const i
         int need = FWD ? soff[base + L] - sa : (sb - sa) + (sb - soff[base + L + 1]);
         meta[sl] = make_int4(need, w[sl], xb[sl], wlong[sl] | (any ? 1 << 31 : 0));
     }
+}
+
+// Prefetch workgroups per subdomain: as many as fit beside the sweeps, one
+// workgroup per CU (a grid of whole rounds of 8 XCDs).  One alone does not keep
+// up and delays the end: 128 subdomains at 2M cells 285 us with one each, 259
+// with none; 64: 280 us with three each, 329 with none.
+static int helpers(int ns, int most) {
+    int h = std::min(most, 256 / ((ns + 7) / 8 * 8) - 1);
+    return h > 1 ? h : 0;
 }
 
 // ----------------------------------------------------------------- set-up
@@ -1567,8 +1599,8 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
     R2P_HIP(hipMemsetAsync(D.ldiag.p, 0xff, sizeof(int) * (size_t)nle, s));
     R2P_HIP(hipMemsetAsync(D.xptr.p + npos, 0, sizeof(int), s));
     F.ldiag = D.ldiag.p; F.xptr = D.xptr.p; F.xl = nullptr;
-    F.prog = D.prog.p; F.ns = ns;
-    F.nhelp = ns % 8 == 0 ? std::max(0, std::min(BHELP, 256 / ns - 1)) : 0;
+    F.prog = D.prog.p; F.ns = ns; F.nsp = (ns + 7) / 8 * 8;
+    F.nhelp = helpers(ns, BHELP);
     k_bilu_gather<<<np, BS, 0, s>>>(F);
     R2P_LAUNCH();
     // positions of wells and perforated cells (the level queue is free again)
@@ -1586,7 +1618,7 @@ int r2p_ras_setup(r2p_cpr *P, hipStream_t s) {
         k_bilu_sym_well<<<256, 256, 0, s>>>(F, wlist, nwlist, 1);
         R2P_LAUNCH();
     }
-    k_bilu0<<<ns * (1 + F.nhelp), BWG, 0, s>>>(F);
+    k_bilu0<<<F.nhelp ? F.nsp * (1 + F.nhelp) : ns, BWG, 0, s>>>(F);
     R2P_LAUNCH();
     // the vectors' unused positions are read too: they start from zero
     const bool f32 = P->o.precision == R2P_FP32;
@@ -1651,11 +1683,15 @@ static int ras_solve_t(r2p_cpr *P, const double *r, double *out, const double *x
     A.mL = D.meta_l.p; A.mU = D.meta_u.p;
     A.lcol = D.lsw.p; A.ucol = D.usw.p;
     A.lval = F.lval.p; A.uval = F.uval.p; A.dinv = F.dinv.p; A.rl = rl; A.y = y;
-    A.ns = ns;
+    A.ns = ns; A.nsp = (ns + 7) / 8 * 8;
     A.prog = D.prog.p;
-    // helpers only where they fit beside the sweeps and share their XCDs
-    A.nhelp = ns % 8 == 0 ? std::max(0, std::min(MAX_HELP, 256 / ns - 1)) : 0;
-    k_ras_sweep<T><<<ns * (1 + A.nhelp), Sweep<T>::wg, 0, s>>>(A);
+    A.nhelp = helpers(ns, MAX_HELP);
+    // what the subdomains of an XCD have read ahead shares its 4 MB of L2: 128
+    // slices are 0.8 MB in FP64, 256 in FP32.  FP32 with 128 instead of 256, 2M
+    // cells: 64 subdomains 185 us instead of 196, 4 subdomains 1,511 instead of
+    // 1,473 (FP64 with 64 instead of 128: 744 instead of 559 at 16)
+    A.ahead = sizeof(T) == 4 && ns <= 16 ? 256 : 128;
+    k_ras_sweep<T><<<A.nhelp ? A.nsp * (1 + A.nhelp) : ns, Sweep<T>::wg, 0, s>>>(A);
     R2P_LAUNCH();
     k_ras_scatter<T><<<nb, BS, 0, s>>>(mtot, P->J->m->ph.n, P->rs.glob_nat.p, P->rs.owned_nat.p,
                                        D.pos.p, y, xp,
