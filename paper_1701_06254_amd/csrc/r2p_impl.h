@@ -227,6 +227,7 @@ struct RasDyn {
     DBuf<int> counters;                   // scratch
     DBuf<int> prog;                       // ns: slice a sweep is at, read by the prefetch helpers
     DBuf<int> swin;                       // ns: ring window of every subdomain's sweep
+    DBuf<double> zeros;                   // main entries' blocks of a slice, all zero
     RasFactors<double> f64;
     RasFactors<float> f32;
 };
