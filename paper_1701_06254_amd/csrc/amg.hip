@@ -941,16 +941,70 @@ static int dense_inverse(r2p_cpr *P, const AmgLevel &C, hipStream_t s) {
     return 0;
 }
 
+// ------------------------------------------------------- fused coarse levels
+// Levels of up to FUSE_ROWS rows form the residual and its restriction in one
+// kernel and the prolongation in the post-smoothing kernel: there a kernel is
+// mostly its launch and a few dependent loads (3 to 4.5 us), so two kernels a
+// level instead of four win, although the chains of loads get longer.  A cycle
+// at 243,107 cells and five levels below: 182 us unfused, 171 with all levels
+// fused (its largest, 82,086 rows, takes the same either way).  At 2M cells
+// fusing the levels of 780,824 and 259,434 rows as well makes a solve 7%
+// slower: such levels are bound by memory, and a fused kernel reads the rows
+// in the order of the aggregates and gathers two vectors.
+//
+// A workgroup of the fused residual and restriction takes its members 64 at a
+// time and rows longer than HEAVY four at a time, about 0.9 us each; where some
+// workgroup has more than FUSE_STEPS such steps (k_fuse_steps), or an aggregate
+// more than FEW members, the two run apart.  Levels of the benchmark's kind have
+// up to 5 (4.5 to 8 us; apart 6 to 9 and a launch); hubs left by one matching
+// round: 8,462 rows with an aggregate of 882 members 32 us, apart 8.
+constexpr int FUSE_ROWS = 1 << 15;
+constexpr int FUSE_STEPS = 5;
+constexpr int CB = 256 / BIG;    // coarse rows of a workgroup of k_down_restrict
+
+// Sets *slow (a pinned word) if a workgroup of k_down_restrict would take more
+// than FUSE_STEPS steps.
+__global__ __launch_bounds__(256) void k_fuse_steps(int nc, int nbs, const int *rp, const int *mptr,
+                                                    const int *mem, const int *big, int *slow) {
+    __shared__ int heavy, members;
+    const int tid = threadIdx.x;
+    int a, b, steps = 0;             // this thread's members: a, a + 256, .. below b
+    if ((int)blockIdx.x < nbs) {
+        int I = blockIdx.x * CB + tid / BIG;
+        a = I < nc ? mptr[I] : 0;
+        b = I < nc ? mptr[I + 1] : 0;
+        if (b - a > BIG) b = a;
+        a += tid % BIG;
+    } else {
+        int I = big[(int)blockIdx.x - nbs];
+        a = mptr[I] + tid;
+        b = mptr[I + 1];
+    }
+    for (bool more = true; more; a += 256) {
+        if (tid == 0) heavy = members = 0;
+        __syncthreads();
+        if (a < b) {
+            int i = mem[a];
+            atomicAdd(&members, 1);
+            if (rp[i + 1] - rp[i] > HEAVY) atomicAdd(&heavy, 1);
+        }
+        more = __syncthreads_or(a + 256 < b);
+        steps += (members + 63) / 64 + (heavy + 3) / 4;
+        __syncthreads();
+    }
+    if (tid == 0 && steps > FUSE_STEPS) *slow = 1;
+}
+
 // --------------------------------------------------------------- set-up
 // Everything runs in order on one stream; the host waits only where it
 // needs a count (the scans that return totals) and for the final status.
-// The pinned word that kernels set for a list or row of more than FEW entries
-// (beside the one that takes the scans' totals), cleared; the stream is idle for
-// it when the host has waited for a scan.
+// Pinned words that kernels set, cleared (beside the one that takes the scans'
+// totals): [0] for a list or row of more than FEW entries, [1] see k_fuse_steps.
+// They are the host's to read once it has waited for a later scan.
 static int hub_word(r2p_cpr *P, volatile int *&hub) {
     R2P_TRY(P->apin.ensure(64));
     hub = (volatile int *)P->apin.p + 8;
-    *hub = 0;
+    hub[0] = hub[1] = 0;
     return 0;
 }
 
@@ -1185,9 +1239,16 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
         R2P_TRY(hub_word(P, hub));
         R2P_TRY(build_members(P, A.n, A.agg.p, nc, A.mptr, A.mem, P->aws.i[0], P->aws.i[1], hub, s));
         R2P_TRY(long_rows(P, nc, A.mptr.p, BIG, A.big, &A.nbig, s));
-        A.hub = *hub != 0;
-        if (A.hub) R2P_TRY(sort_members(P, A.n, A.agg.p, nc, A.mem, s));
+        A.split = A.n > FUSE_ROWS || *hub != 0;
+        if (*hub) R2P_TRY(sort_members(P, A.n, A.agg.p, nc, A.mem, s));
+        if (l > 0 && !A.split) {
+            int nbs = r2p_blocks(nc, CB);
+            k_fuse_steps<<<nbs + A.nbig, 256, 0, s>>>(nc, nbs, A.rp.p, A.mptr.p, A.mem.p, A.big.p,
+                                                      (int *)hub + 1);
+            R2P_LAUNCH();
+        }
         R2P_TRY(long_rows(P, nc, C.rp.p, HEAVY, C.heavy, &C.nheavy, s));
+        A.split |= hub[1] != 0;
         l++;
     }
     P->nlev = l + 1;
@@ -1252,18 +1313,6 @@ int r2p_amg_setup(r2p_cpr *P, hipStream_t s) {
 // row reads is formed beforehand: the pre-smoothed x = b / d by the
 // restriction that produces b, and the prolonged x + P xc by a pass over the
 // fine rows, so each entry costs one gather.
-
-// Levels of up to FUSE_ROWS rows form the residual and its restriction in one
-// kernel and the prolongation in the post-smoothing kernel: there a kernel is
-// mostly its launch and a few dependent loads (3 to 4.5 us), so two kernels a
-// level instead of four win, although the chains of loads get longer.  A cycle
-// at 243,107 cells and five levels below: 182 us unfused, 171 with all levels
-// fused (its largest, 82,086 rows, takes the same either way).  At 2M cells
-// fusing the levels of 780,824 and 259,434 rows as well makes a solve 7%
-// slower: such levels are bound by memory, and a fused kernel reads the rows
-// in the order of the aggregates and gathers two vectors.  Nor are levels with an
-// aggregate of more than FEW members, whose rows one workgroup would take.
-constexpr int FUSE_ROWS = 1 << 15;
 
 template <class T>
 struct CsrArgs {
@@ -1415,7 +1464,6 @@ __global__ __launch_bounds__(256) void k_restrict(int nc, int nbs, const int *mp
 // wavefront) and adds them per coarse row in k_restrict's order.  An
 // aggregate of more than BIG members takes a workgroup of its own, 256
 // members at a time.
-constexpr int CB = 256 / BIG;
 template <class T>
 __device__ __forceinline__ void member_residuals(const CsrArgs<T> &A, const int *list, int cnt, T *res,
                                                  int *heavy, int *nheavy) {
@@ -1846,8 +1894,7 @@ struct Cycle {
         AmgLevel &C = P->lv[c + 1];
         const bool kc = c < P->o.kcycle && c + 1 < nl - 1;
         const bool smooth = c + 1 < nl - 1;
-        const bool fuse = A.n <= FUSE_ROWS && !A.hub;
-        if (fuse) {
+        if (!A.split) {
             int nbs = r2p_blocks(C.n, CB);
             k_down_restrict<T><<<nbs + A.nbig, BS, 0, s>>>(
                 csr(A, vx(A), nullptr), C.n, nbs, A.mptr.p, A.mem.p, A.big.p, vb(C),
@@ -1858,7 +1905,7 @@ struct Cycle {
             R2P_TRY(csr_launch<CSR_DOWN>(A, vx(A), vxo(A)));
             R2P_TRY(restrict_to(c));
         }
-        if (!fuse || kc) {
+        if (A.n > FUSE_ROWS || kc) {
             R2P_TRY(correct(c));
             return csr_launch<CSR_UP>(A, vx(A), out);
         }

@@ -247,7 +247,7 @@ struct AmgLevel {
     DBuf<int> mptr, mem;     // next level's member lists (n_next+1, n)
     DBuf<int> big;           // next-level rows with many members (restricted by a wavefront)
     int nbig = 0;
-    bool hub = false;        // some next-level row has more members than a list compares (FEW)
+    bool split = true;       // residual and restriction run as two kernels (see FUSE_ROWS)
     DBuf<int> heavy;         // rows with many entries (smoothed by a wavefront)
     int nheavy = 0;
     DBuf<double> v7;         // level 0 only: A_pp in the 7-slot stencil layout (slot-major)
