@@ -1612,39 +1612,40 @@ __global__ void k_up0(Level0<T> A, const T *x, double *xo) {
 // column read by 64 lanes is contiguous).  A workgroup of CS_WAVES
 // wavefronts covers 64 rows; wavefront w sums its quarter of the columns,
 // then the quarters are added in wavefront order.  A few workgroups in all, so
-// bound by load latency: b is staged in LDS and CS_COLS columns are in flight
-// (412 rows: 12.3 us with 8 in flight and up to 7 left over one at a time, 8
-// so).
+// bound by load latency: b is staged in LDS and COLS columns are in flight, a
+// power of two that covers a wavefront's quarter up to 64 (412 rows: 12.3 us with
+// 8 in flight and up to 7 left over one at a time, 8 with 64; 15 rows: 2.7 with
+// 8, 4.6 with 64, most of them past the matrix).
 constexpr int CS_WAVES = 4;
-constexpr int CS_COLS = 64;
-template <class T>
+template <class T, int COLS>
 __global__ __launch_bounds__(64 * CS_WAVES, 1) void k_coarse_solve(int n, const double *invT,
                                                                    const T *b, const double *f,
                                                                    int fstride, T *x, double *xd) {
     __shared__ double part[CS_WAVES][64];
-    __shared__ double rhs[CS_WAVES][4096 / CS_WAVES + CS_COLS];   // n is at most 4,096
+    // n is at most 4,096, and 4 COLS below 64
+    __shared__ double rhs[CS_WAVES][COLS < 64 ? 2 * COLS : 4096 / CS_WAVES + COLS];
     int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int i = blockIdx.x * 64 + lane;
     int q = (n + CS_WAVES - 1) / CS_WAVES;
     int c0 = w * q, cnt = min(n, c0 + q) - c0;
     int ii = i < n ? i : n - 1;
     // the wavefront's part of b, zeros behind it
-    for (int c = lane; c < cnt + CS_COLS; c += 64)
+    for (int c = lane; c < cnt + COLS; c += 64)
         rhs[w][c] = c < cnt ? (f ? f[(long)fstride * (c0 + c)] : (double)b[c0 + c]) : 0.0;
     // written by some lanes, read by others of the same wavefront, whose LDS
     // operations keep order
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    double s = 0.0, v[CS_COLS];
+    double s = 0.0, v[COLS];
     const double *col = invT + (long)c0 * n;
-    for (int c = 0; c < cnt; c += CS_COLS) {
+    for (int c = 0; c < cnt; c += COLS) {
 #pragma unroll
-        for (int u = 0; u < CS_COLS; u++) {
+        for (int u = 0; u < COLS; u++) {
             v[u] = col[ii];
             col += c + u + 1 < cnt ? n : 0;
         }
         __builtin_amdgcn_sched_barrier(0);    // all loads first
 #pragma unroll
-        for (int u = 0; u < CS_COLS; u++) s += v[u] * rhs[w][c + u];
+        for (int u = 0; u < COLS; u++) s += v[u] * rhs[w][c + u];
     }
     part[w][lane] = s;
     __syncthreads();
@@ -1845,6 +1846,19 @@ struct Cycle {
         R2P_LAUNCH();
         return 0;
     }
+    // x = A_c^-1 b on the coarsest level, b in vb(C) or, stride fstride, in f.
+    int coarse_solve(AmgLevel &C, const double *f, int fstride, T *x, double *xd) {
+        const int q = (C.n + CS_WAVES - 1) / CS_WAVES;       // columns of a wavefront
+#define R2P_CS(COLS) \
+    k_coarse_solve<T, COLS><<<r2p_blocks(C.n, 64), 64 * CS_WAVES, 0, s>>>(C.n, P->cinv.p, vb(C), f, fstride, x, xd)
+        if (q <= 8) R2P_CS(8);
+        else if (q <= 16) R2P_CS(16);
+        else if (q <= 32) R2P_CS(32);
+        else R2P_CS(64);
+#undef R2P_CS
+        R2P_LAUNCH();
+        return 0;
+    }
     // The coarse correction of level l, added to level l's iterate vx(l).
     int correct(int l) {
         AmgLevel &A = P->lv[l], &C = P->lv[l + 1];
@@ -1886,10 +1900,7 @@ struct Cycle {
     int coarse(int c, T *out) {
         AmgLevel &A = P->lv[c];
         if (c == nl - 1) {
-            k_coarse_solve<T><<<r2p_blocks(A.n, 64), 64 * CS_WAVES, 0, s>>>(
-                A.n, P->cinv.p, vb(A), nullptr, 1, out, nullptr);
-            R2P_LAUNCH();
-            return 0;
+            return coarse_solve(A, nullptr, 1, out, nullptr);
         }
         AmgLevel &C = P->lv[c + 1];
         const bool kc = c < P->o.kcycle && c + 1 < nl - 1;
@@ -1920,10 +1931,7 @@ struct Cycle {
     int run(const double *f, int fstride, double *xp) {
         if (nl == 1) {
             AmgLevel &C = P->lv[0];
-            k_coarse_solve<T><<<r2p_blocks(C.n, 64), 64 * CS_WAVES, 0, s>>>(
-                C.n, P->cinv.p, vb(C), f, fstride, vx(C), xp);
-            R2P_LAUNCH();
-            return 0;
+            return coarse_solve(C, f, fstride, vx(C), xp);
         }
         const Phys &ph = P->J->m->ph;
         Level0<T> Z;
