@@ -112,3 +112,45 @@ def test_weight_gradient_over_several_tiles(shape):
                              cnn.conv_grad_weight(np.abs(g), np.abs(x))):
         err = np.abs(got.cpu().numpy().astype(np.float64) - ref.reshape(-1))
         assert np.all(err <= chain * 2.0 ** -24 * mag.reshape(-1))
+
+
+# columns of 4, 8 and 16 rows by the grid's extent in y, and cross-sections
+# (ny = 1), which run as one plane of nz rows with two axes of taps exchanged
+THIN = [(2, 5, 1, 40), (1, 17, 1, 16), (3, 9, 1, 7), (1, 4, 1, 15), (1, 33, 1, 33), (1, 2, 1, 1),
+        (2, 3, 2, 17), (1, 3, 4, 20), (1, 5, 5, 17), (2, 2, 8, 16), (1, 3, 9, 18)]
+
+
+@pytest.mark.parametrize("flip", [False, True])
+@pytest.mark.parametrize("shape", THIN)
+def test_layer_on_thin_grids(shape, flip):
+    test_layer_at_column_edges(shape, flip)
+
+
+@pytest.mark.parametrize("shape", [(2, 12, 1, 21), (1, 6, 4, 9), (1, 1, 8, 30)])
+def test_cross_section_network_matches_its_transpose(shape):
+    """A grid with the y and z axes exchanged and the weights' taps with them
+    is the same problem: the forward pass agrees to FP32 rounding of each
+    layer's sums (BF16 activations may then round the other way: 2^-8 of the
+    largest output a layer, five layers here)."""
+    from oracle import cnn
+    from paper_1701_06254_amd import r2p
+    nb, nz, ny, nx = shape
+    K = 1
+    theta = cnn.bf16_round(cnn.init_params(np.random.default_rng(3), 32, K, out_scale=1.0)).astype(np.float32)
+    f = np.zeros(shape + (32,))
+    f[..., :6] = np.random.default_rng(4).normal(size=shape + (6,))
+    swapped, o = theta.copy(), 0
+    for l in range(2 * K + 2):
+        cin, cout = 6 if l == 0 else 32, 2 if l == 2 * K + 1 else 32
+        m = 27 * cin * cout
+        W = theta[o:o + m].reshape(3, 3, 3, cout, cin)
+        swapped[o:o + m] = np.ascontiguousarray(W.transpose(1, 0, 2, 3, 4)).reshape(-1)
+        o += m + cout
+    assert o == theta.size
+    out = []
+    for th, a, sh in ((theta, f, shape), (swapped, f.transpose(0, 2, 1, 3, 4), (nb, ny, nz, nx))):
+        net = r2p.Cnn(blocks=K)
+        net.set_params(th)
+        out.append(net.forward(_bits(np.ascontiguousarray(a))[0], sh).cpu().numpy().reshape(sh + (2,)))
+    ref = out[1].transpose(0, 2, 1, 3, 4)
+    assert np.max(np.abs(out[0] - ref)) <= 5 * 2.0 ** -8 * np.max(np.abs(ref))
